@@ -200,9 +200,10 @@ phx_status phx_create(const phx_config *cfg, const phx_fields *fields, void *hip
  * enqueued asynchronously; runs of graph_steps steps are captured once into a
  * hipGraph (on a private stream of default priority) and replayed on the caller's
  * stream, the rest is launched directly (also while kernel timing is on).
- * RK45: attempts Dormand-Prince steps until n_steps are accepted; each attempt
- * reads its error norm back to the host, so the call synchronizes the stream once
- * per attempt.  n_steps >= 0.  *out_or_null receives
+ * RK45: attempts Dormand-Prince steps until n_steps are accepted; each attempt (one
+ * launch; stage by stage with PHX_KERNEL_STAGE, with the drive, while kernel timing is
+ * on, for states of 2 GiB and more, and for two reservoirs in complex128) reads its
+ * error norm back to the host, so the call synchronizes the stream once per attempt.  n_steps >= 0.  *out_or_null receives
  * the progress when not NULL (for RK4 without waiting for the device).
  * PHX_ENONFINITE is returned by the first call that finds the device-side
  * non-finite flag set by an earlier step; PHX_EDTMIN when RK45 cannot meet the

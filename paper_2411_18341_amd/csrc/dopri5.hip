@@ -13,9 +13,17 @@
 // pass sums the partials in a fixed order; the host reads the norm, accepts or
 // rejects, and adapts dt.  After an attempt the next attempt starts from a
 // pointwise kernel that forms y_2 from the state and K_1.
+//
+// These stage kernels run on request (PHX_KERNEL_STAGE), while kernel timing is on (it
+// reports each stage), with the coherent drive, for reservoirs of two components in
+// complex128 and for states of 2 GiB and more; all other attempts take the
+// whole-attempt walk of dp_walk.h (one launch, same steps bit for bit).
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
+#include "dp_walk.h"
 #include "runtime.h"
 #include "stencil.h"
 
@@ -188,13 +196,19 @@ __global__ __launch_bounds__(256) void dp_restart_kernel(const DpArgs<R> a, int 
     if (RES) a.yn_out[o] = a.n[o] + a.ca[0] * a.kn[0][o];
 }
 
-// Fixed-order sum of the per-workgroup error partials: one workgroup.
+// Fixed-order sum of the error partials: one workgroup.  Eight running sums per thread
+// keep eight loads in flight (the partials were just written by other XCDs); the order
+// of the additions depends on the count alone.  `out` is the handle's pinned host word,
+// so the host reads the norm right after the stream has been waited for, without a copy.
 __global__ __launch_bounds__(256) void dp_err_sum_kernel(const double* __restrict__ partials, int blocks,
                                                          double* __restrict__ out)
 {
     __shared__ double lds[4];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < blocks; b += 256) s += partials[b];
+    double r[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int b = threadIdx.x; b < blocks; b += 8 * 256)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) r[k] += b + 256 * k < blocks ? partials[b + 256 * k] : 0.0;
+    double s = ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
     s = wave_sum_d(s);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
     __syncthreads();
@@ -258,7 +272,6 @@ struct DpBuffers {
     char* alt;
     char* alt_n;
     double* partials;
-    double* err;
 };
 
 static DpBuffers dp_buffers(const phx_handle* h)
@@ -279,7 +292,6 @@ static DpBuffers dp_buffers(const phx_handle* h)
         b.alt_n = nb + 9 * rb;
     }
     b.partials = (double*)(h->ws + L.err);
-    b.err = (double*)(h->ws + L.obs);  // the observables slot doubles as the norm output
     return b;
 }
 
@@ -294,9 +306,95 @@ static void dp_slots(int fsal, int (&slot)[7])
     }
 }
 
-template <typename R>
-static phx_status dp_attempt(phx_handle* h, double dt, bool need_k1, double* err_out)
+// Sums `count` partials into the pinned host word, waits for the stream and forms the
+// error norm of the attempt.
+static phx_status dp_error_norm(phx_handle* h, const double* partials, int count, double* err_out)
 {
+    double* word = &h->host[OBS_SLOTS + 1];
+    hipEvent_t t0 = nullptr;
+    hipError_t e = timing_begin(h, &t0);
+    if (e == hipSuccess) {
+        dp_err_sum_kernel<<<1, 256, 0, h->stream>>>(partials, count, word);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = timing_end(h, t0, K_DP_ERR);
+    if (e != hipSuccess) return fail(PHX_EHIP, "Dormand-Prince error sum: %s", hipGetErrorString(e));
+    HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+    const int64_t cells = (int64_t)h->cfg.nx * h->cfg.ny * h->cfg.components;
+    const double real_unknowns = 2.0 * cells + (h->cfg.reservoir ? (double)cells : 0.0);
+    *err_out = sqrt(*(volatile const double*)word / real_unknowns);
+    return PHX_OK;
+}
+
+// Whether an attempt of this handle runs as the one-launch walk: 32-bit buffer offsets
+// (the state under 2 GiB), no drive (its profile would need a ring of its own), and not
+// the two-component reservoirs in complex128, whose K_s in flight exceed the register
+// file.  With kernel timing on the stages run one by one, so that each is timed.
+static bool dp_use_walk(const phx_handle* h)
+{
+    const phx_config& c = h->cfg;
+    if (c.kernel == PHX_KERNEL_STAGE || c.drive || h->timing) return false;
+    if (c.precision == PHX_C128 && c.components == 2 && c.reservoir) return false;
+    return (double)complex_bytes(h) < 2147483648.0 - 256.0;
+}
+
+// Rows per band: the smallest height whose bands, one wave each, fit on the device at
+// once (taller bands read and evaluate fewer of the 14 halo rows), at least 4.
+static int dp_band_rows(const phx_handle* h, int strips)
+{
+    const phx_config& c = h->cfg;
+    auto rows = [&](bool skip) {
+        const int wpe = dp_waves_per_simd(c.precision == PHX_C64, c.components, c.reservoir != 0, h->f.V != nullptr, skip);
+        const int bands = std::max(1, h->cus * 4 * wpe / strips);
+        return std::max(4, (c.ny + bands - 1) / bands);
+    };
+    const int tall = rows(false);
+    return tall < kDpSkipRows ? rows(true) : tall;
+}
+
+template <typename R>
+static phx_status dp_walk_attempt(phx_handle* h, double dt, double* err_out)
+{
+    using C = typename cvec<R>::type;
+    const phx_config& c = h->cfg;
+    DpWalkArgs<R> a{};
+    a.nx = c.nx;
+    a.ny = c.ny;
+    a.bcx = c.bc_x;
+    a.bcy = c.bc_y;
+    a.strips = (c.nx + kDpCols - 1) / kDpCols;
+    a.band_rows = dp_band_rows(h, a.strips);
+    a.tiles = a.strips * ((c.ny + a.band_rows - 1) / a.band_rows);
+    a.c = make_coef<R>(c);
+    a.psi = (const C*)h->cur;
+    a.n = (const R*)h->cur_n;
+    a.V = (const R*)h->f.V;
+    a.P = (const R*)h->f.P;
+    a.psi_out = (C*)h->other;
+    a.n_out = (R*)h->other_n;
+    for (int s = 1; s <= 6; ++s)
+        for (int j = 0; j < s; ++j) a.ca[s - 1][j] = (R)(dt * DP_A[s][j]);
+    for (int j = 0; j < 7; ++j) a.ce[j] = (R)(dt * (DP_B[j] - DP_BHAT[j]));
+    a.rtol = c.rtol;
+    a.atol = c.atol;
+    a.partials = (double*)(h->ws + h->L.k[0]);  // the K arrays of the stage kernels are unused here
+    hipError_t e;
+    if constexpr (sizeof(R) == 4)
+        e = c.components == 1 ? launch_dp_walk<float, 1>(c.reservoir != 0, a, h->stream)
+                              : launch_dp_walk<float, 2>(c.reservoir != 0, a, h->stream);
+    else
+        e = c.components == 1 ? launch_dp_walk<double, 1>(c.reservoir != 0, a, h->stream)
+                              : launch_dp_walk<double, 2>(c.reservoir != 0, a, h->stream);
+    if (e != hipSuccess) return fail(PHX_EHIP, "Dormand-Prince step: %s", hipGetErrorString(e));
+    h->k1_valid = false;  // the walk leaves no K_7 behind for the stage kernels
+    return dp_error_norm(h, a.partials, a.tiles, err_out);
+}
+
+template <typename R>
+static phx_status dp_attempt(phx_handle* h, double dt, double* err_out)
+{
+    if (dp_use_walk(h)) return dp_walk_attempt<R>(h, dt, err_out);
+    const bool need_k1 = !h->k1_valid;
     using C = typename cvec<R>::type;
     const phx_config& c = h->cfg;
     const DpBuffers b = dp_buffers(h);
@@ -374,18 +472,9 @@ static phx_status dp_attempt(phx_handle* h, double dt, bool need_k1, double* err
         if (e == hipSuccess) e = timing_end(h, t0, K_DP_S1 + s - 1);
         if (e != hipSuccess) return fail(PHX_EHIP, "Dormand-Prince stage %d: %s", s, hipGetErrorString(e));
     }
-    e = timing_begin(h, &t0);
-    if (e == hipSuccess) {
-        dp_err_sum_kernel<<<1, 256, 0, h->stream>>>(b.partials, a.tiles, b.err);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = timing_end(h, t0, K_DP_ERR);
-    if (e != hipSuccess) return fail(PHX_EHIP, "Dormand-Prince error sum: %s", hipGetErrorString(e));
-    HIP_OR_FAIL(hipMemcpyAsync(&h->host[OBS_SLOTS + 1], b.err, sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIP_OR_FAIL(hipStreamSynchronize(h->stream));
-    const double real_unknowns = 2.0 * cells + (res ? (double)cells : 0.0);
-    *err_out = sqrt(h->host[OBS_SLOTS + 1] / real_unknowns);
-    return PHX_OK;
+    const phx_status st = dp_error_norm(h, b.partials, a.tiles, err_out);
+    if (st == PHX_OK) h->k1_valid = true;  // K_1 of the current state now sits in slot fsal
+    return st;
 }
 
 phx_status create_rk45(phx_handle* h)
@@ -428,10 +517,8 @@ phx_status step_rk45(phx_handle* h, int64_t n, phx_info* out)
             break;
         }
         double err = 0.0;
-        st = c.precision == PHX_C64 ? dp_attempt<float>(h, dt, !h->k1_valid, &err)
-                                    : dp_attempt<double>(h, dt, !h->k1_valid, &err);
+        st = c.precision == PHX_C64 ? dp_attempt<float>(h, dt, &err) : dp_attempt<double>(h, dt, &err);
         if (st != PHX_OK) break;
-        h->k1_valid = true;  // K_1 of the current state now sits in slot fsal
         if (h->att_log && *h->att_count >= 0 && *h->att_count < h->att_cap) {
             double* e = h->att_log + 3 * *h->att_count;
             e[0] = dt;

@@ -123,6 +123,9 @@ ObsArgs<R> obs_args(const phx_config& c, const TilePlan& tiles, const void* psi,
 void obs_from_slots(const phx_config& c, const double* q, phx_obs* out);
 const void* state_n(const phx_handle* h);
 phx_status create_rk45(phx_handle* h);
+// Whole-attempt Dormand-Prince walk (dp_walk.h).
+template <typename R> struct DpWalkArgs;
+template <typename R, int COMPS> hipError_t launch_dp_walk(bool res, const DpWalkArgs<R>& a, hipStream_t s);
 template <typename R> phx_status rk4_fused_steps(phx_handle* h, int64_t n);
 template <typename R> phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s);
 template <typename R> phx_status rk4_stage_launches(phx_handle* h, int64_t n, hipStream_t s);

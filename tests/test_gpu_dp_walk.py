@@ -1,0 +1,95 @@
+"""The one-launch Dormand-Prince walk against the oracle and the stage kernels.
+
+One step of a given size is the same arithmetic on both paths, so they may differ by
+the rounding of a few operations only (20 units in the last place in relative L2);
+against the oracle the tolerances of the other parity tests hold.  Sizes: strip seams
+(50 output columns), grids below one strip and one band, ragged bands, and a grid tall
+enough for bands of 64 rows and more (the variant that leaves no stage out)."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import C64, C128, TOL, GpuRun, oracle_physics, quantize, rel_l2
+from paper_2411_18341_amd import inputs, phx
+
+pytestmark = pytest.mark.gpu
+
+EPS = {C64: 2.0 ** -24, C128: 2.0 ** -53}
+
+
+def case(components, reservoir, has_v, nx, ny, bc, seed=0):
+    rng = np.random.default_rng(900 + seed)
+    ph = inputs.Physics(nx=nx, ny=ny, dx=0.1, dy=0.12, bc_x=bc[0], bc_y=bc[1], components=components,
+                        reservoir=reservoir, g=1.0, g_x=-0.1 if components == 2 else 0.0,
+                        delta_lt=0.1 if components == 2 else 0.0, g_r=0.02 if reservoir else 0.0,
+                        R=0.01 if reservoir else 0.0, gamma_c=0.15, gamma_r=0.225 if reservoir else 0.0, dt=1e-3)
+    shape = (components, ny, nx)
+    psi = inputs.random_state(shape, seed + 3, 0.5)
+    V = rng.standard_normal((ny, nx)) if has_v else None
+    n = rng.uniform(0, 5, shape) if reservoir else None
+    P = rng.uniform(0, 3, shape) if reservoir else None
+    return ph, psi, n, V, P
+
+
+def one_step(ph, q, precision, kernel):
+    run = GpuRun(ph, *q, precision=precision, integrator=phx.PHX_RK45, rtol=1.0, atol=1.0, dt=ph.dt, kernel=kernel)
+    info = run.step(1)
+    psi, n = run.state()
+    run.close()
+    assert info["steps_accepted"] == 1 and info["t"] == ph.dt
+    return psi, n, info["dt"]
+
+
+@pytest.mark.parametrize("precision", [C64, C128])
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1), (0, 1), (1, 0)])
+@pytest.mark.parametrize("kind", [(1, False, False), (1, False, True), (1, True, False), (1, True, True),
+                                  (2, False, False), (2, False, True), (2, True, True)])
+def test_walk_edges(kind, bc, precision):
+    for nx, ny in ((50, 4), (51, 5), (101, 33), (49, 1), (7, 5), (1, 9), (64, 70)):
+        ph, *fields = case(*kind, nx, ny, bc, seed=nx)
+        q = quantize(precision, *fields)
+        psi, n, dt = one_step(ph, q, precision, phx.PHX_KERNEL_AUTO)
+        s_psi, s_n, s_dt = one_step(ph, q, precision, phx.PHX_KERNEL_STAGE)
+        o_psi, o_n, _, _ = oracle.dopri5_step(oracle_physics(ph), *q, dt=ph.dt)
+        assert dt == s_dt  # both at the controller's bound
+        assert rel_l2(psi, s_psi) <= 20 * EPS[precision] and rel_l2(psi, o_psi) <= TOL[precision], (nx, ny)
+        if ph.reservoir:
+            assert rel_l2(n, s_n) <= 20 * EPS[precision] and rel_l2(n, o_n) <= TOL[precision], (nx, ny)
+
+
+@pytest.mark.parametrize("precision", [C64, C128])
+@pytest.mark.parametrize("kind,nx,ny", [((1, True, False), 2001, 1801), ((2, False, True), 1999, 3500)])
+def test_walk_tall_bands(kind, nx, ny, precision):
+    """Bands of 64 rows and more on a ragged grid, on every cell against the stage kernels;
+    the error norms of two attempts agree to the rounding of their sums."""
+    ph, *fields = case(*kind, nx, ny, (1, 0), seed=5)
+    q = quantize(precision, *fields)
+    psi, n, _ = one_step(ph, q, precision, phx.PHX_KERNEL_AUTO)
+    s_psi, s_n, _ = one_step(ph, q, precision, phx.PHX_KERNEL_STAGE)
+    assert rel_l2(psi, s_psi) <= 20 * EPS[precision]
+    assert n is None or rel_l2(n, s_n) <= 20 * EPS[precision]
+    errs = []
+    for kernel in (phx.PHX_KERNEL_AUTO, phx.PHX_KERNEL_STAGE):
+        run = GpuRun(ph, *q, precision=precision, integrator=phx.PHX_RK45, rtol=1e-3, atol=1e-3, dt=ph.dt, kernel=kernel)
+        run.solver.log_attempts(2)
+        run.step(1)
+        errs.append(run.solver.attempts()[0, 1])
+        run.close()
+    assert abs(errs[0] / errs[1] - 1.0) <= (1e-6 if precision == C64 else 1e-10)
+
+
+def test_walk_and_stage_kernels_take_turns():
+    """Kernel timing runs the stages one by one; switching it on and off in a run (the
+    walk leaves no K_7 for the stage kernels) keeps the trajectory."""
+    ph, *fields = case(2, False, True, 120, 77, (1, 1), seed=9)
+    q = quantize(C128, *fields)
+    out = []
+    for switch in (False, True):
+        run = GpuRun(ph, *q, precision=C128, integrator=phx.PHX_RK45, rtol=1e-5, atol=1e-5, dt=ph.dt)
+        for k in range(4):
+            run.solver.set_timing(switch and k % 2 == 1)
+            info = run.step(2)
+        out.append((run.state()[0], info["t"]))
+        run.close()
+    assert abs(out[0][1] / out[1][1] - 1) <= 1e-10
+    assert rel_l2(out[0][0], out[1][0]) <= 1e-9
