@@ -11,11 +11,14 @@ Metric: grid-point RK4 updates per second, U = Nx Ny steps / seconds (Sec. 4 of
 the paper).  The timed steps are replays of one captured hipGraph (the solver's
 default way of stepping; the graph is captured after the warmup, outside the timed
 region).  Printed as one JSON line together with
-  roofline      the dominant kernel's algorithmic bytes per launch over its mean
-                launch time, from a separate pass of direct launches bracketed by
-                HIP events on the solver's stream, against 8 TB/s; traffic = HBM
-                bytes per launch from rocprofv3 counters when a measurement for the
-                current kernel source is on file;
+  roofline      the dominant kernel's mean launch time from a separate pass of direct
+                launches bracketed by HIP events on the solver's stream.  The kernel that
+                takes two steps per launch is bound by its VALU issue: its flops (without
+                those of halo cells) over that time, against the FP32 vector rate without
+                packed instructions.  The others are held against HBM: algorithmic bytes
+                per launch over the time, against 8 TB/s; traffic = HBM bytes per launch
+                from rocprofv3 counters when a measurement for the current kernel source
+                is on file;
   copy_kernel_GBps  the library's streaming copy kernel on a 1 GiB buffer (read +
                 write bytes over HIP-event time): the attainable-bandwidth reference;
   walk_pattern  (complex64 with the reservoir) the step kernel's bytes moved in the
@@ -39,6 +42,11 @@ sys.path.insert(0, ROOT)
 
 METRIC = "grid-point RK4 updates/s + HBM GB/s at 4096² c64; surrogate vs plain at L2 1e-3"
 HBM_PEAK_GBPS = 8000.0
+# FP32 vector rate without packed instructions: 256 CUs x 4 SIMDs x 16 lanes x 2 flops x 2.4 GHz
+VALU_PEAK_TFLOPS = 78.6
+# flops of one grid-point update of the driven equation in the whole-step kernels (FMA = 2):
+# 163 = 4 stages x 40.75 (16.5 FMA, 3 multiplications, 4.75 additions each on average)
+FLOPS_PER_UPDATE = 163
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "rk4_traffic.json")
 COPY_BYTES = 1 << 30
 
@@ -271,7 +279,7 @@ def main():
     if E is not None:  # the whole-step kernel reads the drive profile once per step
         step_model = {"step": step_model["step"] + 2 * real_bytes}
     per_launch = {f"rk4_stage{s}": stage_model[f"stage{s}"] for s in range(1, 5)}
-    per_launch["rk4_step"] = step_model["step"]
+    per_launch["rk4_step"] = per_launch["rk4_step_pair"] = step_model["step"]
     per_launch["wiener_noise"] = bytemodel.wiener_noise(real_bytes, reservoir=True)
     per_launch["imag_norm"] = bytemodel.imag_norm(real_bytes)["norm"]
     per_launch["imag_scale"] = bytemodel.imag_norm(real_bytes)["scale"]
@@ -297,8 +305,17 @@ def main():
                 "frac": round(d["GBps"] / HBM_PEAK_GBPS, 4), "traffic": traffic,
                 "kernel": shape_key, "bytes_per_launch": d["bytes_per_launch"],
                 "avg_launch_us": round(d["avg_us"], 2)}
-    family_name = "whole-step (1 launch per step)" if dom == "rk4_step" else "stage-fused (4 launches per step)"
-    step_bytes = step_model["step"] if dom == "rk4_step" else stage_model["step"]
+    if dom == "rk4_step_pair":
+        tflops = 2 * FLOPS_PER_UPDATE * cells / (d["avg_us"] * 1e-6) / 1e12
+        roofline = {"bound": "valu", "achieved": round(tflops, 2), "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
+                    "frac": round(tflops / VALU_PEAK_TFLOPS, 4), "traffic": traffic, "kernel": shape_key,
+                    "steps_per_launch": 2, "flops_per_launch": 2 * FLOPS_PER_UPDATE * cells,
+                    "bytes_per_launch": d["bytes_per_launch"], "GBps": round(d["GBps"], 1),
+                    "avg_launch_us": round(d["avg_us"], 2)}
+    family_name = {"rk4_step": "whole-step (1 launch per step)",
+                   "rk4_step_pair": "whole-step (1 launch per two steps)"}.get(dom, "stage-fused (4 launches per step)")
+    step_bytes = {"rk4_step": step_model["step"],
+                  "rk4_step_pair": step_model["step"] / 2}.get(dom, stage_model["step"])
     if args.noise > 0:
         step_bytes += per_launch["wiener_noise"]
     if args.imag:
@@ -310,7 +327,8 @@ def main():
         wus = walk_pattern_us(torch, psi, n, Pd)
         walk = {"us": round(wus, 2), "GBps": round(step_model["step"] * cells / (wus * 1e-6) / 1e9, 1),
                 "band_rows": "the 8-row ring's device-filling height",
-                "step_kernel_over_pattern": round(d["avg_us"] / wus, 3) if dom == "rk4_step" else None}
+                "step_kernel_over_pattern": round(d["avg_us"] / (2 if dom == "rk4_step_pair" else 1) / wus, 3)
+                if dom in ("rk4_step", "rk4_step_pair") else None}
 
     cpu = None
     if not args.no_cpu_baseline:

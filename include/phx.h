@@ -91,7 +91,9 @@ typedef struct phx_config {
     int32_t tile_rows;      /* rows per wave (stage-fused: 1..64); streaming form: rows per
                                band (40, 64, 88, 112); wide streaming form: rows per band
                                (8..4096), or 0 for the height that fills the device with
-                               one wave per band; streaming forms need a state under 2 GiB;
+                               one wave per band (2 x 0 then takes two steps per launch where
+                               neither noise, drive nor imaginary time comes between them);
+                               streaming forms need a state under 2 GiB;
                                0 with tile_wx 0 = automatic                                 */
     int32_t graph_steps;    /* RK4 steps per captured hipGraph chunk replayed by phx_step:
                                0 = default (64), < 0 = launch every kernel directly        */
@@ -269,8 +271,8 @@ typedef struct phx_tune_result {
     int32_t family;         /* PHX_KERNEL_STAGE or PHX_KERNEL_STEP                         */
     int32_t tile_wx, tile_rows;  /* adopted shape                                         */
     int32_t candidates;     /* shapes timed                                               */
-    double best_us;         /* mean launch time of the adopted shape                      */
-    double default_us;      /* mean launch time of the shape in use before the call      */
+    double best_us;         /* mean time of a step with the adopted shape                 */
+    double default_us;      /* mean time of a step with the shape in use before the call */
 } phx_tune_result;
 
 phx_status phx_autotune(phx_handle *h, int32_t reps, phx_tune_result *out);

@@ -46,8 +46,10 @@ static phx_status tune_step(phx_handle* h, int reps, phx_tune_result* out)
         if (!step_shape_allowed(h->cfg, sh)) continue;
         ++timed;
         double us;
-        phx_status s = time_launches(h, reps, [&](int k) { return rk4_step_trial<R>(h, sh, k); }, &us);
+        int steps = 1;  // of one launch
+        phx_status s = time_launches(h, reps, [&](int k) { return rk4_step_trial<R>(h, sh, k, &steps); }, &us);
         if (s != PHX_OK) return s;
+        us /= steps;
         if (sh.waves == before.waves && sh.rows == before.rows) before_us = us;
         if (us < best_us) {
             best_us = us;

@@ -155,10 +155,11 @@ hipError_t launch_rk4_step(bool reservoir, bool has_v, const StepShapeId& sh, co
     return has_v ? launch_step_shape<R, false, true>(sh, a, s) : launch_step_shape<R, false, false>(sh, a, s);
 }
 
-// Arguments of one whole step from `src` to `dst` (state buffers) with shape sh.
+// Arguments of one whole step (pair: of two) from `src` to `dst` (state buffers) with
+// shape sh.
 template <typename R>
 static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const void* src, const void* src_n,
-                             void* dst, void* dst_n)
+                             void* dst, void* dst_n, bool pair = false)
 {
     using C = typename cvec<R>::type;
     const phx_config& c = h->cfg;
@@ -168,7 +169,11 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
     a.bcx = c.bc_x;
     a.bcy = c.bc_y;
     a.tiles_x = (c.nx + 55) / 56;
-    if (wide_shape(sh.waves)) {  // wide streaming: strips of 120 columns, one wave per band of a strip
+    if (pair) {  // two steps per launch: strips of 112 columns, one wave per band of a strip
+        a.tiles_x = pair_strips(c.nx);
+        a.band_rows = pair_band_rows(c, h->f.V != nullptr, h->cus);
+        a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
+    } else if (wide_shape(sh.waves)) {  // wide streaming: strips of 120 columns, one wave per band of a strip
         a.tiles_x = wide_strips(c.nx);
         a.band_rows = wide_band_rows(c, sh, h->f.V != nullptr, h->cus);
         a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
@@ -205,10 +210,12 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
 // copy; later trials alternate between the two workspace copies, so that each one
 // reads the state the previous one wrote, as real steps do (a launch that re-read one
 // unchanged input would find part of it in the Infinity Cache).  The caller's state
-// is never written.
+// is never written.  *steps is the number of steps of the launch.
 template <typename R>
-hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k)
+hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* steps)
 {
+    const bool pair = pair_steps(h->cfg, sh);
+    *steps = pair ? 2 : 1;
     const bool res = h->cfg.reservoir != 0;
     char* A = h->ws + h->L.alt;
     char* An = res ? h->ws + h->L.alt_n : nullptr;
@@ -216,20 +223,28 @@ hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k)
     char* Bn = res ? h->ws + h->L.alt2_n : nullptr;
     StepArgs<R> a;
     if (k == 0)
-        a = step_args<R>(h, sh, h->f.psi, h->f.n, A, An);
+        a = step_args<R>(h, sh, h->f.psi, h->f.n, A, An, pair);
     else if (k & 1)
-        a = step_args<R>(h, sh, A, An, B, Bn);
+        a = step_args<R>(h, sh, A, An, B, Bn, pair);
     else
-        a = step_args<R>(h, sh, B, Bn, A, An);
+        a = step_args<R>(h, sh, B, Bn, A, An, pair);
+    if constexpr (sizeof(R) == 4) {
+        if (pair) return launch_stream_pair(res, h->f.V != nullptr, a, h->stream);
+    }
     return launch_rk4_step<R>(res, h->f.V != nullptr, sh, a, h->stream);
 }
 
-template hipError_t rk4_step_trial<float>(phx_handle*, const StepShapeId&, int);
-template hipError_t rk4_step_trial<double>(phx_handle*, const StepShapeId&, int);
+template hipError_t rk4_step_trial<float>(phx_handle*, const StepShapeId&, int, int*);
+template hipError_t rk4_step_trial<double>(phx_handle*, const StepShapeId&, int, int*);
+
+// Two-step launches among n steps, so that the launches leave the state where n single
+// steps would: the n - pairs launches are even in number exactly when n is.
+static int64_t pair_launches(int64_t n) { return n & 1 ? (n >= 3 ? 2 * ((n + 1) / 4) - 1 : 0) : 2 * (n / 4); }
 
 // Enqueues n whole steps on stream s, alternating between the caller's arrays
 // (buffer 0) and the workspace copy (buffer 1); h->step_parity is the buffer that
-// holds the state before the first of them.
+// holds the state before the first of them.  With the two-step form an odd n >= 3 ends
+// in the buffer it began in, like an even n.
 template <typename R>
 phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
 {
@@ -239,10 +254,13 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
     const StepShapeId sh = h->step_shape;
     const bool fused_noise = c.noise > 0.0 && noise_in_step(c, sh);
+    int64_t pairs = pair_steps(c, sh) ? pair_launches(n) : 0;
     int cur = h->step_parity;
-    for (int64_t k = 0; k < n; ++k) {
-        StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1]);
-        a.check = k == n - 1;  // the wide form tests the last step of the run (values stay non-finite)
+    for (int64_t k = 0, steps = 1; k < n; k += steps) {
+        const bool pair = pairs-- > 0;
+        steps = pair ? 2 : 1;
+        StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], pair);
+        a.check = k + steps == n;  // the wide forms test the last step of the run (values stay non-finite)
         if (fused_noise) {
             a.noise_step = (const uint64_t*)(h->ws + h->L.noise);
             a.noise_offset = k;
@@ -252,8 +270,13 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
             return fail(PHX_EHIP, "drive phasor launch failed");
         hipEvent_t t0 = nullptr;
         hipError_t e = timing_begin(h, &t0);
-        if (e == hipSuccess) e = launch_rk4_step<R>(res, hv, sh, a, s);
-        if (e == hipSuccess) e = timing_end(h, t0, K_RK4_STEP);
+        if (e == hipSuccess) {
+            if constexpr (sizeof(R) == 4)
+                e = pair ? launch_stream_pair(res, hv, a, s) : launch_rk4_step<R>(res, hv, sh, a, s);
+            else
+                e = launch_rk4_step<R>(res, hv, sh, a, s);
+        }
+        if (e == hipSuccess) e = timing_end(h, t0, pair ? K_RK4_PAIR : K_RK4_STEP);
         if (e != hipSuccess) return fail(PHX_EHIP, "RK4 step kernel launch: %s", hipGetErrorString(e));
         cur ^= 1;
         if (c.imag_time) {  // the scale that restores the norm, applied by the next step
@@ -280,8 +303,9 @@ template phx_status rk4_fused_launches<float>(phx_handle*, int64_t, hipStream_t)
 template phx_status rk4_fused_launches<double>(phx_handle*, int64_t, hipStream_t);
 
 // n whole steps ending in the caller's arrays.  An odd count first copies the state
-// into the workspace and takes one step back; the remaining even count alternates
-// (graph replays of an even chunk start and end in the caller's arrays).
+// into the workspace and takes one step back (not where two-step launches make the
+// number of launches even anyway); the remaining even count alternates (graph replays of
+// an even chunk start and end in the caller's arrays).
 template <typename R>
 phx_status rk4_fused_steps(phx_handle* h, int64_t n)
 {
@@ -289,7 +313,10 @@ phx_status rk4_fused_steps(phx_handle* h, int64_t n)
     const size_t rs = sizeof(R);
     const size_t cells = (size_t)c.nx * c.ny;
     h->step_parity = 0;
-    if (n & 1) {
+    const int G = graph_chunk(c);
+    const int64_t direct = h->timing || G == 0 || n < G ? n : n % G;  // steps after the graph replays
+    const bool pair = pair_steps(c, h->step_shape);
+    if ((n & 1) && !(pair && pair_launches(direct) > 0)) {
         void* alt = h->ws + h->L.alt;
         if (hipMemcpyAsync(alt, h->f.psi, cells * c.components * 2 * rs, hipMemcpyDeviceToDevice, h->stream) !=
                 hipSuccess ||

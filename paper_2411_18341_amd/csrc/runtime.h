@@ -108,7 +108,7 @@ namespace phx {
 // Kernel kinds for phx_kernel_times; names in kernel_kind_name().
 enum KernelKind {
     K_RK4_S1 = 0, K_RK4_S2, K_RK4_S3, K_RK4_S4, K_OBS, K_DP_S1, K_DP_S2, K_DP_S3, K_DP_S4,
-    K_DP_S5, K_DP_S6, K_DP_S7, K_DP_ERR, K_BATCH, K_RK4_STEP, K_NOISE, K_IMAG_NORM, K_IMAG_SCALE, K_KINDS_
+    K_DP_S5, K_DP_S6, K_DP_S7, K_DP_ERR, K_BATCH, K_RK4_STEP, K_NOISE, K_IMAG_NORM, K_IMAG_SCALE, K_RK4_PAIR, K_KINDS_
 };
 const char* kernel_kind_name(int k);
 // Timing brackets around one launch (no-ops unless timing is on).
@@ -131,7 +131,7 @@ template <typename R> phx_status rk4_fused_launches(phx_handle* h, int64_t n, hi
 template <typename R> phx_status rk4_stage_launches(phx_handle* h, int64_t n, hipStream_t s);
 int graph_chunk(const phx_config& c);
 template <typename R> phx_status rk4_run_graph(phx_handle* h, int64_t n);
-template <typename R> hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k);
+template <typename R> hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* steps);
 template <typename R> hipError_t rk4_stage_trial(phx_handle* h, const TileShape& ts);
 int step_shapes(int precision, const StepShapeId** out);
 bool step_shape_fits(const phx_config& c, int waves);
@@ -149,6 +149,13 @@ int wide_strips(int nx);
 int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int cus);
 int wide_waves_per_simd(int ring, bool reservoir, bool has_v, bool ghosts, bool noise);
 hipError_t launch_stream_wide(bool reservoir, bool has_v, int ring, const StepArgs<float>& a, hipStream_t s);
+// Two steps per launch of the wide streaming form (stream_pair.h): whether shape sh runs
+// this way for this configuration, its strips and band height.
+bool pair_steps(const phx_config& c, const StepShapeId& sh);
+StepShapeId default_step_shape(const phx_config& c);
+int pair_strips(int nx);
+int pair_band_rows(const phx_config& c, bool has_v, int cus);
+hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<float>& a, hipStream_t s);
 int rk4_family(const phx_config& c);
 phx_status step_rk45(phx_handle* h, int64_t n, phx_info* out);
 phx_status set_info_rk45(phx_handle* h, const phx_info* in);

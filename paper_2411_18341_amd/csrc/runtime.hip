@@ -5,11 +5,13 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <string>
 
 #include "phx_kernels.h"
 #include "runtime.h"
+#include "stream_pair.h"
 
 namespace phx {
 
@@ -213,6 +215,42 @@ int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int c
     return b < 16 ? 16 : b;
 }
 
+int pair_strips(int nx) { return (nx + kPairCols - 1) / kPairCols; }
+
+// Band height of the two-step form: the smallest whose bands, one wave each, fit on the
+// device at once, rounded up so that the walk's B + 16 rows fill whole chunks of 12
+// positions (20, 32, 44, ...).
+int pair_band_rows(const phx_config& c, bool has_v, int cus)
+{
+    const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
+    const int slots = (cus > 0 ? cus : 256) * 4 * pair_waves_per_simd(c.reservoir != 0, has_v, ghosts);
+    const int bands = std::max(1, slots / pair_strips(c.nx));
+    const int b = (c.ny + bands - 1) / bands;
+    return std::max(20, (b + 16 + 11) / 12 * 12 - 16);
+}
+
+// The wide form whose band height the library chooses runs two steps per launch where
+// nothing has to happen between them (no noise or drive, no norm to restore).  Faster at
+// every size (us per step, driven, one step per launch against two): 92.8 / 59.4 at 4096^2,
+// 31.7 / 20.4 at 2048^2, 12.9 / 12.2 at 1024^2.
+bool pair_steps(const phx_config& c, const StepShapeId& sh)
+{
+    return sh.waves == 2 && sh.rows == 0 && c.components == 1 && !c.drive && !c.imag_time && !(c.noise > 0.0);
+}
+
+// Shape used when the caller names none and does not tune.  The wide form fills the
+// device from about 1450^2 on: 19.5 against 20.3 us per step at 1536^2 (driven; 12.2
+// against 10.4 at 1024^2, 20.4 against 30.9 at 2048^2).
+StepShapeId default_step_shape(const phx_config& c)
+{
+    if (c.imag_time || c.drive || c.components == 2) return StepShapeId{1, 40};  // streaming
+    const StepShapeId wide{2, 0};
+    if ((int64_t)c.nx * c.ny >= ((int64_t)1 << 21) && step_shape_fits(c, wide.waves)) return wide;
+    const StepShapeId* shapes;
+    step_shapes(c.precision, &shapes);
+    return shapes[0];
+}
+
 bool step_shape_allowed(const phx_config& c, const StepShapeId& sh)
 {
     if (!step_shape_fits(c, sh.waves)) return false;
@@ -373,10 +411,7 @@ phx_status phx_create(const phx_config* cfg, const phx_fields* f, void* stream,
     h->cur = f->psi;
     h->stage_tiles = L.tiles;
     {
-        const StepShapeId* shapes;
-        step_shapes(cfg->precision, &shapes);
-        h->step_shape = shapes[0];
-        if (cfg->imag_time || cfg->drive || cfg->components == 2) h->step_shape = StepShapeId{1, 40};  // streaming
+        h->step_shape = default_step_shape(*cfg);
         if (cfg->tile_wx != 0 && L.family == PHX_KERNEL_STEP) h->step_shape = StepShapeId{cfg->tile_wx, cfg->tile_rows};
     }
     if (cfg->integrator == PHX_RK45) {
@@ -767,7 +802,7 @@ const char* kernel_kind_name(int k)
     static const char* names[K_KINDS_] = {
         "rk4_stage1", "rk4_stage2", "rk4_stage3", "rk4_stage4", "observables",
         "dp_stage1", "dp_stage2", "dp_stage3", "dp_stage4", "dp_stage5", "dp_stage6",
-        "dp_stage7", "dp_error", "batch_stage", "rk4_step", "wiener_noise", "imag_norm", "imag_scale"};
+        "dp_stage7", "dp_error", "batch_stage", "rk4_step", "wiener_noise", "imag_norm", "imag_scale", "rk4_step_pair"};
     return (k >= 0 && k < K_KINDS_) ? names[k] : "unknown";
 }
 

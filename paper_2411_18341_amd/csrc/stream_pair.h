@@ -1,0 +1,266 @@
+// Device code of the two-step wide streaming RK4 kernel (complex64, one component): two
+// whole steps of Eqs. rk4_K1-rk4_final in one pass over the state.
+//
+// The band walk of stream_wide.h (two grid columns per lane) with eight stages in the
+// pipeline instead of four: at row j the stages of the first step run at rows j - 1 ..
+// j - 4 and finish row j - 4 of the state in between, which stays in registers; the
+// stages of the second step run at rows j - 5 .. j - 8 on it, and row j - 8 is stored.
+// The state thus moves through HBM once for two steps.  The halo doubles: 8 columns on
+// each side (112 output columns per strip of 128) and B + 16 rows for B output rows.
+// The arithmetic per cell and its order are those of the other whole-step forms, so the
+// results agree bit for bit with two single steps.
+//
+// Stage k = 1..8 of the pipeline starts at position 2 k: no stage after it needs its
+// earlier rows.  The first twelve positions are a copy of the loop body with the stages
+// left out that have not started.  The walk runs in whole chunks of twelve positions (an
+// exit inside a chunk would make every ring slot live to a common end).
+//
+// Bound by the VALU issue: 24.8 instructions per cell and stage, and with the halo (128 x
+// (B + 10) cells evaluated for 112 x B stored) all SIMDs issue back to back: 118.8 us per
+// launch, 59.4 us per step, at 4096^2 driven (B 80, 1924 waves, 2 per SIMD); the one-step
+// wide form takes 92.8 us per step, bound by HBM (28 bytes per point and step).  One
+// wave per SIMD with bands of 152 rows takes 63.6 us, ragged fillings 66 to 95 us.
+#pragma once
+
+#include <type_traits>
+
+#include "stream_wide.h"
+
+namespace phx {
+
+// Waves per SIMD that the registers allow without scratch memory.
+constexpr int pair_waves_per_simd(bool res, bool hasv, bool ghosts)
+{
+    return res ? (hasv ? 1 : 2) : (hasv || ghosts ? 2 : 3);
+}
+
+constexpr int kPairHalo = 8, kPairCols = 128 - 2 * kPairHalo;
+
+// Forms the value here: without this the compiler moves sums that only a later position
+// reads to that position, where their operands then stay live as well.
+__device__ __forceinline__ void keep_here(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void keep_here(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
+// One band of `B` rows of strip `strip`; `finish(bad)` gets whether a stored value is not
+// finite (CHECK; else false without testing).
+template <bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, typename F>
+__device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int strip, int band, int B, int dir, F finish)
+{
+    using C = float2;
+    constexpr int K = 12;  // rows j - 8 .. j + PF of the inputs are in flight
+    constexpr int PF = 3;  // rows loaded ahead of their first use
+    const int lane = threadIdx.x & 63;
+    const Coef<float>& c = a.c;
+    const int gi = strip * kPairCols - kPairHalo + 2 * lane;  // first column of the lane's pair
+    const int ci = wrap_any(gi, a.nx, a.bcx);                  // -1: ghost pair (zero x boundary)
+    const bool gcol = GHOSTS && ci < 0;
+    const float keep = gcol ? 0.f : 1.f;
+    const int b0 = band * B;
+    const float kdiag = 2.f * (c.ax + c.ay);
+    const int row8 = a.nx * 8, row4 = a.nx * 4;
+    const size_t cells = (size_t)a.nx * a.ny;
+    const __amdgpu_buffer_rsrc_t rpi = buffer_of(a.psi_in, cells * 8);
+    const __amdgpu_buffer_rsrc_t rni = buffer_of(a.n_in, RES ? cells * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rP = buffer_of(a.P, RES ? cells * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rV = buffer_of(a.V, HASV ? cells * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rpo = buffer_of(a.psi_out, cells * 8);
+    const __amdgpu_buffer_rsrc_t rno = buffer_of(a.n_out, RES ? cells * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rnull = buffer_of(a.psi_out, 0);  // every access out of range
+    const int v8 = gcol ? kOutOfRange : (ci < 0 ? 0 : ci) * 8;
+    const int v4 = gcol ? kOutOfRange : (ci < 0 ? 0 : ci) * 4;
+    const bool out_col = lane >= kPairHalo / 2 && lane < 64 - kPairHalo / 2 && gi < a.nx;
+    const int o8 = out_col ? gi * 8 : kOutOfRange;
+    const int o4 = out_col ? gi * 4 : kOutOfRange;
+
+    // [step][slot][cell of the pair]; step 0 reads the input, step 1 the state in between
+    C sp[2][K][2], acc[2][4][2], w[2][3][3][2];  // w[.][q]: argument of stage q + 2
+    float sn[2][K][2], accn[2][4][2], wn[2][3][3][2];
+    float sP[K][2], sk[K][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            sP[s][e] = 0.f;
+            sk[s][e] = kdiag;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int s = 0; s < K; ++s) {
+                sp[h][s][e] = czero<C>();
+                sn[h][s][e] = 0.f;
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                acc[h][s][e] = czero<C>();
+                accn[h][s][e] = 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) {
+                    w[h][q][s][e] = czero<C>();
+                    wn[h][q][s][e] = 0.f;
+                }
+        }
+    }
+
+    const int npos = B + 2 * kPairHalo;
+    const int start = dir > 0 ? b0 - kPairHalo : b0 + B - 1 + kPairHalo;
+    int g = start;
+    int rw = wrap_any(g, a.ny, a.bcy);
+    auto fetch = [&](int s, bool use) __attribute__((always_inline)) {
+        const int rr = rw < 0 ? 0 : rw;
+        const wf4 v = wload4(rpi, v8, rr * row8);
+        if (YZERO) {
+            const float rk = rw < 0 ? 0.f : 1.f;
+            sp[0][s][0] = C{rk * v.x, rk * v.y};
+            sp[0][s][1] = C{rk * v.z, rk * v.w};
+        } else {
+            sp[0][s][0] = C{v.x, v.y};
+            sp[0][s][1] = C{v.z, v.w};
+        }
+        if (RES) {
+            const wf2 nv = wload2(rni, v4, rr * row4);
+            const wf2 pv = wload2(rP, v4, rr * row4);
+            sn[0][s][0] = nv.x;
+            sn[0][s][1] = nv.y;
+            sP[s][0] = pv.x;
+            sP[s][1] = pv.y;
+        }
+        if (HASV) {
+            const wf2 vv = wload2(rV, v4, rr * row4);
+            sk[s][0] = fmaf(c.inv_hbar, vv.x, kdiag);
+            sk[s][1] = fmaf(c.inv_hbar, vv.y, kdiag);
+        }
+        const int gn = g + dir;
+        int rn;
+        if (YZERO) {
+            rn = (gn >= 0 && gn < a.ny) ? gn : -1;
+        } else {
+            rn = rw + dir;
+            rn = rn == a.ny ? 0 : (rn < 0 ? a.ny - 1 : rn);
+        }
+        g = use ? gn : g;
+        rw = use ? rn : rw;
+    };
+#pragma unroll
+    for (int t = 0; t < PF; ++t) fetch(t, true);
+
+    unsigned bad = 0u;
+    auto positions = [&](auto phase, int base) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(phase)::value;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int j = start + dir * (base + u);        // newest row of this position
+            fetch(slot<K>(u, -PF), base + u + PF < npos);  // row j + PF
+            // Row j arrives: its values leave the four- and two-register groups that the
+            // loads write (kept there for their whole life they fragment the register file).
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int q = slot<K>(u, 0);
+                keep_here(sp[0][q][e]);
+                if (RES) {
+                    keep_here(sn[0][q][e]);
+                    keep_here(sP[q][e]);
+                }
+                if (HASV) keep_here(sk[q][e]);
+            }
+#pragma unroll
+            for (int k = 1; k <= 8; ++k) {
+                if (FIRST && u < 2 * k) continue;
+                const int h = (k - 1) / 4, s = (k - 1) % 4 + 1;  // step and its stage
+                const int q = slot<K>(u, k);                     // ring slot of row j - k
+                const int m = slot<3>(u, k), a4 = slot<4>(u, k);
+                const int r = j - k * dir;
+                // argument rows: the state itself in stage 1, else the stage argument
+                C cur[2], up[2], dn[2];
+                float nn[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    if (s == 1) {
+                        cur[e] = sp[h][q][e];
+                        up[e] = sp[h][slot<K>(u, k + 1)][e];
+                        dn[e] = sp[h][slot<K>(u, k - 1)][e];
+                        nn[e] = sn[h][q][e];
+                    } else {
+                        cur[e] = w[h][s - 2][m][e];
+                        up[e] = w[h][s - 2][slot<3>(u, k + 1)][e];
+                        dn[e] = w[h][s - 2][slot<3>(u, k - 1)][e];
+                        nn[e] = wn[h][s - 2][m][e];
+                    }
+                }
+                // neighbours in x: the pair's other cell and the adjacent lane's
+                const C lr[2] = {C{lane_prev(cur[1].x) + cur[1].x, lane_prev(cur[1].y) + cur[1].y},
+                                 C{cur[0].x + lane_next(cur[0].x), cur[0].y + lane_next(cur[0].y)}};
+                __builtin_amdgcn_sched_barrier(0);
+                const float kk = YZERO ? ((unsigned)r >= (unsigned)a.ny ? 0.f : keep) : keep;
+                float y[4], yn[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    float fx, fy, fn;
+                    cell_rhs<float, RES>(c, cur[e], lr[e].x, lr[e].y, up[e].x + dn[e].x, up[e].y + dn[e].y, nn[e],
+                                         sP[q][e], sk[q][e], fx, fy, fn);
+                    C& ac = acc[h][a4][e];
+                    float& an = accn[h][a4][e];
+                    const C p0 = sp[h][q][e];
+                    const float n0 = sn[h][q][e];
+                    if (s < 4) {
+                        const float step = s == 3 ? a.dt : a.half_dt;
+                        ac = s == 1 ? C{fx, fy} : C{fmaf(2.f, fx, ac.x), fmaf(2.f, fy, ac.y)};
+                        an = s == 1 ? fn : fmaf(2.f, fn, an);
+                        w[h][s - 1][m][e] = C{kk * fmaf(step, fx, p0.x), kk * fmaf(step, fy, p0.y)};
+                        wn[h][s - 1][m][e] = kk * fmaf(step, fn, n0);
+                        keep_here(ac);
+                        keep_here(w[h][s - 1][m][e]);
+                        if (RES) {
+                            keep_here(an);
+                            keep_here(wn[h][s - 1][m][e]);
+                        }
+                    } else {
+                        y[2 * e] = fmaf(a.dt6, ac.x + fx, p0.x);
+                        y[2 * e + 1] = fmaf(a.dt6, ac.y + fy, p0.y);
+                        yn[e] = fmaf(a.dt6, an + fn, n0);
+                        if (h == 0) {  // the state in between (0 in ghost cells)
+                            sp[1][q][e] = C{kk * y[2 * e], kk * y[2 * e + 1]};
+                            sn[1][q][e] = kk * yn[e];
+                            keep_here(sp[1][q][e]);
+                            if (RES) keep_here(sn[1][q][e]);
+                        }
+                    }
+                }
+                if (k == 8) {
+                    // issued at every position (no branch); a row outside the band goes to
+                    // a descriptor of size 0, whose stores are dropped
+                    const bool st = r >= b0 && r < b0 + B && r < a.ny;  // uniform
+                    const int rr = st ? r : 0;
+                    wstore4(wf4{y[0], y[1], y[2], y[3]}, st ? rpo : rnull, o8, rr * row8);
+                    if (RES) wstore2(wf2{yn[0], yn[1]}, st ? rno : rnull, o4, rr * row4);
+                    if (CHECK) {
+                        unsigned nf = (unsigned)!isfinite(y[0]) | (unsigned)!isfinite(y[1]) |
+                                      (unsigned)!isfinite(y[2]) | (unsigned)!isfinite(y[3]);
+                        if (RES) nf |= (unsigned)!isfinite(yn[0]) | (unsigned)!isfinite(yn[1]);
+                        bad |= (st && out_col) ? nf : 0u;
+                    }
+                }
+            }
+        }
+    };
+    positions(std::true_type{}, 0);
+    for (int base = K; base < npos; base += K) positions(std::false_type{}, base);
+    finish(bad != 0u);
+}
+
+template <bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
+void rk4_stream_pair_kernel(const StepArgs<float> a)
+{
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    const int band = t / a.tiles_x, strip = t - band * a.tiles_x;
+    stream_band_pair<RES, HASV, GHOSTS, YZERO, CHECK>(a, strip, band, a.band_rows, (band & 1) ? -1 : 1,
+                                                         [&](bool bad) __attribute__((always_inline)) {
+                                                             if (bad) a.flag[0] = 1u;  // benign race
+                                                         });
+}
+
+}  // namespace phx

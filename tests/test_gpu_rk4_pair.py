@@ -1,0 +1,92 @@
+"""Two RK4 steps per launch (the wide form with the library's band height).
+
+The same arithmetic per cell as the other whole-step forms, so the state equals the
+region form's bit for bit: over strip seams (112 output columns), bands of 20 rows,
+grids narrower than a strip's halo, every boundary mix, with and without reservoir and
+potential, and for every remainder of the step count (pairs, single steps, graph
+replays, an odd count that needs a copy)."""
+import numpy as np
+import pytest
+
+from gpu_helpers import C64, GpuRun, quantize
+from paper_2411_18341_amd import build, inputs, phx
+
+gpu = pytest.mark.gpu
+
+
+def case(nx, ny, bc, reservoir, has_v, seed=0):
+    rng = np.random.default_rng(700 + seed)
+    ph = inputs.Physics(nx=nx, ny=ny, dx=0.2, dy=0.25, bc_x=bc[0], bc_y=bc[1], reservoir=reservoir, g=0.01,
+                        g_r=0.02 if reservoir else 0.0, R=0.01 if reservoir else 0.0, gamma_c=0.15,
+                        gamma_r=0.225 if reservoir else 0.0, dt=0.02)
+    psi = inputs.random_state((1, ny, nx), seed, 0.5)
+    n = rng.uniform(0, 5, (1, ny, nx)) if reservoir else None
+    P = rng.uniform(0, 3, (1, ny, nx)) if reservoir else None
+    V = rng.standard_normal((ny, nx)) if has_v else None
+    return ph, quantize(C64, psi, n, V, P)
+
+
+def states(ph, q, tile, calls, graph_steps=0):
+    run = GpuRun(ph, *q, precision=C64, kernel=phx.PHX_KERNEL_STEP, tile_wx=tile[0], tile_rows=tile[1],
+                 graph_steps=graph_steps)
+    out = []
+    for k in calls:
+        run.step(k)
+        out.append(run.state())
+    run.close()
+    return out
+
+
+def same(a, b):
+    return all(np.array_equal(p[0], q[0]) and (p[1] is None or np.array_equal(p[1], q[1])) for p, q in zip(a, b))
+
+
+@gpu
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1), (0, 1), (1, 0)])
+@pytest.mark.parametrize("reservoir", [False, True])
+@pytest.mark.parametrize("has_v", [False, True])
+def test_pair_edges(has_v, reservoir, bc):
+    for nx, ny in ((112, 20), (114, 21), (110, 19), (226, 41), (336, 33), (2, 1), (2, 7), (8, 3), (16, 50), (128, 64)):
+        ph, q = case(nx, ny, bc, reservoir, has_v, seed=nx)
+        calls = (4, 3)
+        assert same(states(ph, q, (8, 4), calls), states(ph, q, (2, 0), calls)), (nx, ny)
+
+
+@gpu
+@pytest.mark.parametrize("graph_steps", [-1, 2, 4, 6])
+def test_pair_step_counts(graph_steps):
+    ph, q = case(300, 150, (0, 1), True, False, seed=3)
+    calls = (1, 2, 3, 4, 5, 6, 7, 9, 13, 4, 1, 3)
+    assert same(states(ph, q, (8, 4), calls, graph_steps), states(ph, q, (2, 0), calls, graph_steps))
+
+
+@gpu
+def test_pair_reports_nonfinite():
+    ph, q = case(240, 60, (0, 0), True, False, seed=4)
+    q[0][0, 30, 100] = np.nan
+    run = GpuRun(ph, *q, precision=C64, kernel=phx.PHX_KERNEL_STEP, tile_wx=2, tile_rows=0)
+    run.step(4)
+    assert run.observables()["nonfinite"] > 0
+    with pytest.raises(phx.PhxError):
+        run.step(1)
+    run.close()
+
+
+@gpu
+@pytest.mark.parametrize("nx,ny", [(1450, 1450), (1452, 1446), (1451, 1450)])
+def test_default_shape_bitwise(nx, ny):
+    """Around the size from which the default is the wide form (even widths)."""
+    ph, q = case(nx, ny, (0, 0), True, False, seed=6)
+    run = GpuRun(ph, *q, precision=C64)
+    run.step(5)
+    default = [run.state()]
+    run.close()
+    assert same(states(ph, q, (8, 4), (5,)), default)
+
+
+@pytest.mark.parametrize("unit", ["rk4_stream_pair.hip", "dp_walk_d1.hip"])
+def test_wide_stores_keep_their_data(unit):
+    """No store of more than 64 bits has its data rewritten by the next instruction."""
+    asm = build.device_asm(unit)
+    assert "buffer_store_dwordx4" in asm
+    assert build.store_data_hazards(asm) == []
