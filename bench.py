@@ -240,8 +240,10 @@ def main():
     Pd = None if P is None else torch.from_numpy(P).to(dtype=rdt, device=dev).contiguous()
     Vd = None if V0 is None else torch.from_numpy(V0).to(dtype=rdt, device=dev).contiguous()
     family = {"auto": phx.PHX_KERNEL_AUTO, "stage": phx.PHX_KERNEL_STAGE, "step": phx.PHX_KERNEL_STEP}[args.kernel]
-    # the timed steps are replays of one captured graph of G steps (G even, dividing K)
-    G = next((g for g in range(min(64, args.steps), 1, -1) if g % 2 == 0 and args.steps % g == 0), 0)
+    # the timed steps are replays of one captured graph of G steps (G even, dividing K; a
+    # multiple of 4 where there is one, so that all its launches take two steps)
+    chunks = [g for g in range(min(64, args.steps), 1, -1) if g % 2 == 0 and args.steps % g == 0]
+    G = next((g for g in chunks if g % 4 == 0), chunks[0] if chunks else 0)
     cfg = phx.config_from_physics(ph, precision=precision, kernel=family, noise=args.noise, seed=1,
                                   drive=E is not None, drive_omega=args.drive or 0.0, imag_time=args.imag,
                                   graph_steps=G if G else -1)

@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libphx.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["rk4_step.hip", "rk4_stream_spinor_res_f40.hip", "rk4_stream_spinor_res_f64.hip", "rk4_stream_spinor_res_d40.hip", "rk4_stream_spinor_res_d64.hip", "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip", "rk4_stream_spinor_drive_d.hip", "runtime.hip", "rk4.hip", "reduce.hip", "dopri5.hip", "batch.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive.hip", "rk4_stream_spinor.hip", "rk4_stream_wide.hip", "rk4_stream_pair.hip", "dp_walk_f1.hip", "dp_walk_f2.hip", "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip"]
+SOURCES = ["rk4_step.hip", "rk4_stream_spinor_res_f40.hip", "rk4_stream_spinor_res_f64.hip", "rk4_stream_spinor_res_d40.hip", "rk4_stream_spinor_res_d64.hip", "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip", "rk4_stream_spinor_drive_d.hip", "runtime.hip", "rk4.hip", "reduce.hip", "dopri5.hip", "batch.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive.hip", "rk4_stream_spinor.hip", "rk4_stream_wide.hip", "rk4_stream_pair_f2.hip", "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip", "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip"]
 
 ARCH = "gfx950"
 FLAGS = [
@@ -38,7 +38,7 @@ EXTRA_FLAGS = {f"rk4_stream_spinor{t}.hip": _FULL_UNROLL
 # the wide walk with the Wiener increment drawn at its final store (a generator call
 # per position) likewise exceeds the default limit
 EXTRA_FLAGS["rk4_stream_wide.hip"] = _FULL_UNROLL
-EXTRA_FLAGS["rk4_stream_pair.hip"] = _FULL_UNROLL
+EXTRA_FLAGS.update({f"rk4_stream_pair_{t}.hip": _FULL_UNROLL for t in ("f2", "f1", "d1")})
 EXTRA_FLAGS.update({f"dp_walk_{t}.hip": _FULL_UNROLL for t in ("f1", "f2", "d1", "d2")})
 # Units whose streaming kernels are checked for private (scratch) memory: a ring
 # that is not in registers makes the walk several times slower.

@@ -155,11 +155,20 @@ hipError_t launch_rk4_step(bool reservoir, bool has_v, const StepShapeId& sh, co
     return has_v ? launch_step_shape<R, false, true>(sh, a, s) : launch_step_shape<R, false, false>(sh, a, s);
 }
 
-// Arguments of one whole step (pair: of two) from `src` to `dst` (state buffers) with
+template <typename R>
+static hipError_t launch_pair(int columns, bool res, bool hv, const StepArgs<R>& a, hipStream_t s)
+{
+    if constexpr (sizeof(R) == 4) {
+        if (columns == 2) return launch_stream_pair<R, 2>(res, hv, a, s);
+    }
+    return launch_stream_pair<R, 1>(res, hv, a, s);
+}
+
+// Arguments of one whole step (pair > 0: of two) from `src` to `dst` (state buffers) with
 // shape sh.
 template <typename R>
 static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const void* src, const void* src_n,
-                             void* dst, void* dst_n, bool pair = false)
+                             void* dst, void* dst_n, int pair = 0)
 {
     using C = typename cvec<R>::type;
     const phx_config& c = h->cfg;
@@ -169,9 +178,9 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
     a.bcx = c.bc_x;
     a.bcy = c.bc_y;
     a.tiles_x = (c.nx + 55) / 56;
-    if (pair) {  // two steps per launch: strips of 112 columns, one wave per band of a strip
-        a.tiles_x = pair_strips(c.nx);
-        a.band_rows = pair_band_rows(c, h->f.V != nullptr, h->cus);
+    if (pair) {  // two steps per launch, `pair` columns per lane: one wave per band of a strip
+        a.tiles_x = pair_strips(c.nx, pair);
+        a.band_rows = pair_band_rows(c, pair, h->f.V != nullptr, h->cus);
         a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
     } else if (wide_shape(sh.waves)) {  // wide streaming: strips of 120 columns, one wave per band of a strip
         a.tiles_x = wide_strips(c.nx);
@@ -214,7 +223,7 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
 template <typename R>
 hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* steps)
 {
-    const bool pair = pair_steps(h->cfg, sh);
+    const int pair = pair_columns(h->cfg, sh);
     *steps = pair ? 2 : 1;
     const bool res = h->cfg.reservoir != 0;
     char* A = h->ws + h->L.alt;
@@ -228,9 +237,7 @@ hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* step
         a = step_args<R>(h, sh, A, An, B, Bn, pair);
     else
         a = step_args<R>(h, sh, B, Bn, A, An, pair);
-    if constexpr (sizeof(R) == 4) {
-        if (pair) return launch_stream_pair(res, h->f.V != nullptr, a, h->stream);
-    }
+    if (pair) return launch_pair<R>(pair, res, h->f.V != nullptr, a, h->stream);
     return launch_rk4_step<R>(res, h->f.V != nullptr, sh, a, h->stream);
 }
 
@@ -254,12 +261,13 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
     const StepShapeId sh = h->step_shape;
     const bool fused_noise = c.noise > 0.0 && noise_in_step(c, sh);
-    int64_t pairs = pair_steps(c, sh) ? pair_launches(n) : 0;
+    const int columns = pair_columns(c, sh);
+    int64_t pairs = columns ? pair_launches(n) : 0;
     int cur = h->step_parity;
     for (int64_t k = 0, steps = 1; k < n; k += steps) {
         const bool pair = pairs-- > 0;
         steps = pair ? 2 : 1;
-        StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], pair);
+        StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], pair ? columns : 0);
         a.check = k + steps == n;  // the wide forms test the last step of the run (values stay non-finite)
         if (fused_noise) {
             a.noise_step = (const uint64_t*)(h->ws + h->L.noise);
@@ -270,12 +278,7 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
             return fail(PHX_EHIP, "drive phasor launch failed");
         hipEvent_t t0 = nullptr;
         hipError_t e = timing_begin(h, &t0);
-        if (e == hipSuccess) {
-            if constexpr (sizeof(R) == 4)
-                e = pair ? launch_stream_pair(res, hv, a, s) : launch_rk4_step<R>(res, hv, sh, a, s);
-            else
-                e = launch_rk4_step<R>(res, hv, sh, a, s);
-        }
+        if (e == hipSuccess) e = pair ? launch_pair<R>(columns, res, hv, a, s) : launch_rk4_step<R>(res, hv, sh, a, s);
         if (e == hipSuccess) e = timing_end(h, t0, pair ? K_RK4_PAIR : K_RK4_STEP);
         if (e != hipSuccess) return fail(PHX_EHIP, "RK4 step kernel launch: %s", hipGetErrorString(e));
         cur ^= 1;
@@ -315,8 +318,7 @@ phx_status rk4_fused_steps(phx_handle* h, int64_t n)
     h->step_parity = 0;
     const int G = graph_chunk(c);
     const int64_t direct = h->timing || G == 0 || n < G ? n : n % G;  // steps after the graph replays
-    const bool pair = pair_steps(c, h->step_shape);
-    if ((n & 1) && !(pair && pair_launches(direct) > 0)) {
+    if ((n & 1) && !(pair_columns(c, h->step_shape) && pair_launches(direct) > 0)) {
         void* alt = h->ws + h->L.alt;
         if (hipMemcpyAsync(alt, h->f.psi, cells * c.components * 2 * rs, hipMemcpyDeviceToDevice, h->stream) !=
                 hipSuccess ||

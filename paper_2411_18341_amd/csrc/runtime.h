@@ -149,13 +149,15 @@ int wide_strips(int nx);
 int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int cus);
 int wide_waves_per_simd(int ring, bool reservoir, bool has_v, bool ghosts, bool noise);
 hipError_t launch_stream_wide(bool reservoir, bool has_v, int ring, const StepArgs<float>& a, hipStream_t s);
-// Two steps per launch of the wide streaming form (stream_pair.h): whether shape sh runs
-// this way for this configuration, its strips and band height.
-bool pair_steps(const phx_config& c, const StepShapeId& sh);
+// Two steps per launch of the streaming forms (stream_pair.h): the columns per lane with
+// which shape sh runs this way for this configuration (0: it takes single steps), the
+// strips and the band height.
+int pair_columns(const phx_config& c, const StepShapeId& sh);
 StepShapeId default_step_shape(const phx_config& c);
-int pair_strips(int nx);
-int pair_band_rows(const phx_config& c, bool has_v, int cus);
-hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<float>& a, hipStream_t s);
+int pair_strips(int nx, int w);
+int pair_band_rows(const phx_config& c, int w, bool has_v, int cus);
+template <typename R, int W>
+hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
 int rk4_family(const phx_config& c);
 phx_status step_rk45(phx_handle* h, int64_t n, phx_info* out);
 phx_status set_info_rk45(phx_handle* h, const phx_info* in);

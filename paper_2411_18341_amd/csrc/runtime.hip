@@ -215,40 +215,64 @@ int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int c
     return b < 16 ? 16 : b;
 }
 
-int pair_strips(int nx) { return (nx + kPairCols - 1) / kPairCols; }
+int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
 
-// Band height of the two-step form: the smallest whose bands, one wave each, fit on the
-// device at once, rounded up so that the walk's B + 16 rows fill whole chunks of 12
-// positions (20, 32, 44, ...).
-int pair_band_rows(const phx_config& c, bool has_v, int cus)
+// Band height of the two-step form with w columns per lane: the smallest whose bands, one
+// wave each, fit on the device at once, rounded up so that the walk's B + 16 rows fill
+// whole chunks of 12 positions (20, 32, 44, ...).
+int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 {
     const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
-    const int slots = (cus > 0 ? cus : 256) * 4 * pair_waves_per_simd(c.reservoir != 0, has_v, ghosts);
-    const int bands = std::max(1, slots / pair_strips(c.nx));
+    const int words = w * (c.precision == PHX_C64 ? 1 : 2);
+    const int slots = (cus > 0 ? cus : 256) * 4 * pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts);
+    const int bands = std::max(1, slots / pair_strips(c.nx, w));
     const int b = (c.ny + bands - 1) / bands;
     return std::max(20, (b + 16 + 11) / 12 * 12 - 16);
 }
 
-// The wide form whose band height the library chooses runs two steps per launch where
-// nothing has to happen between them (no noise or drive, no norm to restore).  Faster at
-// every size (us per step, driven, one step per launch against two): 92.8 / 59.4 at 4096^2,
-// 31.7 / 20.4 at 2048^2, 12.9 / 12.2 at 1024^2.
-bool pair_steps(const phx_config& c, const StepShapeId& sh)
+// Two steps per launch where nothing has to happen between them (no noise or drive, no norm
+// to restore): the wide form whose band height the library chooses, with two columns per
+// lane, and the one-column form with tall bands (1 x 64; the two-step walk picks its own
+// height).  Faster than single steps at every size.  us per step, driven, one against two
+// steps per launch: wide 92.8 / 59.4 at 4096^2, 31.7 / 20.4 at 2048^2, 12.9 / 12.2 at
+// 1024^2; one column, complex64 115.7 / 72.6 at 4095^2, 22.6 / 11.9 at 1023^2; complex128
+// 190.6 / 130.4 at 4096^2, 63.7 / 37.7 at 2047^2, 33.0 / 17.0 at 1023^2.
+int pair_columns(const phx_config& c, const StepShapeId& sh)
 {
-    return sh.waves == 2 && sh.rows == 0 && c.components == 1 && !c.drive && !c.imag_time && !(c.noise > 0.0);
+    if (c.components != 1 || c.drive || c.imag_time || c.noise > 0.0) return 0;
+    if (sh.waves == 2 && sh.rows == 0) return 2;
+    return sh.waves == 1 && sh.rows == 64 ? 1 : 0;
 }
 
-// Shape used when the caller names none and does not tune.  The wide form fills the
-// device from about 1450^2 on: 19.5 against 20.3 us per step at 1536^2 (driven; 12.2
-// against 10.4 at 1024^2, 20.4 against 30.9 at 2048^2).
+// Shape used when the caller names none and does not tune: the region form on grids that
+// its many small workgroups fill better, the walks beyond.  us per step, driven: region
+// 8 x 4 / two steps with one column / with two columns per lane, complex64: 10.4 / 11.9 /
+// 12.2 at 1024^2, 20.5 / 16.2 / 19.5 at 1536^2, 31.0 / 22.7 / 20.4 at 2048^2; complex128
+// (region / one column): 6.4 / 10.7 at 512^2, 23.5 / 17.0 at 1023^2, 75.8 / 37.7 at 2047^2;
+// without the reservoir 15.3 / 16.2 at 1023^2, 27.9 / 23.7 at 1531^2.  With the noise the
+// steps are single: the wide form, which draws the increments itself on periodic grids,
+// saves the separate pass; in complex128 the one-column form takes 62 against 76 us at 2047^2.
 StepShapeId default_step_shape(const phx_config& c)
 {
     if (c.imag_time || c.drive || c.components == 2) return StepShapeId{1, 40};  // streaming
-    const StepShapeId wide{2, 0};
-    if ((int64_t)c.nx * c.ny >= ((int64_t)1 << 21) && step_shape_fits(c, wide.waves)) return wide;
+    const int64_t cells = (int64_t)c.nx * c.ny, k = (int64_t)1 << 18;
+    const bool c64 = c.precision == PHX_C64;
     const StepShapeId* shapes;
     step_shapes(c.precision, &shapes);
-    return shapes[0];
+    const StepShapeId wide{2, 0}, one{1, 64};
+    StepShapeId pick = shapes[0];
+    if (c.noise > 0.0) {
+        if (c64 && cells >= 4 * k && step_shape_fits(c, 2) && noise_in_step(c, wide)) pick = wide;
+        if (!c64 && cells >= 6 * k) pick = StepShapeId{1, 40};
+    } else if (c64) {
+        if (cells >= 14 * k && step_shape_fits(c, 2))
+            pick = wide;
+        else if (cells >= 6 * k)
+            pick = one;
+    } else if (cells >= (c.reservoir ? 3 : 5) * k) {
+        pick = one;
+    }
+    return step_shape_fits(c, pick.waves) ? pick : shapes[0];
 }
 
 bool step_shape_allowed(const phx_config& c, const StepShapeId& sh)

@@ -1,12 +1,13 @@
-// Device code of the two-step wide streaming RK4 kernel (complex64, one component): two
-// whole steps of Eqs. rk4_K1-rk4_final in one pass over the state.
+// Device code of the two-step streaming RK4 kernel (one component): two whole steps of
+// Eqs. rk4_K1-rk4_final in one pass over the state.
 //
-// The band walk of stream_wide.h (two grid columns per lane) with eight stages in the
-// pipeline instead of four: at row j the stages of the first step run at rows j - 1 ..
+// The band walk of stream_wide.h (W = 2 grid columns per lane: complex64 on even widths)
+// or of stream_body.h (W = 1: complex128, odd widths) with eight stages in the pipeline
+// instead of four: at row j the stages of the first step run at rows j - 1 ..
 // j - 4 and finish row j - 4 of the state in between, which stays in registers; the
 // stages of the second step run at rows j - 5 .. j - 8 on it, and row j - 8 is stored.
 // The state thus moves through HBM once for two steps.  The halo doubles: 8 columns on
-// each side (112 output columns per strip of 128) and B + 16 rows for B output rows.
+// each side (112 output columns per strip of 128, 48 of 64) and B + 16 rows for B output rows.
 // The arithmetic per cell and its order are those of the other whole-step forms, so the
 // results agree bit for bit with two single steps.
 //
@@ -28,59 +29,65 @@
 
 namespace phx {
 
-// Waves per SIMD that the registers allow without scratch memory.
-constexpr int pair_waves_per_simd(bool res, bool hasv, bool ghosts)
+// Waves per SIMD that the registers allow without scratch memory; words = 32-bit words of
+// the lane's real values per row (2: two complex64 columns or one complex128 column).
+constexpr int pair_waves_per_simd(int words, bool res, bool hasv, bool ghosts)
 {
+    if (words == 1) return res && hasv ? 3 : 4;
     return res ? (hasv ? 1 : 2) : (hasv || ghosts ? 2 : 3);
 }
 
-constexpr int kPairHalo = 8, kPairCols = 128 - 2 * kPairHalo;
+constexpr int kPairHalo = 8;
+constexpr int pair_cols(int w) { return 64 * w - 2 * kPairHalo; }  // output columns per strip
 
 // Forms the value here: without this the compiler moves sums that only a later position
 // reads to that position, where their operands then stay live as well.
 __device__ __forceinline__ void keep_here(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void keep_here(double& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void keep_here(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+__device__ __forceinline__ void keep_here(double2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 
 // One band of `B` rows of strip `strip`; `finish(bad)` gets whether a stored value is not
 // finite (CHECK; else false without testing).
-template <bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, typename F>
-__device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int strip, int band, int B, int dir, F finish)
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, typename F>
+__device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip, int band, int B, int dir, F finish)
 {
-    using C = float2;
+    using C = typename cvec<R>::type;
+    static_assert(W == 1 || (W == 2 && sizeof(R) == 4), "two columns per lane: complex64");
     constexpr int K = 12;  // rows j - 8 .. j + PF of the inputs are in flight
-    constexpr int PF = 3;  // rows loaded ahead of their first use
+    constexpr int PF = RES && HASV ? 2 : 3;  // rows loaded ahead of their first use
     const int lane = threadIdx.x & 63;
-    const Coef<float>& c = a.c;
-    const int gi = strip * kPairCols - kPairHalo + 2 * lane;  // first column of the lane's pair
-    const int ci = wrap_any(gi, a.nx, a.bcx);                  // -1: ghost pair (zero x boundary)
+    const Coef<R>& c = a.c;
+    const int gi = strip * pair_cols(W) - kPairHalo + W * lane;  // first column of the lane
+    const int ci = wrap_any(gi, a.nx, a.bcx);                     // -1: ghost (zero x boundary)
     const bool gcol = GHOSTS && ci < 0;
-    const float keep = gcol ? 0.f : 1.f;
+    const R keep = gcol ? R(0) : R(1);
     const int b0 = band * B;
-    const float kdiag = 2.f * (c.ax + c.ay);
-    const int row8 = a.nx * 8, row4 = a.nx * 4;
+    const R kdiag = R(2) * (c.ax + c.ay);
+    const int rowc = a.nx * (int)sizeof(C), rowr = a.nx * (int)sizeof(R);
     const size_t cells = (size_t)a.nx * a.ny;
-    const __amdgpu_buffer_rsrc_t rpi = buffer_of(a.psi_in, cells * 8);
-    const __amdgpu_buffer_rsrc_t rni = buffer_of(a.n_in, RES ? cells * 4 : 0);
-    const __amdgpu_buffer_rsrc_t rP = buffer_of(a.P, RES ? cells * 4 : 0);
-    const __amdgpu_buffer_rsrc_t rV = buffer_of(a.V, HASV ? cells * 4 : 0);
-    const __amdgpu_buffer_rsrc_t rpo = buffer_of(a.psi_out, cells * 8);
-    const __amdgpu_buffer_rsrc_t rno = buffer_of(a.n_out, RES ? cells * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rpi = buffer_of(a.psi_in, cells * sizeof(C));
+    const __amdgpu_buffer_rsrc_t rni = buffer_of(a.n_in, RES ? cells * sizeof(R) : 0);
+    const __amdgpu_buffer_rsrc_t rP = buffer_of(a.P, RES ? cells * sizeof(R) : 0);
+    const __amdgpu_buffer_rsrc_t rV = buffer_of(a.V, HASV ? cells * sizeof(R) : 0);
+    const __amdgpu_buffer_rsrc_t rpo = buffer_of(a.psi_out, cells * sizeof(C));
+    const __amdgpu_buffer_rsrc_t rno = buffer_of(a.n_out, RES ? cells * sizeof(R) : 0);
     const __amdgpu_buffer_rsrc_t rnull = buffer_of(a.psi_out, 0);  // every access out of range
-    const int v8 = gcol ? kOutOfRange : (ci < 0 ? 0 : ci) * 8;
-    const int v4 = gcol ? kOutOfRange : (ci < 0 ? 0 : ci) * 4;
-    const bool out_col = lane >= kPairHalo / 2 && lane < 64 - kPairHalo / 2 && gi < a.nx;
-    const int o8 = out_col ? gi * 8 : kOutOfRange;
-    const int o4 = out_col ? gi * 4 : kOutOfRange;
+    const int vc = gcol ? kOutOfRange : (ci < 0 ? 0 : ci) * (int)sizeof(C);
+    const int vr = gcol ? kOutOfRange : (ci < 0 ? 0 : ci) * (int)sizeof(R);
+    const bool out_col = lane >= kPairHalo / W && lane < 64 - kPairHalo / W && gi < a.nx;
+    const int oc = out_col ? gi * (int)sizeof(C) : kOutOfRange;
+    const int orr = out_col ? gi * (int)sizeof(R) : kOutOfRange;
 
-    // [step][slot][cell of the pair]; step 0 reads the input, step 1 the state in between
-    C sp[2][K][2], acc[2][4][2], w[2][3][3][2];  // w[.][q]: argument of stage q + 2
-    float sn[2][K][2], accn[2][4][2], wn[2][3][3][2];
-    float sP[K][2], sk[K][2];
+    // [step][slot][cell of the lane]; step 0 reads the input, step 1 the state in between
+    C sp[2][K][W], acc[2][4][W], w[2][3][3][W];  // w[.][q]: argument of stage q + 2
+    R sn[2][K][W], accn[2][4][W], wn[2][3][3][W];
+    R sP[K][W], sk[K][W];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
+    for (int e = 0; e < W; ++e) {
 #pragma unroll
         for (int s = 0; s < K; ++s) {
-            sP[s][e] = 0.f;
+            sP[s][e] = R(0);
             sk[s][e] = kdiag;
         }
 #pragma unroll
@@ -88,19 +95,19 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
 #pragma unroll
             for (int s = 0; s < K; ++s) {
                 sp[h][s][e] = czero<C>();
-                sn[h][s][e] = 0.f;
+                sn[h][s][e] = R(0);
             }
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 acc[h][s][e] = czero<C>();
-                accn[h][s][e] = 0.f;
+                accn[h][s][e] = R(0);
             }
 #pragma unroll
             for (int q = 0; q < 3; ++q)
 #pragma unroll
                 for (int s = 0; s < 3; ++s) {
                     w[h][q][s][e] = czero<C>();
-                    wn[h][q][s][e] = 0.f;
+                    wn[h][q][s][e] = R(0);
                 }
         }
     }
@@ -110,28 +117,33 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
     int g = start;
     int rw = wrap_any(g, a.ny, a.bcy);
     auto fetch = [&](int s, bool use) __attribute__((always_inline)) {
-        const int rr = rw < 0 ? 0 : rw;
-        const wf4 v = wload4(rpi, v8, rr * row8);
-        if (YZERO) {
-            const float rk = rw < 0 ? 0.f : 1.f;
-            sp[0][s][0] = C{rk * v.x, rk * v.y};
-            sp[0][s][1] = C{rk * v.z, rk * v.w};
-        } else {
+        const bool grow = YZERO && rw < 0;  // uniform: a ghost row reads 0 through the empty descriptor
+        const int rr = grow ? 0 : rw;
+        if constexpr (W == 2) {
+            const wf4 v = wload4(grow ? rnull : rpi, vc, rr * rowc);
             sp[0][s][0] = C{v.x, v.y};
             sp[0][s][1] = C{v.z, v.w};
+        } else {
+            sp[0][s][0] = buf_load<C>(grow ? rnull : rpi, vc, rr * rowc);
         }
+        auto load_real = [&](__amdgpu_buffer_rsrc_t r, R (&v)[W]) __attribute__((always_inline)) {
+            if constexpr (W == 2) {
+                const wf2 x = wload2(r, vr, rr * rowr);
+                v[0] = x.x;
+                v[1] = x.y;
+            } else {
+                v[0] = buf_load<R>(r, vr, rr * rowr);
+            }
+        };
         if (RES) {
-            const wf2 nv = wload2(rni, v4, rr * row4);
-            const wf2 pv = wload2(rP, v4, rr * row4);
-            sn[0][s][0] = nv.x;
-            sn[0][s][1] = nv.y;
-            sP[s][0] = pv.x;
-            sP[s][1] = pv.y;
+            load_real(grow ? rnull : rni, sn[0][s]);
+            load_real(grow ? rnull : rP, sP[s]);
         }
         if (HASV) {
-            const wf2 vv = wload2(rV, v4, rr * row4);
-            sk[s][0] = fmaf(c.inv_hbar, vv.x, kdiag);
-            sk[s][1] = fmaf(c.inv_hbar, vv.y, kdiag);
+            R v[W];
+            load_real(grow ? rnull : rV, v);
+#pragma unroll
+            for (int e = 0; e < W; ++e) sk[s][e] = fma(c.inv_hbar, v[e], kdiag);
         }
         const int gn = g + dir;
         int rn;
@@ -157,7 +169,7 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
             // Row j arrives: its values leave the four- and two-register groups that the
             // loads write (kept there for their whole life they fragment the register file).
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
+            for (int e = 0; e < W; ++e) {
                 const int q = slot<K>(u, 0);
                 keep_here(sp[0][q][e]);
                 if (RES) {
@@ -174,10 +186,10 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
                 const int m = slot<3>(u, k), a4 = slot<4>(u, k);
                 const int r = j - k * dir;
                 // argument rows: the state itself in stage 1, else the stage argument
-                C cur[2], up[2], dn[2];
-                float nn[2];
+                C cur[W], up[W], dn[W], lr[W];
+                R nn[W];
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
+                for (int e = 0; e < W; ++e) {
                     if (s == 1) {
                         cur[e] = sp[h][q][e];
                         up[e] = sp[h][slot<K>(u, k + 1)][e];
@@ -190,27 +202,32 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
                         nn[e] = wn[h][s - 2][m][e];
                     }
                 }
-                // neighbours in x: the pair's other cell and the adjacent lane's
-                const C lr[2] = {C{lane_prev(cur[1].x) + cur[1].x, lane_prev(cur[1].y) + cur[1].y},
-                                 C{cur[0].x + lane_next(cur[0].x), cur[0].y + lane_next(cur[0].y)}};
+                // neighbours in x: the adjacent lanes' cells (and the lane's other one)
+                if constexpr (W == 2) {
+                    lr[0] = C{lane_prev(cur[1].x) + cur[1].x, lane_prev(cur[1].y) + cur[1].y};
+                    lr[1] = C{cur[0].x + lane_next(cur[0].x), cur[0].y + lane_next(cur[0].y)};
+                } else {
+                    lr[0] = C{lane_prev(cur[0].x) + lane_next(cur[0].x), lane_prev(cur[0].y) + lane_next(cur[0].y)};
+                }
                 __builtin_amdgcn_sched_barrier(0);
-                const float kk = YZERO ? ((unsigned)r >= (unsigned)a.ny ? 0.f : keep) : keep;
-                float y[4], yn[2];
+                const R kk = YZERO ? ((unsigned)r >= (unsigned)a.ny ? R(0) : keep) : keep;
+                C y[W];
+                R yn[W];
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    float fx, fy, fn;
-                    cell_rhs<float, RES>(c, cur[e], lr[e].x, lr[e].y, up[e].x + dn[e].x, up[e].y + dn[e].y, nn[e],
+                for (int e = 0; e < W; ++e) {
+                    R fx, fy, fn;
+                    cell_rhs<R, RES>(c, cur[e], lr[e].x, lr[e].y, up[e].x + dn[e].x, up[e].y + dn[e].y, nn[e],
                                          sP[q][e], sk[q][e], fx, fy, fn);
                     C& ac = acc[h][a4][e];
-                    float& an = accn[h][a4][e];
+                    R& an = accn[h][a4][e];
                     const C p0 = sp[h][q][e];
-                    const float n0 = sn[h][q][e];
+                    const R n0 = sn[h][q][e];
                     if (s < 4) {
-                        const float step = s == 3 ? a.dt : a.half_dt;
-                        ac = s == 1 ? C{fx, fy} : C{fmaf(2.f, fx, ac.x), fmaf(2.f, fy, ac.y)};
-                        an = s == 1 ? fn : fmaf(2.f, fn, an);
-                        w[h][s - 1][m][e] = C{kk * fmaf(step, fx, p0.x), kk * fmaf(step, fy, p0.y)};
-                        wn[h][s - 1][m][e] = kk * fmaf(step, fn, n0);
+                        const R step = s == 3 ? a.dt : a.half_dt;
+                        ac = s == 1 ? C{fx, fy} : C{fma(R(2), fx, ac.x), fma(R(2), fy, ac.y)};
+                        an = s == 1 ? fn : fma(R(2), fn, an);
+                        w[h][s - 1][m][e] = C{kk * fma(step, fx, p0.x), kk * fma(step, fy, p0.y)};
+                        wn[h][s - 1][m][e] = kk * fma(step, fn, n0);
                         keep_here(ac);
                         keep_here(w[h][s - 1][m][e]);
                         if (RES) {
@@ -218,11 +235,10 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
                             keep_here(wn[h][s - 1][m][e]);
                         }
                     } else {
-                        y[2 * e] = fmaf(a.dt6, ac.x + fx, p0.x);
-                        y[2 * e + 1] = fmaf(a.dt6, ac.y + fy, p0.y);
-                        yn[e] = fmaf(a.dt6, an + fn, n0);
+                        y[e] = C{fma(a.dt6, ac.x + fx, p0.x), fma(a.dt6, ac.y + fy, p0.y)};
+                        yn[e] = fma(a.dt6, an + fn, n0);
                         if (h == 0) {  // the state in between (0 in ghost cells)
-                            sp[1][q][e] = C{kk * y[2 * e], kk * y[2 * e + 1]};
+                            sp[1][q][e] = C{kk * y[e].x, kk * y[e].y};
                             sn[1][q][e] = kk * yn[e];
                             keep_here(sp[1][q][e]);
                             if (RES) keep_here(sn[1][q][e]);
@@ -234,12 +250,20 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
                     // a descriptor of size 0, whose stores are dropped
                     const bool st = r >= b0 && r < b0 + B && r < a.ny;  // uniform
                     const int rr = st ? r : 0;
-                    wstore4(wf4{y[0], y[1], y[2], y[3]}, st ? rpo : rnull, o8, rr * row8);
-                    if (RES) wstore2(wf2{yn[0], yn[1]}, st ? rno : rnull, o4, rr * row4);
+                    if constexpr (W == 2) {
+                        wstore4(wf4{y[0].x, y[0].y, y[1].x, y[1].y}, st ? rpo : rnull, oc, rr * rowc);
+                        if (RES) wstore2(wf2{yn[0], yn[1]}, st ? rno : rnull, orr, rr * rowr);
+                    } else {
+                        buf_store_nt(y[0], st ? rpo : rnull, (int)((unsigned)oc + (unsigned)(rr * rowc)));
+                        if (RES) buf_store_nt(yn[0], st ? rno : rnull, (int)((unsigned)orr + (unsigned)(rr * rowr)));
+                    }
                     if (CHECK) {
-                        unsigned nf = (unsigned)!isfinite(y[0]) | (unsigned)!isfinite(y[1]) |
-                                      (unsigned)!isfinite(y[2]) | (unsigned)!isfinite(y[3]);
-                        if (RES) nf |= (unsigned)!isfinite(yn[0]) | (unsigned)!isfinite(yn[1]);
+                        unsigned nf = 0u;
+#pragma unroll
+                        for (int e = 0; e < W; ++e) {
+                            nf |= (unsigned)!isfinite(y[e].x) | (unsigned)!isfinite(y[e].y);
+                            if (RES) nf |= (unsigned)!isfinite(yn[e]);
+                        }
                         bad |= (st && out_col) ? nf : 0u;
                     }
                 }
@@ -251,13 +275,13 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<float>& a, int s
     finish(bad != 0u);
 }
 
-template <bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
-void rk4_stream_pair_kernel(const StepArgs<float> a)
+void rk4_stream_pair_kernel(const StepArgs<R> a)
 {
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     const int band = t / a.tiles_x, strip = t - band * a.tiles_x;
-    stream_band_pair<RES, HASV, GHOSTS, YZERO, CHECK>(a, strip, band, a.band_rows, (band & 1) ? -1 : 1,
+    stream_band_pair<R, W, RES, HASV, GHOSTS, YZERO, CHECK>(a, strip, band, a.band_rows, (band & 1) ? -1 : 1,
                                                          [&](bool bad) __attribute__((always_inline)) {
                                                              if (bad) a.flag[0] = 1u;  // benign race
                                                          });

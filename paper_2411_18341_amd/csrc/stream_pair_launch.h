@@ -1,0 +1,39 @@
+// Launch of the two-step streaming kernel (stream_pair.h) for one precision and column
+// count; each is instantiated in a unit of its own.
+#pragma once
+
+#include "runtime.h"
+#include "stream_pair.h"
+
+namespace phx {
+
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO>
+static void launch_pair_t(const StepArgs<R>& a, hipStream_t s)
+{
+    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS);
+    if (a.check)
+        rk4_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, true><<<a.tiles, 64, 0, s>>>(a);
+    else
+        rk4_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, false><<<a.tiles, 64, 0, s>>>(a);
+}
+
+template <typename R, int W, bool RES, bool HASV>
+static hipError_t launch_pair_v(const StepArgs<R>& a, hipStream_t s)
+{
+    if (a.bcy == PHX_BC_ZERO)
+        launch_pair_t<R, W, RES, HASV, true, true>(a, s);
+    else if (a.bcx == PHX_BC_ZERO)
+        launch_pair_t<R, W, RES, HASV, true, false>(a, s);
+    else
+        launch_pair_t<R, W, RES, HASV, false, false>(a, s);
+    return hipGetLastError();
+}
+
+template <typename R, int W>
+hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s)
+{
+    if (reservoir) return has_v ? launch_pair_v<R, W, true, true>(a, s) : launch_pair_v<R, W, true, false>(a, s);
+    return has_v ? launch_pair_v<R, W, false, true>(a, s) : launch_pair_v<R, W, false, false>(a, s);
+}
+
+}  // namespace phx
