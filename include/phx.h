@@ -93,7 +93,9 @@ typedef struct phx_config {
                                (8..4096), or 0 for the height that fills the device with
                                one wave per band (2 x 0 then takes two steps per launch where
                                neither noise, drive nor imaginary time comes between them);
-                               streaming forms need a state under 2 GiB;
+                               1 x 64 does so with one column per lane, and lets the library
+                               pick the band height for two steps per launch and for the
+                               spinor; streaming forms need a state under 2 GiB;
                                0 with tile_wx 0 = automatic                                 */
     int32_t graph_steps;    /* RK4 steps per captured hipGraph chunk replayed by phx_step:
                                0 = default (64), < 0 = launch every kernel directly        */

@@ -19,7 +19,16 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libphx.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["rk4_step.hip", "rk4_stream_spinor_res_f40.hip", "rk4_stream_spinor_res_f64.hip", "rk4_stream_spinor_res_d40.hip", "rk4_stream_spinor_res_d64.hip", "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip", "rk4_stream_spinor_drive_d.hip", "runtime.hip", "rk4.hip", "reduce.hip", "dopri5.hip", "batch.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive.hip", "rk4_stream_spinor.hip", "rk4_stream_wide.hip", "rk4_stream_pair_f2.hip", "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip", "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip"]
+SOURCES = [
+    "rk4_step.hip", "rk4_stream_spinor_f2.hip", "rk4_stream_spinor_f1.hip",
+    "rk4_stream_spinor_d.hip", "rk4_stream_spinor_res_f.hip", "rk4_stream_spinor_res_d.hip",
+    "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip",
+    "rk4_stream_spinor_drive_d.hip", "rk4_stream_spinor.hip", "runtime.hip", "rk4.hip",
+    "reduce.hip", "dopri5.hip", "batch.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip",
+    "imag.hip", "rk4_stream_drive.hip", "rk4_stream_wide.hip", "rk4_stream_pair_f2.hip",
+    "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip",
+    "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip",
+]
 
 ARCH = "gfx950"
 FLAGS = [
@@ -33,8 +42,8 @@ FLAGS = [
 # the two-component walk with reservoirs is larger than LLVM's default size limit
 # for a requested full unroll, so its unit raises that limit.
 _FULL_UNROLL = ["-mllvm", "-pragma-unroll-threshold=40000"]
-EXTRA_FLAGS = {f"rk4_stream_spinor{t}.hip": _FULL_UNROLL
-               for t in ("", "_res_f40", "_res_f64", "_res_d40", "_res_d64", "_imag_f", "_imag_d", "_drive_f", "_drive_d")}
+EXTRA_FLAGS = {f"rk4_stream_spinor_{t}.hip": _FULL_UNROLL
+               for t in ("f2", "f1", "d", "res_f", "res_d", "imag_f", "imag_d", "drive_f", "drive_d")}
 # the wide walk with the Wiener increment drawn at its final store (a generator call
 # per position) likewise exceeds the default limit
 EXTRA_FLAGS["rk4_stream_wide.hip"] = _FULL_UNROLL

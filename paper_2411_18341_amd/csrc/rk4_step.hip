@@ -134,7 +134,7 @@ static hipError_t launch_step_shape(const StepShapeId& sh, const StepArgs<R>& a,
 template <typename R>
 hipError_t launch_stream_drive(bool reservoir, bool has_v, int rows, const StepArgs<R>& a, hipStream_t s);
 template <typename R>
-hipError_t launch_stream_spinor(bool reservoir, bool has_v, int rows, const StepArgs<R>& a, hipStream_t s);
+hipError_t launch_stream_spinor(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
 
 template <typename R>
 hipError_t launch_rk4_step(bool reservoir, bool has_v, const StepShapeId& sh, const StepArgs<R>& a,
@@ -150,7 +150,7 @@ hipError_t launch_rk4_step(bool reservoir, bool has_v, const StepShapeId& sh, co
         return hipErrorInvalidValue;
     }
     if (a.comps == 2)
-        return sh.waves == 1 ? launch_stream_spinor<R>(reservoir, has_v, sh.rows, a, s) : hipErrorInvalidValue;
+        return sh.waves == 1 ? launch_stream_spinor<R>(reservoir, has_v, a, s) : hipErrorInvalidValue;
     if (reservoir) return has_v ? launch_step_shape<R, true, true>(sh, a, s) : launch_step_shape<R, true, false>(sh, a, s);
     return has_v ? launch_step_shape<R, false, true>(sh, a, s) : launch_step_shape<R, false, false>(sh, a, s);
 }
@@ -185,6 +185,12 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
     } else if (wide_shape(sh.waves)) {  // wide streaming: strips of 120 columns, one wave per band of a strip
         a.tiles_x = wide_strips(c.nx);
         a.band_rows = wide_band_rows(c, sh, h->f.V != nullptr, h->cus);
+        a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
+    } else if (c.components == 2) {  // the spinor walk: one wave per band of a strip
+        const SpinorPlan p = spinor_plan(c, sh.rows == 64 ? 0 : sh.rows, h->cus);
+        a.columns = p.columns;
+        a.tiles_x = p.strips;
+        a.band_rows = p.band_rows;
         a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
     } else if (sh.waves == 1) {  // streaming: strips of 56 columns, workgroups of 4 strips x one band
         a.tiles = ((a.tiles_x + 3) / 4) * ((c.ny + sh.rows - 1) / sh.rows);
@@ -284,8 +290,9 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
         cur ^= 1;
         if (c.imag_time) {  // the scale that restores the norm, applied by the next step
             e = timing_begin(h, &t0);
-            // one norm partial per wave: 4 per workgroup of the one-column walk, 1 for the wide
-            if (e == hipSuccess) e = launch_imag_finish(h, wide_shape(sh.waves) ? a.tiles : 4 * a.tiles, s);
+            // one norm partial per wave: 4 per workgroup of the one-column walk, else 1
+            const bool single = wide_shape(sh.waves) || c.components == 2;
+            if (e == hipSuccess) e = launch_imag_finish(h, single ? a.tiles : 4 * a.tiles, s);
             if (e == hipSuccess) e = timing_end(h, t0, K_IMAG_NORM);
             if (e != hipSuccess) return fail(PHX_EHIP, "imaginary-time norm launch: %s", hipGetErrorString(e));
         }

@@ -1,8 +1,6 @@
-// Spinor streaming whole-step kernel in imaginary time (no reservoirs), float, bands of
-// 40 and 64 rows.
+// Spinor streaming whole-step kernel, complex64 in imaginary time.
 #include "stream_spinor_launch.h"
 
 namespace phx {
-template hipError_t launch_spinor_imag<float, 40>(bool, const StepArgs<float>&, hipStream_t);
-template hipError_t launch_spinor_imag<float, 64>(bool, const StepArgs<float>&, hipStream_t);
+template hipError_t launch_spinor_part<float, 1, false, true, false>(bool, const StepArgs<float>&, hipStream_t);
 }  // namespace phx

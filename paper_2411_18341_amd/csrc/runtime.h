@@ -149,12 +149,44 @@ int wide_strips(int nx);
 int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int cus);
 int wide_waves_per_simd(int ring, bool reservoir, bool has_v, bool ghosts, bool noise);
 hipError_t launch_stream_wide(bool reservoir, bool has_v, int ring, const StepArgs<float>& a, hipStream_t s);
+// Band height of a walk that is bound by its VALU issue: of the heights with which every
+// wave (one per band of a strip) is resident at once, the one whose busiest SIMD ends first.
+// A wave walks rows + halo positions, `skipped` of them without work; heights are
+// lo + k step.  n waves on a SIMD issue at a share of its rate that was measured on the
+// two-step walk: one wave 0.82 (63.6 us per step at 4096^2 with bands of 152 rows, against 59.4 with
+// two waves and bands of 80), two 0.97.
+struct BandFill {
+    int rows;
+    double cost;  // positions times waves on the busiest SIMD, over the issue rate
+};
+inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int step, int cus, int waves_per_simd)
+{
+    const int simds = 4 * (cus > 0 ? cus : 256);
+    BandFill best{0, 0.0};
+    for (int n = 1; n <= waves_per_simd; ++n) {
+        const int bands = simds * n / strips;
+        if (bands < 1 && n < waves_per_simd) continue;
+        const int need = bands < 1 ? ny : (ny + bands - 1) / bands;
+        const int rows = need <= lo ? lo : lo + (need - lo + step - 1) / step * step;
+        const int64_t waves = (int64_t)strips * ((ny + rows - 1) / rows);
+        const int busy = (int)((waves + simds - 1) / simds);
+        const double rate = busy == 1 ? 0.82 : (busy == 2 ? 0.97 : 1.0);
+        const double cost = busy * (double)(rows + halo - skipped) / rate;
+        if (best.rows == 0 || cost < best.cost) best = BandFill{rows, cost};
+    }
+    return best;
+}
 // Two steps per launch of the streaming forms (stream_pair.h): the columns per lane with
 // which shape sh runs this way for this configuration (0: it takes single steps), the
 // strips and the band height.
 int pair_columns(const phx_config& c, const StepShapeId& sh);
 StepShapeId default_step_shape(const phx_config& c);
 int pair_strips(int nx, int w);
+// Columns per lane, strips and band height of the spinor walk (stream_spinor.h).
+struct SpinorPlan {
+    int columns, strips, band_rows;
+};
+SpinorPlan spinor_plan(const phx_config& c, int rows, int cus);
 int pair_band_rows(const phx_config& c, int w, bool has_v, int cus);
 template <typename R, int W>
 hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);

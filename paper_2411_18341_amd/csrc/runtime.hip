@@ -146,6 +146,9 @@ Layout make_layout(const phx_config& c)
         const int64_t blocks = imag_norm_blocks(c.nx * (int64_t)c.ny * c.components);
         int64_t slots = stream_waves > blocks ? stream_waves : blocks;
         if (wide_waves > slots) slots = wide_waves;
+        // the spinor walk: one wave per band of one 56-column strip, bands of at least 8 rows
+        const int64_t spinor_waves = c.components == 2 ? (int64_t)((c.nx + 55) / 56) * ((c.ny + 7) / 8) : 0;
+        if (spinor_waves > slots) slots = spinor_waves;
         L.imag_partials = take((size_t)slots * sizeof(double));
     }
     if (c.integrator == PHX_RK4) {
@@ -217,17 +220,14 @@ int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int c
 
 int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
 
-// Band height of the two-step form with w columns per lane: the smallest whose bands, one
-// wave each, fit on the device at once, rounded up so that the walk's B + 16 rows fill
-// whole chunks of 12 positions (20, 32, 44, ...).
+// Band height of the two-step form with w columns per lane; the walk's B + 16 rows fill
+// whole chunks of 12 positions (B = 20, 32, 44, ...).
 int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 {
     const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
     const int words = w * (c.precision == PHX_C64 ? 1 : 2);
-    const int slots = (cus > 0 ? cus : 256) * 4 * pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts);
-    const int bands = std::max(1, slots / pair_strips(c.nx, w));
-    const int b = (c.ny + bands - 1) / bands;
-    return std::max(20, (b + 16 + 11) / 12 * 12 - 16);
+    return band_fill(pair_strips(c.nx, w), c.ny, 16, 9, 20, 12, cus,
+                     pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts)).rows;
 }
 
 // Two steps per launch where nothing has to happen between them (no noise or drive, no norm
@@ -254,7 +254,9 @@ int pair_columns(const phx_config& c, const StepShapeId& sh)
 // saves the separate pass; in complex128 the one-column form takes 62 against 76 us at 2047^2.
 StepShapeId default_step_shape(const phx_config& c)
 {
-    if (c.imag_time || c.drive || c.components == 2) return StepShapeId{1, 40};  // streaming
+    // streaming only; 1 x 64 of the spinor walk lets it pick the band height itself
+    if (c.components == 2) return StepShapeId{1, 64};
+    if (c.imag_time || c.drive) return StepShapeId{1, 40};
     const int64_t cells = (int64_t)c.nx * c.ny, k = (int64_t)1 << 18;
     const bool c64 = c.precision == PHX_C64;
     const StepShapeId* shapes;

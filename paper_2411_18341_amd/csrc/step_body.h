@@ -43,7 +43,8 @@ struct StepArgs {
     const C* E;
     const C* drive_ph;
     int comps;  // 2: the spinor streaming kernel (component stride nx*ny)
-    int band_rows;        // wide streaming form: rows per band (a launch argument)
+    int band_rows;        // wide, two-step and spinor walks: rows per band (a launch argument)
+    int columns;          // spinor walk: columns per lane
     int check;            // wide streaming form: test the stored values for non-finite ones
     // wide streaming form with the Wiener increment added before the final store
     // (null: no noise): step index *noise_step + noise_offset, variance a n + b, key

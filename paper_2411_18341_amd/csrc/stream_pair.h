@@ -40,13 +40,6 @@ constexpr int pair_waves_per_simd(int words, bool res, bool hasv, bool ghosts)
 constexpr int kPairHalo = 8;
 constexpr int pair_cols(int w) { return 64 * w - 2 * kPairHalo; }  // output columns per strip
 
-// Forms the value here: without this the compiler moves sums that only a later position
-// reads to that position, where their operands then stay live as well.
-__device__ __forceinline__ void keep_here(float& v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ void keep_here(double& v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ void keep_here(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
-__device__ __forceinline__ void keep_here(double2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
-
 // One band of `B` rows of strip `strip`; `finish(bad)` gets whether a stored value is not
 // finite (CHECK; else false without testing).
 template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, typename F>

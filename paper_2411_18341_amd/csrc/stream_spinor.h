@@ -5,16 +5,31 @@
 // with gain, reservoir interaction and pumps P_+-.
 //
 // The band walk is the one-component kernel's (stream_body.h): one wave per strip of
-// 56 columns plus a 4-column halo, rows walked once with the four stages pipelined
-// one row apart, inputs in an 8-row ring, running sums in a 4-row ring, stage
-// arguments in 3-row windows -- here for both components.  x-neighbours come from
-// DPP lane shifts; the mixed difference
+// columns plus a 4-column halo (W = 1 column per lane: 56 output columns; W = 2, complex64
+// without reservoirs on even widths: 120), rows walked once with the four stages pipelined
+// one row apart, inputs in an 8-row ring, running sums and stage arguments in rings of 4 --
+// here for both components.  x-neighbours come from DPP lane shifts; the mixed difference
 //   X = o[i+1,j+1] - o[i+1,j-1] - o[i-1,j+1] + o[i-1,j-1]
-// is the lane shift of (row below - row above) of the other component, and changes
-// sign with the walking direction (odd bands walk upwards).
+// is the shift by one column of (row below - row above) of the other component, and
+// changes sign with the walking direction (odd bands walk upwards).
+//
+// The kernel is bound by its VALU issue, so what counts is the number of instructions:
+// two columns per lane halve the halo columns (128 / 120 instead of 64 / 56) and leave one
+// lane shift per neighbour sum instead of two; bands are as tall as the device's wave
+// slots allow, so that all waves run at once (with bands of 64 rows 4096^2 took one and a
+// half rounds of waves); stage s starts at position 2 s, before which no stage needs its
+// rows.  Every ring length divides the 8 positions of the unrolled body; the values that
+// later positions read are pinned where they are formed (keep_here).  Measured, us per
+// step with zero boundaries and a potential (before: one column per lane, bands of 40 rows,
+// 24 positions unrolled): complex64 143 (186) at 4096^2, 49.7 (75.2) at 2048^2, 9.6 (34.2) at
+// 512^2; with reservoirs 64.6 (96.4) at 2048^2; complex128 75.9 (108.7) at 2048^2; drive 61.2
+// (102.2), imaginary time with its norm pass 56.4 (90.5) at 2048^2.  At 4096^2 the 2030 waves of
+// 80 positions issue 532 VALU instructions each, 137 us back to back.
 #pragma once
 
-#include "stream_body.h"
+#include <type_traits>
+
+#include "stream_wide.h"
 
 namespace phx {
 
@@ -32,7 +47,7 @@ template <typename R, bool RES, bool IMAG = false>
 __device__ __forceinline__ void spinor_rhs(const Coef<R>& c, const typename cvec<R>::type (&cur)[2],
                                            const typename cvec<R>::type (&lr)[2],
                                            const typename cvec<R>::type (&ud)[2],
-                                           const typename cvec<R>::type (&dy)[2], R kv, R bxyd,
+                                           const typename cvec<R>::type (&xx)[2], R kv, R bxyd,
                                            const R (&nn)[2], const R (&pv)[2], typename cvec<R>::type (&f)[2],
                                            R (&fn)[2])
 {
@@ -56,11 +71,9 @@ __device__ __forceinline__ void spinor_rhs(const Coef<R>& c, const typename cvec
         const R ty = fma(c.ax, lr[s].y, fma(c.ay, ud[s].y, oy));
         // the walking direction's sign rides on the coefficient (bxyd = dir bxy, chosen
         // once per band), not on each difference
-        const R xx = lane_next(dy[o].x) - lane_prev(dy[o].x);
-        const R xy = lane_next(dy[o].y) - lane_prev(dy[o].y);
         const R sb = s == 0 ? -bxyd : bxyd;
-        f[s].x = fma(sb, xx, fma(u, p.x, fma(om, p.y, -ty)));
-        f[s].y = fma(sb, xy, fma(u, p.y, fma(-om, p.x, tx)));
+        f[s].x = fma(sb, xx[o].x, fma(u, p.x, fma(om, p.y, -ty)));
+        f[s].y = fma(sb, xx[o].y, fma(u, p.y, fma(-om, p.x, tx)));
         if constexpr (IMAG) {  // imaginary time: -i f
             const R t = f[s].x;
             f[s].x = f[s].y;
@@ -69,27 +82,42 @@ __device__ __forceinline__ void spinor_rhs(const Coef<R>& c, const typename cvec
     }
 }
 
+constexpr int spinor_cols(int w) { return 64 * w - 8; }  // output columns per strip
+
+// Waves per SIMD that the registers allow without scratch memory.
+constexpr int spinor_waves_per_simd(bool c64, int w, bool res, bool imag, bool drive)
+{
+    if (!c64) return res || drive ? 1 : 2;
+    if (w == 2 || res) return 2;
+    return imag || drive ? 3 : 4;
+}
+// VALU instructions of one position (four stages, one row of the lane's columns).
+constexpr int spinor_instructions(int w) { return w == 2 ? 532 : 297; }
+
+// One band of `B` rows (a multiple of 8) of strip `strip`; `finish(bad, norm)` gets whether
+// a stored value is not finite and the lane's norm partial.
 // IMAG: imaginary time (no reservoirs): each stage's derivative is rotated by -i, the
 // input is multiplied by the scale a.imag_slots[1] that restores the previous step's
-// norm, and *norm receives this lane's FP64 sum of |psi_out|^2 over both components of
-// the cells it stores.
+// norm, and the norm partial is this lane's FP64 sum of |psi_out|^2 over both components
+// of the cells it stores.
 // DRIVE (no reservoirs, real time): the coherent drive -(i/hbar) E_s(r) exp(-i omega t_k)
 // joins the derivative of component s at stage k; both components of E ride in the
 // input ring beside psi, the four stage phasors come from a.drive_ph.
-template <typename R, bool RES, bool HASV, bool GHOSTS, bool YZERO, int B, bool IMAG = false, bool DRIVE = false>
-__device__ __forceinline__ bool stream_band_spinor(const StepArgs<R>& a, int strip, int band, int dir,
-                                                   double* norm = nullptr)
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool IMAG, bool DRIVE, typename F>
+__device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int strip, int band, int B, int dir, F finish)
 {
     static_assert(!(IMAG && RES), "imaginary time has no reservoir");
     static_assert(!(DRIVE && (RES || IMAG)), "the drive runs without reservoirs, in real time");
+    static_assert(W == 1 || (W == 2 && sizeof(R) == 4 && !RES && !IMAG && !DRIVE), "two columns per lane: complex64");
+    using C = typename cvec<R>::type;
+    constexpr int K = 8;              // rows j - 4 .. j + PF are in flight
+    // rows loaded ahead of their first use (fewer where the registers are full)
+    constexpr int PF = W == 2 || (RES && sizeof(R) == 8 && YZERO) ? 2 : 3;
     const R sc = IMAG ? (R)a.imag_slots[1] : R(1);  // uniform
     double nrm = 0.0;
-    using C = typename cvec<R>::type;
-    static_assert((B + 8) % 24 == 0, "band rows + 8 must be a multiple of the unroll length");
-    constexpr int PF = 3;
     const int lane = threadIdx.x & 63;
     const Coef<R>& c = a.c;
-    const int gi = strip * 56 - 4 + lane;
+    const int gi = strip * spinor_cols(W) - 4 + W * lane;
     const int ci = wrap_any(gi, a.nx, a.bcx);
     const bool gcol = GHOSTS && ci < 0;
     // Ghost columns and rows stay 0 in every stage: their inputs read as 0, so the stage
@@ -113,22 +141,34 @@ __device__ __forceinline__ bool stream_band_spinor(const StepArgs<R>& a, int str
     const __amdgpu_buffer_rsrc_t rnull = buffer_of(a.psi_in, 0);
     const __amdgpu_buffer_rsrc_t rE = buffer_of(a.E, DRIVE ? 2 * cells * sizeof(C) : 0);
 
-    C sp[2][8];
-    C sE[2][8];  // DRIVE: the profile of both components, in the input ring
-    C ph[4];     // DRIVE: the phasors of the four stage times
-    R sk[8];
-    R sn[2][8], sP[2][8];
-    C acc[2][4];
-    R accn[2][4];
-    C w2[2][3], w3[2][3], w4[2][3];
-    R n2[2][2], n3[2][2], n4[2][2];
+    // [component][slot][column of the lane]
+    C sp[2][K][W], sE[2][K][W];  // state; DRIVE: the profile
+    R sk[K][W];
+    R sn[2][K][W], sP[2][K][W];
+    C acc[2][4][W], w[2][3][4][W];  // w[.][q]: argument of stage q + 2
+    R accn[2][4][W], wn[2][3][4][W];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        sp[0][s] = sp[1][s] = czero<C>();
-        sn[0][s] = sn[1][s] = sP[0][s] = sP[1][s] = R(0);
-        sk[s] = kdiag;
-        if constexpr (DRIVE) sE[0][s] = sE[1][s] = czero<C>();
-    }
+    for (int e = 0; e < W; ++e)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+#pragma unroll
+            for (int s = 0; s < K; ++s) {
+                sp[m][s][e] = sE[m][s][e] = czero<C>();
+                sn[m][s][e] = sP[m][s][e] = R(0);
+                sk[s][e] = kdiag;
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                acc[m][s][e] = czero<C>();
+                accn[m][s][e] = R(0);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    w[m][q][s][e] = czero<C>();
+                    wn[m][q][s][e] = R(0);
+                }
+            }
+        }
+    C ph[4];  // DRIVE: the phasors of the four stage times
     if constexpr (DRIVE) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) ph[s] = a.drive_ph[s];
@@ -140,20 +180,8 @@ __device__ __forceinline__ bool stream_band_spinor(const StepArgs<R>& a, int str
         f.x = fma(c.inv_hbar, zy, f.x);
         f.y = fma(-c.inv_hbar, zx, f.y);
     };
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        acc[0][s] = acc[1][s] = czero<C>();
-        accn[0][s] = accn[1][s] = R(0);
-    }
-#pragma unroll
-    for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) w2[m][s] = w3[m][s] = w4[m][s] = czero<C>();
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) n2[m][s] = n3[m][s] = n4[m][s] = R(0);
 
+    const int npos = B + 8;
     const int start = dir > 0 ? b0 - 4 : b0 + B + 3;
     int g = start;
     int rw = wrap_any(g, a.ny, a.bcy);
@@ -162,30 +190,37 @@ __device__ __forceinline__ bool stream_band_spinor(const StepArgs<R>& a, int str
     const int vr = gcol ? kOutOfRange : ci0 * (int)sizeof(R);
     const int comp_c = (int)(cells * sizeof(C)), comp_r = (int)(cells * sizeof(R));
     const int row_c = a.nx * (int)sizeof(C), row_r = a.nx * (int)sizeof(R);
-    auto fetch = [&](int s, bool use) {
+    auto load_c = [&](__amdgpu_buffer_rsrc_t r, C (&v)[W], int soff) __attribute__((always_inline)) {
+        if constexpr (W == 2) {
+            const wf4 x = wload4(r, vc, soff);
+            v[0] = C{x.x, x.y};
+            v[1] = C{x.z, x.w};
+        } else {
+            v[0] = buf_load<C>(r, vc, soff);
+        }
+    };
+    auto load_r = [&](__amdgpu_buffer_rsrc_t r, R (&v)[W], int soff) __attribute__((always_inline)) {
+        if constexpr (W == 2) {
+            const wf2 x = wload2(r, vr, soff);
+            v[0] = x.x;
+            v[1] = x.y;
+        } else {
+            v[0] = buf_load<R>(r, vr, soff);
+        }
+    };
+    auto fetch = [&](int s, bool use) __attribute__((always_inline)) {
         const bool grow = YZERO && rw < 0;  // uniform
         const int rr = grow ? 0 : rw;
-        sp[0][s] = buf_load<C>(grow ? rnull : rpi, vc, rr * row_c);
-        sp[1][s] = buf_load<C>(grow ? rnull : rpi, vc, comp_c + rr * row_c);
-        if constexpr (DRIVE) {
-            sE[0][s] = buf_load<C>(grow ? rnull : rE, vc, rr * row_c);
-            sE[1][s] = buf_load<C>(grow ? rnull : rE, vc, comp_c + rr * row_c);
-        }
-        if constexpr (IMAG) {
 #pragma unroll
-            for (int m = 0; m < 2; ++m) sp[m][s] = C{sp[m][s].x * sc, sp[m][s].y * sc};
-        }
-        if (RES) {
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                sn[m][s] = buf_load<R>(grow ? rnull : rni, vr, m * comp_r + rr * row_r);
-                sP[m][s] = buf_load<R>(grow ? rnull : rP, vr, m * comp_r + rr * row_r);
+        for (int m = 0; m < 2; ++m) {
+            load_c(grow ? rnull : rpi, sp[m][s], m * comp_c + rr * row_c);
+            if constexpr (DRIVE) load_c(grow ? rnull : rE, sE[m][s], m * comp_c + rr * row_c);
+            if (RES) {
+                load_r(grow ? rnull : rni, sn[m][s], m * comp_r + rr * row_r);
+                load_r(grow ? rnull : rP, sP[m][s], m * comp_r + rr * row_r);
             }
         }
-        if (HASV) {
-            const R vv = buf_load<R>(grow ? rnull : rV, vr, rr * row_r);
-            sk[s] = fma(c.inv_hbar, vv, kdiag);
-        }
+        if (HASV) load_r(grow ? rnull : rV, sk[s], rr * row_r);
         const int gn = g + dir;
         int rn;
         if (YZERO) {
@@ -197,161 +232,150 @@ __device__ __forceinline__ bool stream_band_spinor(const StepArgs<R>& a, int str
         g = use ? gn : g;
         rw = use ? rn : rw;
     };
+    // the row loaded PF positions ago arrives: scaled (IMAG), V turned into the per-cell
+    // constant, and moved out of the register groups that the loads write
+    auto arrive = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                if constexpr (IMAG) sp[m][q][e] = C{sp[m][q][e].x * sc, sp[m][q][e].y * sc};
+                keep_here(sp[m][q][e]);
+                if constexpr (DRIVE) keep_here(sE[m][q][e]);
+                if (RES) {
+                    keep_here(sn[m][q][e]);
+                    keep_here(sP[m][q][e]);
+                }
+            }
+            if (HASV) {
+                sk[q][e] = fma(c.inv_hbar, sk[q][e], kdiag);
+                keep_here(sk[q][e]);
+            }
+        }
+    };
 #pragma unroll
     for (int t = 0; t < PF; ++t) fetch(t, true);
 
     // the lane's step h, or 0 on a ghost row (zero y boundary; uniform over the wave)
     auto row_h = [&](int r, R h) { return (YZERO && (unsigned)r >= (unsigned)a.ny) ? R(0) : h; };
 
-    // neighbour sums and y-differences of one stage argument (rows above, at, below
-    // in walking order) for both components
-    auto sums = [&](const C (&up)[2], const C (&cur)[2], const C (&dn)[2], C (&lr)[2], C (&ud)[2], C (&dy)[2]) {
+    R nf = R(0);  // not 0: a value was not finite
+    const bool out_col = lane >= 4 / W && lane < 64 - 4 / W && gi < a.nx;
+    auto positions = [&](auto phase, int base) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(phase)::value;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            lr[m] = C{lane_prev(cur[m].x) + lane_next(cur[m].x), lane_prev(cur[m].y) + lane_next(cur[m].y)};
-            ud[m] = C{up[m].x + dn[m].x, up[m].y + dn[m].y};
-            dy[m] = C{dn[m].x - up[m].x, dn[m].y - up[m].y};
+        for (int u = 0; u < K; ++u) {
+            const int j = start + dir * (base + u);
+            fetch(slot<K>(u, -PF), base + u + PF < npos);
+            arrive(slot<K>(u, 0));
+#pragma unroll
+            for (int s = 1; s <= 4; ++s) {
+                if (FIRST && u < 2 * s) continue;
+                const int q = slot<K>(u, s), m4 = slot<4>(u, s);
+                const int r = j - s * dir;
+                __builtin_amdgcn_sched_barrier(0);
+                C lr[2][W], ud[2][W], dy[2][W], cur[2][W];
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+#pragma unroll
+                    for (int e = 0; e < W; ++e) {
+                        cur[m][e] = s == 1 ? sp[m][q][e] : w[m][s - 2][m4][e];
+                        const C up = s == 1 ? sp[m][slot<K>(u, 2)][e] : w[m][s - 2][slot<4>(u, s + 1)][e];
+                        const C dn = s == 1 ? sp[m][slot<K>(u, 0)][e] : w[m][s - 2][slot<4>(u, s - 1)][e];
+                        ud[m][e] = C{up.x + dn.x, up.y + dn.y};
+                        dy[m][e] = C{dn.x - up.x, dn.y - up.y};
+                    }
+                    if constexpr (W == 2) {
+                        lr[m][0] = C{lane_prev(cur[m][1].x) + cur[m][1].x, lane_prev(cur[m][1].y) + cur[m][1].y};
+                        lr[m][1] = C{cur[m][0].x + lane_next(cur[m][0].x), cur[m][0].y + lane_next(cur[m][0].y)};
+                    } else {
+                        lr[m][0] = C{lane_prev(cur[m][0].x) + lane_next(cur[m][0].x),
+                                     lane_prev(cur[m][0].y) + lane_next(cur[m][0].y)};
+                    }
+                }
+                const R hk = row_h(r, s == 3 ? kh : kh2);
+#pragma unroll
+                for (int e = 0; e < W; ++e) {
+                    // the mixed difference of each component: right minus left column
+                    C xx[2], f[2];
+                    R fn[2], nn[2], pv[2];
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        if constexpr (W == 2)
+                            xx[m] = e == 0 ? C{dy[m][1].x - lane_prev(dy[m][1].x), dy[m][1].y - lane_prev(dy[m][1].y)}
+                                           : C{lane_next(dy[m][0].x) - dy[m][0].x, lane_next(dy[m][0].y) - dy[m][0].y};
+                        else
+                            xx[m] = C{lane_next(dy[m][0].x) - lane_prev(dy[m][0].x),
+                                      lane_next(dy[m][0].y) - lane_prev(dy[m][0].y)};
+                        nn[m] = s == 1 ? sn[m][q][e] : wn[m][s - 2][m4][e];
+                        pv[m] = sP[m][q][e];
+                    }
+                    const C cu[2] = {cur[0][e], cur[1][e]}, l2[2] = {lr[0][e], lr[1][e]}, u2[2] = {ud[0][e], ud[1][e]};
+                    spinor_rhs<R, RES, IMAG>(c, cu, l2, u2, xx, sk[q][e], bxyd, nn, pv, f, fn);
+                    if constexpr (DRIVE) {
+                        drive(f[0], sE[0][q][e], ph[s - 1]);
+                        drive(f[1], sE[1][q][e], ph[s - 1]);
+                    }
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        C& ac = acc[m][m4][e];
+                        R& an = accn[m][m4][e];
+                        const C p0 = sp[m][q][e];
+                        const R n0 = sn[m][q][e];
+                        if (s < 4) {
+                            ac = s == 1 ? f[m] : C{fma(R(2), f[m].x, ac.x), fma(R(2), f[m].y, ac.y)};
+                            w[m][s - 1][m4][e] = C{fma(hk, f[m].x, p0.x), fma(hk, f[m].y, p0.y)};
+                            keep_here(ac);
+                            keep_here(w[m][s - 1][m4][e]);
+                            if (RES) {
+                                an = s == 1 ? fn[m] : fma(R(2), fn[m], an);
+                                wn[m][s - 1][m4][e] = fma(hk, fn[m], n0);
+                                keep_here(an);
+                                keep_here(wn[m][s - 1][m4][e]);
+                            }
+                        } else {
+                            // the finished row (kept in the dead sums until both columns are done)
+                            ac = C{fma(a.dt6, ac.x + f[m].x, p0.x), fma(a.dt6, ac.y + f[m].y, p0.y)};
+                            if (RES) an = fma(a.dt6, an + fn[m], n0);
+                        }
+                    }
+                }
+                if (s == 4) {
+                    // stored when it lies in the band and in the grid (else the store goes to
+                    // the empty descriptor or an out-of-range column and is dropped)
+                    const bool st = r >= b0 && r < b0 + B && r < a.ny;  // uniform
+                    const int rr = st ? r : 0;
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const int oc = out_col ? gi * (int)sizeof(C) : kOutOfRange;
+                        const int orr = out_col ? gi * (int)sizeof(R) : kOutOfRange;
+                        const C* y = acc[m][m4];
+                        const unsigned off = (unsigned)oc + (unsigned)(m * comp_c + rr * row_c);
+                        if constexpr (W == 2)
+                            wstore4(wf4{y[0].x, y[0].y, y[1].x, y[1].y}, st ? rpo : rnull, (int)off, 0);
+                        else
+                            buf_store_nt(y[0], st ? rpo : rnull, (int)off);
+                        if constexpr (RES)
+                            buf_store_nt(accn[m][m4][0], st ? rno : rnull,
+                                         (int)((unsigned)orr + (unsigned)(m * comp_r + rr * row_r)));
+#pragma unroll
+                        for (int e = 0; e < W; ++e) {
+                            if constexpr (IMAG)
+                                nrm += st && out_col ? (double)y[e].x * y[e].x + (double)y[e].y * y[e].y : 0.0;
+                            // stays 0 while the row's values are finite (a row past the band is
+                            // a row of the grid that another band stores, or a ghost row)
+                            nf = fma(y[e].x, R(0), nf);
+                            nf = fma(y[e].y, R(0), nf);
+                            if (RES) nf = fma(accn[m][m4][e], R(0), nf);
+                        }
+                    }
+                }
+            }
         }
     };
-
-    bool bad = false;
-    const bool out_col = lane >= 4 && lane < 60 && gi < a.nx;
-    for (int base = 0; base < B + 8; base += 24) {
-#pragma unroll
-        for (int u = 0; u < 24; ++u) {
-            const int j = start + dir * (base + u);
-            fetch(slot<8>(u, -PF), base + u + PF < B + 8);
-            C f[2], lr[2], ud[2], dy[2];
-            R fn[2], nn[2], pv[2];
-            // stage 1 at row j-1 from the input ring
-            {
-                const int s0 = slot<8>(u, 1);
-                const C cur[2] = {sp[0][s0], sp[1][s0]};
-                const C up[2] = {sp[0][slot<8>(u, 2)], sp[1][slot<8>(u, 2)]};
-                const C dn[2] = {sp[0][slot<8>(u, 0)], sp[1][slot<8>(u, 0)]};
-                sums(up, cur, dn, lr, ud, dy);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    nn[m] = sn[m][s0];
-                    pv[m] = sP[m][s0];
-                }
-                spinor_rhs<R, RES, IMAG>(c, cur, lr, ud, dy, sk[s0], bxyd, nn, pv, f, fn);
-                if constexpr (DRIVE) {
-                    drive(f[0], sE[0][s0], ph[0]);
-                    drive(f[1], sE[1][s0], ph[0]);
-                }
-                const R hk = row_h(j - 1 * dir, kh2);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    acc[m][slot<4>(u, 1)] = f[m];
-                    w2[m][slot<3>(u, 1)] = C{fma(hk, f[m].x, cur[m].x), fma(hk, f[m].y, cur[m].y)};
-                    if (RES) {
-                        accn[m][slot<4>(u, 1)] = fn[m];
-                        n2[m][slot<2>(u, 1)] = fma(hk, fn[m], sn[m][s0]);
-                    }
-                }
-            }
-            // stage 2 at row j-2 from w2
-            {
-                const int s0 = slot<8>(u, 2);
-                const C cur[2] = {w2[0][slot<3>(u, 2)], w2[1][slot<3>(u, 2)]};
-                const C up[2] = {w2[0][slot<3>(u, 3)], w2[1][slot<3>(u, 3)]};
-                const C dn[2] = {w2[0][slot<3>(u, 1)], w2[1][slot<3>(u, 1)]};
-                sums(up, cur, dn, lr, ud, dy);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    nn[m] = n2[m][slot<2>(u, 2)];
-                    pv[m] = sP[m][s0];
-                }
-                spinor_rhs<R, RES, IMAG>(c, cur, lr, ud, dy, sk[s0], bxyd, nn, pv, f, fn);
-                if constexpr (DRIVE) {
-                    drive(f[0], sE[0][s0], ph[1]);
-                    drive(f[1], sE[1][s0], ph[1]);
-                }
-                const R hk = row_h(j - 2 * dir, kh2);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    C& ac = acc[m][slot<4>(u, 2)];
-                    ac = C{fma(R(2), f[m].x, ac.x), fma(R(2), f[m].y, ac.y)};
-                    const C p0 = sp[m][s0];
-                    w3[m][slot<3>(u, 2)] = C{fma(hk, f[m].x, p0.x), fma(hk, f[m].y, p0.y)};
-                    if (RES) {
-                        accn[m][slot<4>(u, 2)] = fma(R(2), fn[m], accn[m][slot<4>(u, 2)]);
-                        n3[m][slot<2>(u, 2)] = fma(hk, fn[m], sn[m][s0]);
-                    }
-                }
-            }
-            // stage 3 at row j-3 from w3
-            {
-                const int s0 = slot<8>(u, 3);
-                const C cur[2] = {w3[0][slot<3>(u, 3)], w3[1][slot<3>(u, 3)]};
-                const C up[2] = {w3[0][slot<3>(u, 4)], w3[1][slot<3>(u, 4)]};
-                const C dn[2] = {w3[0][slot<3>(u, 2)], w3[1][slot<3>(u, 2)]};
-                sums(up, cur, dn, lr, ud, dy);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    nn[m] = n3[m][slot<2>(u, 3)];
-                    pv[m] = sP[m][s0];
-                }
-                spinor_rhs<R, RES, IMAG>(c, cur, lr, ud, dy, sk[s0], bxyd, nn, pv, f, fn);
-                if constexpr (DRIVE) {
-                    drive(f[0], sE[0][s0], ph[2]);
-                    drive(f[1], sE[1][s0], ph[2]);
-                }
-                const R hk = row_h(j - 3 * dir, kh);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    C& ac = acc[m][slot<4>(u, 3)];
-                    ac = C{fma(R(2), f[m].x, ac.x), fma(R(2), f[m].y, ac.y)};
-                    const C p0 = sp[m][s0];
-                    w4[m][slot<3>(u, 3)] = C{fma(hk, f[m].x, p0.x), fma(hk, f[m].y, p0.y)};
-                    if (RES) {
-                        accn[m][slot<4>(u, 3)] = fma(R(2), fn[m], accn[m][slot<4>(u, 3)]);
-                        n4[m][slot<2>(u, 3)] = fma(hk, fn[m], sn[m][s0]);
-                    }
-                }
-            }
-            // stage 4 at row j-4 from w4; the finished row is stored when it lies in the
-            // band and in the grid
-            {
-                const int s0 = slot<8>(u, 4);
-                const C cur[2] = {w4[0][slot<3>(u, 4)], w4[1][slot<3>(u, 4)]};
-                const C up[2] = {w4[0][slot<3>(u, 5)], w4[1][slot<3>(u, 5)]};
-                const C dn[2] = {w4[0][slot<3>(u, 3)], w4[1][slot<3>(u, 3)]};
-                sums(up, cur, dn, lr, ud, dy);
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    nn[m] = n4[m][slot<2>(u, 4)];
-                    pv[m] = sP[m][s0];
-                }
-                spinor_rhs<R, RES, IMAG>(c, cur, lr, ud, dy, sk[s0], bxyd, nn, pv, f, fn);
-                if constexpr (DRIVE) {
-                    drive(f[0], sE[0][s0], ph[3]);
-                    drive(f[1], sE[1][s0], ph[3]);
-                }
-                const int r = j - 4 * dir;
-                const bool st = out_col && r >= b0 && r < b0 + B && r < a.ny;
-                const int cell = r * a.nx + gi;
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    const C ac = acc[m][slot<4>(u, 4)];
-                    const C p0 = sp[m][s0];
-                    const C y = C{fma(a.dt6, ac.x + f[m].x, p0.x), fma(a.dt6, ac.y + f[m].y, p0.y)};
-                    buf_store_nt(y, rpo, st ? (int)((m * cells + cell) * sizeof(C)) : kOutOfRange);
-                    if constexpr (IMAG) nrm += st ? (double)y.x * y.x + (double)y.y * y.y : 0.0;
-                    bool b = !(isfinite(y.x) && isfinite(y.y));
-                    if (RES) {
-                        const R yn = fma(a.dt6, accn[m][slot<4>(u, 4)] + fn[m], sn[m][s0]);
-                        buf_store_nt(yn, rno, st ? (int)((m * cells + cell) * sizeof(R)) : kOutOfRange);
-                        b = b || !isfinite(yn);
-                    }
-                    bad = bad || (st && b);
-                }
-            }
-        }
-    }
-    if constexpr (IMAG) *norm = nrm;
-    return bad;
+    positions(std::true_type{}, 0);
+    for (int base = K; base < npos; base += K) positions(std::false_type{}, base);
+    finish(out_col && !(nf == R(0)), nrm);
 }
 
 }  // namespace phx

@@ -35,6 +35,13 @@ typedef float wf2 __attribute__((ext_vector_type(2)));
 typedef unsigned int wu4 __attribute__((ext_vector_type(4)));
 typedef unsigned int wu2 __attribute__((ext_vector_type(2)));
 
+// Forms the value here: without this the compiler moves sums that only a later position
+// reads to that position, where their operands then stay live as well.
+__device__ __forceinline__ void keep_here(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void keep_here(double& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void keep_here(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+__device__ __forceinline__ void keep_here(double2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
 constexpr int kWideCols = 120;  // output columns per strip (128 lanes-columns minus 2 x 4 halo)
 
 __device__ __forceinline__ wf4 wload4(__amdgpu_buffer_rsrc_t r, int voff, int soff)
