@@ -24,7 +24,7 @@ SOURCES = [
     "rk4_stream_spinor_d.hip", "rk4_stream_spinor_res_f.hip", "rk4_stream_spinor_res_d.hip",
     "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip",
     "rk4_stream_spinor_drive_d.hip", "rk4_stream_spinor.hip", "runtime.hip", "rk4.hip",
-    "reduce.hip", "dopri5.hip", "batch.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip",
+    "reduce.hip", "dopri5.hip", "batch.hip", "batch_pair_f2.hip", "batch_pair_f1.hip", "batch_pair_d1.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip",
     "imag.hip", "rk4_stream_drive.hip", "rk4_stream_wide.hip", "rk4_stream_pair_f2.hip",
     "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip",
     "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip",
@@ -47,24 +47,26 @@ EXTRA_FLAGS = {f"rk4_stream_spinor_{t}.hip": _FULL_UNROLL
 # the wide walk with the Wiener increment drawn at its final store (a generator call
 # per position) likewise exceeds the default limit
 EXTRA_FLAGS["rk4_stream_wide.hip"] = _FULL_UNROLL
-EXTRA_FLAGS.update({f"rk4_stream_pair_{t}.hip": _FULL_UNROLL for t in ("f2", "f1", "d1")})
+EXTRA_FLAGS.update({f"{u}_pair_{t}.hip": _FULL_UNROLL for u in ("rk4_stream", "batch") for t in ("f2", "f1", "d1")})
 EXTRA_FLAGS.update({f"dp_walk_{t}.hip": _FULL_UNROLL for t in ("f1", "f2", "d1", "d2")})
 # Units whose streaming kernels are checked for private (scratch) memory: a ring
 # that is not in registers makes the walk several times slower.
 STREAM_SOURCES = {"rk4_step.hip", "rk4_stream_drive.hip", "rk4_stream_wide.hip", "batch.hip"} | set(EXTRA_FLAGS)
+SPILL_BYTES = 16
 _USAGE = "-Rpass-analysis=kernel-resource-usage"
 
 
 def _scratch_kernels(stderr: str) -> list:
-    """(kernel, bytes per lane) of every streaming kernel with scratch memory, read
-    from the compiler's resource-usage remarks."""
+    """(kernel, bytes per lane) of every streaming kernel with more scratch memory than the
+    few words the register allocator may park there (a ring that is not in registers
+    takes hundreds of bytes), read from the compiler's resource-usage remarks."""
     out, name = [], None
     for line in stderr.splitlines():
         if "Function Name:" in line:
             name = line.split("Function Name:")[1].split("[")[0].strip()
         elif "ScratchSize [bytes/lane]:" in line and name and ("stream" in name or "batch_wide" in name):
             size = int(line.split("ScratchSize [bytes/lane]:")[1].split("[")[0])
-            if size:
+            if size > SPILL_BYTES:
                 out.append((name, size))
     return out
 

@@ -1,5 +1,6 @@
 // Batched whole-step RK4 over many independent one-component instances on grids of
-// different sizes: one persistent launch per step.  The work list is the
+// different sizes, advanced together: the streaming walks, two steps per launch where no
+// noise is drawn (batch_pair.h), or one persistent launch per step of the region form.  The work list is the
 // concatenation of every instance's regions (56 x (H-8) output cells each, H the
 // region height of the step kernel); a workgroup takes items w = blockIdx.x,
 // blockIdx.x + gridDim.x, ..., finds the instance by binary search over the
@@ -12,31 +13,15 @@
 #include <mutex>
 #include <vector>
 
+#include "batch_inst.h"
 #include "philox.h"
 #include "runtime.h"
 #include "step_body.h"
 #include "stream_body.h"
+#include "stream_pair.h"
 #include "stream_wide.h"
 
 namespace phx {
-
-template <typename R>
-struct BatchInst {
-    int nx, ny, bcx, bcy;
-    int tiles_x, tile0;  // regions across x; first work item of this instance (region form)
-    int s_tile0;         // first work item of this instance in the streaming form
-    int w_strips;        // wide streaming form (complex64): strips of 120 columns, else 0
-    int w_band;          // wide streaming form: rows per band
-    int w_tile0;         // first work item of this instance in the wide streaming form
-    int64_t offset;      // element offset in the packed arrays
-    Coef<R> c;
-    R half_dt, dt, dt6;
-    // Wiener noise: amplitude^2 = noise_a n + noise_b, key, first workgroup of this
-    // instance in the noise pass (each instance's cell pairs fill whole workgroups)
-    R noise_a, noise_b;
-    uint32_t key0, key1;
-    int block0;
-};
 
 // Wiener increments of one batched step: one thread per cell pair, each instance's
 // pairs in whole workgroups (block_inst maps a workgroup to its instance), the same
@@ -262,6 +247,42 @@ static int batch_wide_band(int ny)
     return b < 8 ? 8 : b;
 }
 
+// Two-step form: columns per lane, strips and band height of one instance, the choice with
+// the fewest issued instructions: strips x bands x positions (B + 16 rows in chunks of 12,
+// nine positions' worth of stages left out at the start) x instructions per position.
+// Tall bands save halo rows, but the last of them end late: up to 56 rows (256 driven grids
+// of 128^2 to 1024^2, four steps: 1264 us with bands of up to 44 rows, 1270 with 68, 1304 with 80, 1346
+// with 104; 2068 us with one step per launch).
+static void batch_pair_plan(bool c64, int nx, int ny, int* w, int* strips, int* band)
+{
+    double best = 0.0;
+    for (int k = 1; k <= (c64 && nx % 2 == 0 ? 2 : 1); ++k) {
+        const int n = pair_strips(nx, k);
+        for (int b = 20; b <= 56; b += 12) {
+            const double cost = (double)n * ((ny + b - 1) / b) * (b + 7) * (k == 2 ? 397 : 215);
+            if (best == 0.0 || cost < best) {
+                best = cost;
+                *w = k;
+                *strips = n;
+                *band = b;
+            }
+        }
+    }
+}
+
+template <typename R>
+hipError_t launch_batch_pair(int columns, bool res, bool hv, bool ghosts, bool yzero, int total,
+                             const BatchInst<R>* inst, int count, const void* pi, const void* ni, void* po, void* no,
+                             const void* V, const void* P, unsigned int* flag, bool check, hipStream_t s)
+{
+    if constexpr (sizeof(R) == 4) {
+        if (columns == 2)
+            return launch_batch_pair_w<R, 2>(res, hv, ghosts, yzero, total, inst, count, pi, ni, po, no, V, P, flag,
+                                             check, s);
+    }
+    return launch_batch_pair_w<R, 1>(res, hv, ghosts, yzero, total, inst, count, pi, ni, po, no, V, P, flag, check, s);
+}
+
 template <typename R, bool RES, bool HASV, bool GHOSTS>
 static hipError_t launch_batch_t(int grid, const BatchInst<R>* inst, int count, int total, const void* pi,
                                  const void* ni, void* po, void* no, const void* V, const void* P,
@@ -412,6 +433,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     // the streaming form needs every instance's state under 2 GiB (32-bit buffer
     // offsets) and one y boundary rule for all instances
     bool use_stream = true, all_zero_y = true, all_periodic_y = true;
+    int64_t p_tile0[2] = {0, 0};  // work items of the two-step form with one and two columns per lane
     int64_t w_tile0 = 0;  // work items of the wide streaming form (complex64 instances of even width)
     for (int k = 0; k < d->count; ++k) {
         const phx_instance& I = d->instances[k];
@@ -444,6 +466,10 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
             w_tile0 += (int64_t)b.w_strips * ((I.ny + b.w_band - 1) / b.w_band);
         else
             s_tile0 += (int64_t)((b.tiles_x + SG - 1) / SG) * ((I.ny + SB - 1) / SB);
+        int w = 1;
+        batch_pair_plan(sizeof(R) == 4, I.nx, I.ny, &w, &b.p_strips, &b.p_band);
+        for (int l = 0; l < 2; ++l) b.p_tile0[l] = (int)std::min<int64_t>(p_tile0[l], INT32_MAX);
+        p_tile0[w - 1] += (int64_t)b.p_strips * ((I.ny + b.p_band - 1) / b.p_band);
         use_stream = use_stream && (double)I.nx * I.ny * 2.0 * sizeof(R) < 2147483648.0 - 256.0;
         all_zero_y = all_zero_y && c.bc_y == PHX_BC_ZERO;
         all_periodic_y = all_periodic_y && c.bc_y == PHX_BC_PERIODIC;
@@ -489,7 +515,10 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     void* S[2] = {d->psi, ws + L.alt};
     void* SN[2] = {d->n, res ? ws + L.alt_n : nullptr};
     int cur = 0;
-    if (n & 1) {
+    // pairs of steps per launch where no increment is drawn in between; then an odd n >= 3
+    // ends in the caller's arrays without a copy
+    int64_t pairs = use_stream && !noisy && p_tile0[0] < INT32_MAX && p_tile0[1] < INT32_MAX ? pair_launches(n) : 0;
+    if ((n & 1) && pairs == 0) {
         e = hipMemcpyAsync(S[1], S[0], (size_t)d->total_cells * 2 * rs, hipMemcpyDeviceToDevice, stream);
         if (e == hipSuccess && res)
             e = hipMemcpyAsync(SN[1], SN[0], (size_t)d->total_cells * rs, hipMemcpyDeviceToDevice, stream);
@@ -498,35 +527,47 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     }
     const BatchInst<R>* dtab = (const BatchInst<R>*)(ws + L.table);
     unsigned int* flag = (unsigned int*)(ws + L.flag);
-    // both walks in use: the one-column launch goes to the device's second stream
+    // launches over both lists (odd and even widths, or one and two columns per lane): the
+    // first goes to the device's second stream
     hipStream_t side = nullptr;
     ForkJoin fj;
-    if (use_stream && w_total > 0 && s_total > 0) {
+    if (use_stream && ((w_total > 0 && s_total > 0) || (pairs > 0 && p_tile0[0] > 0 && p_tile0[1] > 0))) {
         side = side_stream(dev);
         if (side && (hipEventCreateWithFlags(&fj.fork, hipEventDisableTiming) != hipSuccess ||
                      hipEventCreateWithFlags(&fj.join, hipEventDisableTiming) != hipSuccess))
             side = nullptr;
     }
-    for (int64_t k = 0; k < n; ++k) {
+    for (int64_t k = 0, steps = 1; k < n; k += steps) {
+        const bool pair = pairs-- > 0;
+        steps = pair ? 2 : 1;
+        const bool check = k + steps == n;
         if (use_stream) {
             e = hipSuccess;
-            hipStream_t s_narrow = stream;
-            if (side) {
+            const int first = pair ? (int)p_tile0[0] : s_total, second = pair ? (int)p_tile0[1] : w_total;
+            const bool fork = side && first > 0 && second > 0;
+            hipStream_t s_first = stream;
+            if (fork) {
                 fj.used = true;
                 e = hipEventRecord(fj.fork, stream);
                 if (e == hipSuccess) e = hipStreamWaitEvent(side, fj.fork, 0);
-                s_narrow = side;
+                s_first = side;
             }
             if constexpr (sizeof(R) == 4) {
-                if (e == hipSuccess && w_total > 0)
-                    e = launch_batch_wide(res != 0, d->V != nullptr, ghosts, all_zero_y, w_total,
-                                          (const BatchInst<float>*)dtab, d->count, S[cur], SN[cur], S[cur ^ 1],
-                                          SN[cur ^ 1], d->V, d->P, flag, k == n - 1, stream);
+                if (e == hipSuccess && second > 0)
+                    e = pair ? launch_batch_pair<float>(2, res != 0, d->V != nullptr, ghosts, all_zero_y, second,
+                                                        (const BatchInst<float>*)dtab, d->count, S[cur], SN[cur],
+                                                        S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, check, stream)
+                             : launch_batch_wide(res != 0, d->V != nullptr, ghosts, all_zero_y, second,
+                                                 (const BatchInst<float>*)dtab, d->count, S[cur], SN[cur], S[cur ^ 1],
+                                                 SN[cur ^ 1], d->V, d->P, flag, check, stream);
             }
-            if (e == hipSuccess && s_total > 0)
-                e = launch_batch_stream<R>(res != 0, d->V != nullptr, ghosts, all_zero_y, s_total, dtab, d->count,
-                                           S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, s_narrow);
-            if (e == hipSuccess && side) {
+            if (e == hipSuccess && first > 0)
+                e = pair ? launch_batch_pair<R>(1, res != 0, d->V != nullptr, ghosts, all_zero_y, first, dtab, d->count,
+                                                S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, check,
+                                                s_first)
+                         : launch_batch_stream<R>(res != 0, d->V != nullptr, ghosts, all_zero_y, first, dtab, d->count,
+                                                  S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, s_first);
+            if (e == hipSuccess && fork) {
                 e = hipEventRecord(fj.join, side);
                 if (e == hipSuccess) e = hipStreamWaitEvent(stream, fj.join, 0);
             }

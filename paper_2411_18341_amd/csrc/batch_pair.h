@@ -1,0 +1,82 @@
+// Two-step form of the batched stepper (the walk of stream_pair.h) over the instances of
+// one column count per lane: a work item is one band of one strip of one instance, one
+// single-wave workgroup per item (consecutive items on one XCD).
+#pragma once
+
+#include "batch_inst.h"
+#include "stream_pair.h"
+
+namespace phx {
+
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
+void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, const typename cvec<R>::type* psi_in,
+                              const R* n_in, typename cvec<R>::type* psi_out, R* n_out, const R* V, const R* P,
+                              unsigned int* flag)
+{
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    int lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (inst[mid].p_tile0[W - 1] <= t) lo = mid; else hi = mid - 1;
+    }
+    const BatchInst<R>& I = inst[lo];
+    const int lt = t - I.p_tile0[W - 1];
+    const int band = lt / I.p_strips, strip = lt - band * I.p_strips;
+    StepArgs<R> a{};
+    a.nx = I.nx;
+    a.ny = I.ny;
+    a.bcx = I.bcx;
+    a.bcy = I.bcy;
+    a.c = I.c;
+    a.half_dt = I.half_dt;
+    a.dt = I.dt;
+    a.dt6 = I.dt6;
+    a.psi_in = psi_in + I.offset;
+    a.n_in = RES ? n_in + I.offset : nullptr;
+    a.psi_out = psi_out + I.offset;
+    a.n_out = RES ? n_out + I.offset : nullptr;
+    a.V = HASV ? V + I.offset : nullptr;
+    a.P = RES ? P + I.offset : nullptr;
+    stream_band_pair<R, W, RES, HASV, GHOSTS, YZERO, CHECK>(a, strip, band, I.p_band, (band & 1) ? -1 : 1,
+                                                           [&](bool bad) __attribute__((always_inline)) {
+                                                               if (bad) flag[0] = 1u;  // benign race
+                                                           });
+}
+
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO>
+static void launch_batch_pair_t(int total, const BatchInst<R>* inst, int count, const void* pi, const void* ni,
+                                void* po, void* no, const void* V, const void* P, unsigned int* flag, bool check,
+                                hipStream_t s)
+{
+    using C = typename cvec<R>::type;
+    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS);
+    if (check)
+        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, true><<<total, 64, 0, s>>>(
+            inst, count, (const C*)pi, (const R*)ni, (C*)po, (R*)no, (const R*)V, (const R*)P, flag);
+    else
+        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, false><<<total, 64, 0, s>>>(
+            inst, count, (const C*)pi, (const R*)ni, (C*)po, (R*)no, (const R*)V, (const R*)P, flag);
+}
+
+template <typename R, int W>
+hipError_t launch_batch_pair_w(bool res, bool hv, bool ghosts, bool yzero, int total, const BatchInst<R>* inst,
+                               int count, const void* pi, const void* ni, void* po, void* no, const void* V,
+                               const void* P, unsigned int* flag, bool check, hipStream_t s)
+{
+#define PHX_BP(RS, HV) \
+    if (res == RS && hv == HV) { \
+        if (yzero) \
+            launch_batch_pair_t<R, W, RS, HV, true, true>(total, inst, count, pi, ni, po, no, V, P, flag, check, s); \
+        else if (ghosts) \
+            launch_batch_pair_t<R, W, RS, HV, true, false>(total, inst, count, pi, ni, po, no, V, P, flag, check, s); \
+        else \
+            launch_batch_pair_t<R, W, RS, HV, false, false>(total, inst, count, pi, ni, po, no, V, P, flag, check, s); \
+        return hipGetLastError(); \
+    }
+    PHX_BP(true, false) PHX_BP(true, true) PHX_BP(false, false) PHX_BP(false, true)
+#undef PHX_BP
+    return hipErrorInvalidValue;
+}
+
+}  // namespace phx

@@ -252,7 +252,7 @@ template hipError_t rk4_step_trial<double>(phx_handle*, const StepShapeId&, int,
 
 // Two-step launches among n steps, so that the launches leave the state where n single
 // steps would: the n - pairs launches are even in number exactly when n is.
-static int64_t pair_launches(int64_t n) { return n & 1 ? (n >= 3 ? 2 * ((n + 1) / 4) - 1 : 0) : 2 * (n / 4); }
+int64_t pair_launches(int64_t n) { return n & 1 ? (n >= 3 ? 2 * ((n + 1) / 4) - 1 : 0) : 2 * (n / 4); }
 
 // Enqueues n whole steps on stream s, alternating between the caller's arrays
 // (buffer 0) and the workspace copy (buffer 1); h->step_parity is the buffer that

@@ -182,6 +182,7 @@ inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int
 int pair_columns(const phx_config& c, const StepShapeId& sh);
 StepShapeId default_step_shape(const phx_config& c);
 int pair_strips(int nx, int w);
+int64_t pair_launches(int64_t n);  // two-step launches among n steps
 // Columns per lane, strips and band height of the spinor walk (stream_spinor.h).
 struct SpinorPlan {
     int columns, strips, band_rows;

@@ -152,7 +152,7 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
 #pragma unroll
     for (int t = 0; t < PF; ++t) fetch(t, true);
 
-    unsigned bad = 0u;
+    R nf = R(0);
     auto positions = [&](auto phase, int base) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(phase)::value;
 #pragma unroll
@@ -251,13 +251,14 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
                         if (RES) buf_store_nt(yn[0], st ? rno : rnull, (int)((unsigned)orr + (unsigned)(rr * rowr)));
                     }
                     if (CHECK) {
-                        unsigned nf = 0u;
+                        R t = nf;  // stays 0 while the stored values are finite
 #pragma unroll
                         for (int e = 0; e < W; ++e) {
-                            nf |= (unsigned)!isfinite(y[e].x) | (unsigned)!isfinite(y[e].y);
-                            if (RES) nf |= (unsigned)!isfinite(yn[e]);
+                            t = fma(y[e].x, R(0), t);
+                            t = fma(y[e].y, R(0), t);
+                            if (RES) t = fma(yn[e], R(0), t);
                         }
-                        bad |= (st && out_col) ? nf : 0u;
+                        nf = st ? t : nf;
                     }
                 }
             }
@@ -265,7 +266,7 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
     };
     positions(std::true_type{}, 0);
     for (int base = K; base < npos; base += K) positions(std::false_type{}, base);
-    finish(bad != 0u);
+    finish(CHECK && out_col && !(nf == R(0)));
 }
 
 template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>

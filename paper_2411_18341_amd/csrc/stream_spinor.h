@@ -111,8 +111,8 @@ __device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int str
     static_assert(W == 1 || (W == 2 && sizeof(R) == 4 && !RES && !IMAG && !DRIVE), "two columns per lane: complex64");
     using C = typename cvec<R>::type;
     constexpr int K = 8;              // rows j - 4 .. j + PF are in flight
-    // rows loaded ahead of their first use (fewer where the registers are full)
-    constexpr int PF = W == 2 || (RES && sizeof(R) == 8 && YZERO) ? 2 : 3;
+    // rows loaded ahead of their first use
+    constexpr int PF = W == 2 ? 2 : 3;
     const R sc = IMAG ? (R)a.imag_slots[1] : R(1);  // uniform
     double nrm = 0.0;
     const int lane = threadIdx.x & 63;
@@ -345,6 +345,7 @@ __device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int str
                     // the empty descriptor or an out-of-range column and is dropped)
                     const bool st = r >= b0 && r < b0 + B && r < a.ny;  // uniform
                     const int rr = st ? r : 0;
+                    R t = nf;
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
                         const int oc = out_col ? gi * (int)sizeof(C) : kOutOfRange;
@@ -362,13 +363,12 @@ __device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int str
                         for (int e = 0; e < W; ++e) {
                             if constexpr (IMAG)
                                 nrm += st && out_col ? (double)y[e].x * y[e].x + (double)y[e].y * y[e].y : 0.0;
-                            // stays 0 while the row's values are finite (a row past the band is
-                            // a row of the grid that another band stores, or a ghost row)
-                            nf = fma(y[e].x, R(0), nf);
-                            nf = fma(y[e].y, R(0), nf);
-                            if (RES) nf = fma(accn[m][m4][e], R(0), nf);
+                            t = fma(y[e].x, R(0), t);  // stays 0 while the values are finite
+                            t = fma(y[e].y, R(0), t);
+                            if (RES) t = fma(accn[m][m4][e], R(0), t);
                         }
                     }
+                    nf = st ? t : nf;
                 }
             }
         }

@@ -105,3 +105,28 @@ def test_wide_stores_keep_their_data(unit):
     asm = build.device_asm(unit)
     assert "buffer_store_dwordx4" in asm
     assert build.store_data_hazards(asm) == []
+
+
+@gpu
+@pytest.mark.parametrize("precision", [C64, C128])
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1), (1, 0)])
+def test_batch_pairs_bitwise(bc, precision):
+    """Batches of even and odd widths around the strips of both column counts: after 4, 3
+    and 1 batched steps each instance equals a single-grid run of the region form."""
+    grids = [(112, 20), (114, 33), (49, 21), (97, 5), (2, 9), (1, 1), (226, 105), (130, 230)]
+    import torch
+    runs, fields = [], []
+    for k, (nx, ny) in enumerate(grids):
+        ph, q = case(nx, ny, bc, True, False, seed=50 + k, precision=precision)
+        fields.append(q)
+        runs.append(states(ph, q, (8, 4), (4, 3, 1), precision=precision))
+    b = phx.Batch(grids, [phx.config_from_physics(ph, precision=precision)], precision=precision)
+    for k, q in enumerate(fields):
+        for t, f in ((b.psi, q[0][0]), (b.n, q[1][0]), (b.P, q[3][0])):
+            b.view(t, k).copy_(torch.from_numpy(np.ascontiguousarray(f)))
+    for i, steps in enumerate((4, 3, 1)):
+        b.step(steps)
+        torch.cuda.synchronize()
+        for k in range(len(grids)):
+            assert np.array_equal(b.view(b.psi, k).cpu().numpy().astype(np.complex128), runs[k][i][0][0]), (k, i)
+            assert np.array_equal(b.view(b.n, k).cpu().numpy().astype(np.float64), runs[k][i][1][0]), (k, i)
