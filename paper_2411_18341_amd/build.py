@@ -24,8 +24,9 @@ SOURCES = [
     "rk4_stream_spinor_d.hip", "rk4_stream_spinor_res_f.hip", "rk4_stream_spinor_res_d.hip",
     "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip",
     "rk4_stream_spinor_drive_d.hip", "rk4_stream_spinor.hip", "runtime.hip", "rk4.hip",
-    "reduce.hip", "dopri5.hip", "batch.hip", "batch_pair_f2.hip", "batch_pair_f1.hip", "batch_pair_d1.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip",
-    "imag.hip", "rk4_stream_drive.hip", "rk4_stream_wide.hip", "rk4_stream_pair_f2.hip",
+    "reduce.hip", "dopri5.hip", "batch.hip", "batch_pair_f2.hip", "batch_pair_f1.hip",
+    "batch_pair_d1.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive_f.hip", "rk4_stream_drive_d.hip", "rk4_stream_wide.hip", "rk4_stream_one_f.hip",
+    "rk4_stream_one_d.hip", "batch_one_f.hip", "batch_one_d.hip", "rk4_stream_pair_f2.hip",
     "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip",
     "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip",
 ]
@@ -37,21 +38,19 @@ FLAGS = [
     "-Wall", "-Wno-unused-function", "-I", INCLUDE, "-I", CSRC,
 ]
 
-# The streaming whole-step kernels keep their row rings in registers only when the
-# walk's 24-row loop is unrolled completely (every ring index is then a constant);
-# the two-component walk with reservoirs is larger than LLVM's default size limit
-# for a requested full unroll, so its unit raises that limit.
+# The streaming kernels keep their row rings in registers only when the positions of
+# their chunks are unrolled completely (every ring index is then a constant); the larger
+# ones exceed LLVM's default size limit for a requested full unroll, so their units raise it.
 _FULL_UNROLL = ["-mllvm", "-pragma-unroll-threshold=40000"]
 EXTRA_FLAGS = {f"rk4_stream_spinor_{t}.hip": _FULL_UNROLL
                for t in ("f2", "f1", "d", "res_f", "res_d", "imag_f", "imag_d", "drive_f", "drive_d")}
-# the wide walk with the Wiener increment drawn at its final store (a generator call
-# per position) likewise exceeds the default limit
-EXTRA_FLAGS["rk4_stream_wide.hip"] = _FULL_UNROLL
+EXTRA_FLAGS.update({f"rk4_stream_{t}.hip": _FULL_UNROLL for t in ("wide", "one_f", "one_d", "drive_f", "drive_d")})
+EXTRA_FLAGS.update({u: _FULL_UNROLL for u in ("batch.hip", "batch_one_f.hip", "batch_one_d.hip")})
 EXTRA_FLAGS.update({f"{u}_pair_{t}.hip": _FULL_UNROLL for u in ("rk4_stream", "batch") for t in ("f2", "f1", "d1")})
 EXTRA_FLAGS.update({f"dp_walk_{t}.hip": _FULL_UNROLL for t in ("f1", "f2", "d1", "d2")})
 # Units whose streaming kernels are checked for private (scratch) memory: a ring
 # that is not in registers makes the walk several times slower.
-STREAM_SOURCES = {"rk4_step.hip", "rk4_stream_drive.hip", "rk4_stream_wide.hip", "batch.hip"} | set(EXTRA_FLAGS)
+STREAM_SOURCES = set(EXTRA_FLAGS)
 SPILL_BYTES = 16
 _USAGE = "-Rpass-analysis=kernel-resource-usage"
 
@@ -64,7 +63,7 @@ def _scratch_kernels(stderr: str) -> list:
     for line in stderr.splitlines():
         if "Function Name:" in line:
             name = line.split("Function Name:")[1].split("[")[0].strip()
-        elif "ScratchSize [bytes/lane]:" in line and name and ("stream" in name or "batch_wide" in name):
+        elif "ScratchSize [bytes/lane]:" in line and name and "stream" in name:
             size = int(line.split("ScratchSize [bytes/lane]:")[1].split("[")[0])
             if size > SPILL_BYTES:
                 out.append((name, size))

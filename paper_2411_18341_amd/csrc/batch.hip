@@ -1,11 +1,12 @@
 // Batched whole-step RK4 over many independent one-component instances on grids of
 // different sizes, advanced together: the streaming walks, two steps per launch where no
-// noise is drawn (batch_pair.h), or one persistent launch per step of the region form.  The work list is the
-// concatenation of every instance's regions (56 x (H-8) output cells each, H the
-// region height of the step kernel); a workgroup takes items w = blockIdx.x,
-// blockIdx.x + gridDim.x, ..., finds the instance by binary search over the
-// instances' first item, and runs the same device code as the single-grid
-// whole-step kernel on that instance's slice of the packed arrays.
+// noise is drawn (batch_pair.h) and one otherwise (batch_walk.h), or one persistent launch
+// per step of the region form (a state of 2 GiB, mixed y boundaries).  The region form's
+// work list is the concatenation of every instance's regions (56 x (H-8) output cells each,
+// H the region height of the step kernel); a workgroup takes items w = blockIdx.x,
+// blockIdx.x + gridDim.x, ..., finds the instance by binary search over the instances'
+// first item, and runs the same device code as the single-grid whole-step kernel on that
+// instance's slice of the packed arrays.
 #include <math.h>
 #include <string.h>
 
@@ -13,13 +14,11 @@
 #include <mutex>
 #include <vector>
 
-#include "batch_inst.h"
+#include "batch_walk.h"
 #include "philox.h"
 #include "runtime.h"
 #include "step_body.h"
-#include "stream_body.h"
 #include "stream_pair.h"
-#include "stream_wide.h"
 
 namespace phx {
 
@@ -85,166 +84,21 @@ __global__ __launch_bounds__(WAVES * 64) void batch_step_kernel(
 // region shape of the batched kernel per precision (8 waves x 4 rows)
 constexpr int BW = 8, BR = 4;
 
-// Streaming form of the batched step (the band walk of stream_body.h): a work item is
-// one band of SB rows of SG adjacent strips of one instance, one workgroup per item
-// (consecutive items on one XCD); tiles_x counts an instance's strips of 56 columns.
-// Single-strip items (one wave each) measured 1 % faster on the batched workload than
-// groups of 2 or 4 strips, whose waves share nothing.  YZERO: every instance has a
-// zero y boundary (else every one is periodic in y).
-constexpr int SB = 40, SG = 1;
-
-template <typename R, bool RES, bool HASV, bool GHOSTS, bool YZERO>
-__global__ __launch_bounds__(64 * SG) void batch_stream_kernel(
-    const BatchInst<R>* __restrict__ inst, int count, const typename cvec<R>::type* psi_in, const R* n_in,
-    typename cvec<R>::type* psi_out, R* n_out, const R* V, const R* P, unsigned int* flag)
+// Relative time of a list of `waves` bands that take `positions` each: the issue of the
+// busiest SIMD (a single wave reaches 0.82 of the rate), half a wave more for the tail.
+static double list_cost(int64_t waves, int positions, int simds)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (inst[mid].s_tile0 <= t) lo = mid; else hi = mid - 1;
-    }
-    const BatchInst<R>& I = inst[lo];
-    const int lt = t - I.s_tile0;
-    const int gx = (I.tiles_x + SG - 1) / SG;
-    const int band = lt / gx, strip = (lt - band * gx) * SG + wave;
-    if (strip >= I.tiles_x) return;
-    StepArgs<R> a{};
-    a.nx = I.nx;
-    a.ny = I.ny;
-    a.bcx = I.bcx;
-    a.bcy = I.bcy;
-    a.tiles_x = I.tiles_x;
-    a.c = I.c;
-    a.half_dt = I.half_dt;
-    a.dt = I.dt;
-    a.dt6 = I.dt6;
-    a.psi_in = psi_in + I.offset;
-    a.n_in = RES ? n_in + I.offset : nullptr;
-    a.psi_out = psi_out + I.offset;
-    a.n_out = RES ? n_out + I.offset : nullptr;
-    a.V = HASV ? V + I.offset : nullptr;
-    a.P = RES ? P + I.offset : nullptr;
-    a.comps = 1;
-    if (stream_band<R, RES, HASV, GHOSTS, YZERO, SB>(a, strip, band, (band & 1) ? -1 : 1))
-        flag[0] = 1u;  // benign race: every writer stores 1
+    return positions * (std::max(1.2, (double)waves / simds) + 0.5);
 }
 
-template <typename R, bool RES, bool HASV, bool GHOSTS, bool YZERO>
-static hipError_t launch_batch_stream_t(int total, const BatchInst<R>* inst, int count, const void* pi,
-                                        const void* ni, void* po, void* no, const void* V, const void* P,
-                                        unsigned int* flag, hipStream_t s)
+// Band height of the one-step walk, a multiple of 8 rows evened out over an instance's
+// bands; the tallest is the cheapest by list_cost (16 grids of 256^2: bands of 8 rows, 1536
+// waves; the step took 31.6 us with bands of 48 and takes 14).  Drawing the increments in
+// the step: 128 noisy grids of 256^2, eight steps, 762 us with the separate pass, 562 now.
+static int batch_step_band(int ny, int cap)
 {
-    using C = typename cvec<R>::type;
-    batch_stream_kernel<R, RES, HASV, GHOSTS, YZERO><<<total, 64 * SG, 0, s>>>(
-        inst, count, (const C*)pi, (const R*)ni, (C*)po, (R*)no, (const R*)V, (const R*)P, flag);
-    return hipGetLastError();
-}
-
-template <typename R>
-static hipError_t launch_batch_stream(bool res, bool hv, bool ghosts, bool yzero, int total, const BatchInst<R>* inst,
-                                      int count, const void* pi, const void* ni, void* po, void* no, const void* V,
-                                      const void* P, unsigned int* flag, hipStream_t s)
-{
-#define PHX_BS(RS, HV, G, Y) \
-    if (res == RS && hv == HV && ghosts == G && yzero == Y) \
-        return launch_batch_stream_t<R, RS, HV, G, Y>(total, inst, count, pi, ni, po, no, V, P, flag, s)
-    PHX_BS(true, false, false, false); PHX_BS(true, true, false, false);
-    PHX_BS(false, false, false, false); PHX_BS(false, true, false, false);
-    PHX_BS(true, false, true, false); PHX_BS(true, true, true, false);
-    PHX_BS(false, false, true, false); PHX_BS(false, true, true, false);
-    PHX_BS(true, false, true, true); PHX_BS(true, true, true, true);
-    PHX_BS(false, false, true, true); PHX_BS(false, true, true, true);
-#undef PHX_BS
-    return hipErrorInvalidValue;
-}
-
-// Wide streaming form of the batched step (the two-column walk of stream_wide.h) for
-// complex64 instances of even width: a work item is one band of an instance's w_band
-// rows of one 120-column strip, one single-wave workgroup per item (consecutive items
-// on one XCD).  The register budget per wave and the testing variant (CHECK, the last
-// step of a call) follow the single-grid wide kernel with the 8-row ring.
-template <bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
-void batch_wide_kernel(const BatchInst<float>* __restrict__ inst, int count, const float2* psi_in, const float* n_in,
-                       float2* psi_out, float* n_out, const float* V, const float* P, unsigned int* flag)
-{
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (inst[mid].w_tile0 <= t) lo = mid; else hi = mid - 1;
-    }
-    const BatchInst<float>& I = inst[lo];
-    const int lt = t - I.w_tile0;
-    const int band = lt / I.w_strips, strip = lt - band * I.w_strips;
-    StepArgs<float> a{};
-    a.nx = I.nx;
-    a.ny = I.ny;
-    a.bcx = I.bcx;
-    a.bcy = I.bcy;
-    a.tiles_x = I.w_strips;
-    a.c = I.c;
-    a.half_dt = I.half_dt;
-    a.dt = I.dt;
-    a.dt6 = I.dt6;
-    a.psi_in = psi_in + I.offset;
-    a.n_in = RES ? n_in + I.offset : nullptr;
-    a.psi_out = psi_out + I.offset;
-    a.n_out = RES ? n_out + I.offset : nullptr;
-    a.V = HASV ? V + I.offset : nullptr;
-    a.P = RES ? P + I.offset : nullptr;
-    a.comps = 1;
-    a.band_rows = I.w_band;
-    if (stream_band_wide<RES, HASV, GHOSTS, YZERO, 8, 3, CHECK>(a, strip, band, I.w_band, (band & 1) ? -1 : 1))
-        flag[0] = 1u;  // benign race: every writer stores 1
-}
-
-template <bool RES, bool HASV, bool GHOSTS, bool YZERO>
-static hipError_t launch_batch_wide_t(int total, const BatchInst<float>* inst, int count, const void* pi,
-                                      const void* ni, void* po, void* no, const void* V, const void* P,
-                                      unsigned int* flag, bool check, hipStream_t s)
-{
-    constexpr int WPE = !(RES && (HASV || GHOSTS)) ? 3 : 2;
-    constexpr int WPE_CHECK = RES ? 2 : WPE;
-    if (check)
-        batch_wide_kernel<RES, HASV, GHOSTS, YZERO, WPE_CHECK, true><<<total, 64, 0, s>>>(
-            inst, count, (const float2*)pi, (const float*)ni, (float2*)po, (float*)no, (const float*)V,
-            (const float*)P, flag);
-    else
-        batch_wide_kernel<RES, HASV, GHOSTS, YZERO, WPE, false><<<total, 64, 0, s>>>(
-            inst, count, (const float2*)pi, (const float*)ni, (float2*)po, (float*)no, (const float*)V,
-            (const float*)P, flag);
-    return hipGetLastError();
-}
-
-static hipError_t launch_batch_wide(bool res, bool hv, bool ghosts, bool yzero, int total,
-                                    const BatchInst<float>* inst, int count, const void* pi, const void* ni, void* po,
-                                    void* no, const void* V, const void* P, unsigned int* flag, bool check,
-                                    hipStream_t s)
-{
-#define PHX_BW(RS, HV, G, Y) \
-    if (res == RS && hv == HV && ghosts == G && yzero == Y) \
-        return launch_batch_wide_t<RS, HV, G, Y>(total, inst, count, pi, ni, po, no, V, P, flag, check, s)
-    PHX_BW(true, false, false, false); PHX_BW(true, true, false, false);
-    PHX_BW(false, false, false, false); PHX_BW(false, true, false, false);
-    PHX_BW(true, false, true, false); PHX_BW(true, true, true, false);
-    PHX_BW(false, false, true, false); PHX_BW(false, true, true, false);
-    PHX_BW(true, false, true, true); PHX_BW(true, true, true, true);
-    PHX_BW(false, false, true, true); PHX_BW(false, true, true, true);
-#undef PHX_BW
-    return hipErrorInvalidValue;
-}
-
-// Band height of the batched wide walk: about 48 rows, evened out over an instance's
-// bands (the walk's 8 halo rows per band then cover no empty rows).
-constexpr int kBatchWideRows = 48;
-static int batch_wide_band(int ny)
-{
-    const int bands = (ny + kBatchWideRows - 1) / kBatchWideRows;
-    const int b = (ny + bands - 1) / bands;
-    return b < 8 ? 8 : b;
+    const int bands = (ny + cap - 1) / cap;
+    return ((ny + bands - 1) / bands + 7) / 8 * 8;
 }
 
 // Two-step form: columns per lane, strips and band height of one instance, the choice with
@@ -252,13 +106,13 @@ static int batch_wide_band(int ny)
 // nine positions' worth of stages left out at the start) x instructions per position.
 // Tall bands save halo rows, but the last of them end late: up to 56 rows (256 driven grids
 // of 128^2 to 1024^2, four steps: 1264 us with bands of up to 44 rows, 1270 with 68, 1304 with 80, 1346
-// with 104; 2068 us with one step per launch).
-static void batch_pair_plan(bool c64, int nx, int ny, int* w, int* strips, int* band)
+// with 104; 2068 us with one step per launch), fewer where the device would not be full.
+static void batch_pair_plan(bool c64, int nx, int ny, int cap, int* w, int* strips, int* band)
 {
     double best = 0.0;
     for (int k = 1; k <= (c64 && nx % 2 == 0 ? 2 : 1); ++k) {
         const int n = pair_strips(nx, k);
-        for (int b = 20; b <= 56; b += 12) {
+        for (int b = 20; b <= cap; b += 12) {
             const double cost = (double)n * ((ny + b - 1) / b) * (b + 7) * (k == 2 ? 397 : 215);
             if (best == 0.0 || cost < best) {
                 best = cost;
@@ -270,18 +124,15 @@ static void batch_pair_plan(bool c64, int nx, int ny, int* w, int* strips, int* 
     }
 }
 
-template <typename R>
-hipError_t launch_batch_pair(int columns, bool res, bool hv, bool ghosts, bool yzero, int total,
-                             const BatchInst<R>* inst, int count, const void* pi, const void* ni, void* po, void* no,
-                             const void* V, const void* P, unsigned int* flag, bool check, hipStream_t s)
-{
-    if constexpr (sizeof(R) == 4) {
-        if (columns == 2)
-            return launch_batch_pair_w<R, 2>(res, hv, ghosts, yzero, total, inst, count, pi, ni, po, no, V, P, flag,
-                                             check, s);
-    }
-    return launch_batch_pair_w<R, 1>(res, hv, ghosts, yzero, total, inst, count, pi, ni, po, no, V, P, flag, check, s);
-}
+extern template hipError_t launch_batch_step_w<float, 1, false>(const BatchForm&, int, const BatchInst<float>*, int,
+                                                                const BatchState<float>&, uint64_t, bool, hipStream_t);
+extern template hipError_t launch_batch_step_w<double, 1, false>(const BatchForm&, int, const BatchInst<double>*, int,
+                                                                 const BatchState<double>&, uint64_t, bool,
+                                                                 hipStream_t);
+template hipError_t launch_batch_step_w<float, 2, false>(const BatchForm&, int, const BatchInst<float>*, int,
+                                                         const BatchState<float>&, uint64_t, bool, hipStream_t);
+template hipError_t launch_batch_step_w<float, 2, true>(const BatchForm&, int, const BatchInst<float>*, int,
+                                                        const BatchState<float>&, uint64_t, bool, hipStream_t);
 
 template <typename R, bool RES, bool HASV, bool GHOSTS>
 static hipError_t launch_batch_t(int grid, const BatchInst<R>* inst, int count, int total, const void* pi,
@@ -427,14 +278,45 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     const int res = d->params[0].reservoir;
     std::vector<BatchInst<R>> table(d->count);
     int tile0 = 0;
-    int64_t s_tile0 = 0;
     std::vector<int> block_inst;
     bool ghosts = false, noisy = false;
-    // the streaming form needs every instance's state under 2 GiB (32-bit buffer
+    // the streaming forms need every instance's state under 2 GiB (32-bit buffer
     // offsets) and one y boundary rule for all instances
     bool use_stream = true, all_zero_y = true, all_periodic_y = true;
-    int64_t p_tile0[2] = {0, 0};  // work items of the two-step form with one and two columns per lane
-    int64_t w_tile0 = 0;  // work items of the wide streaming form (complex64 instances of even width)
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    // tallest bands of the walks: the candidates that give the shortest list
+    int s_cap = 64, p_cap = 56;
+    double s_best = 0.0, p_best = 0.0;
+    for (int cap = 64; cap >= 8; cap -= 8) {
+        int64_t waves = 0;
+        for (int k = 0; k < d->count; ++k) {
+            const phx_instance& I = d->instances[k];
+            const int cols = step_cols(sizeof(R) == 4 && I.nx % 2 == 0 ? 2 : 1), band = batch_step_band(I.ny, cap);
+            waves += (int64_t)((I.nx + cols - 1) / cols) * ((I.ny + band - 1) / band);
+        }
+        const double cost = list_cost(waves, cap + 4, 4 * cus);
+        if (s_best == 0.0 || cost < s_best) {
+            s_best = cost;
+            s_cap = cap;
+        }
+    }
+    for (int cap = 56; cap >= 20; cap -= 12) {
+        int64_t waves = 0;
+        for (int k = 0; k < d->count; ++k) {
+            int w = 1, strips = 1, band = 20;
+            batch_pair_plan(sizeof(R) == 4, d->instances[k].nx, d->instances[k].ny, cap, &w, &strips, &band);
+            waves += (int64_t)strips * ((d->instances[k].ny + band - 1) / band);
+        }
+        const double cost = list_cost(waves, cap + 7, 4 * cus);
+        if (p_best == 0.0 || cost < p_best) {
+            p_best = cost;
+            p_cap = cap;
+        }
+    }
+    int64_t s_tile0[2] = {0, 0}, p_tile0[2] = {0, 0};  // work items with one and two columns per lane
     for (int k = 0; k < d->count; ++k) {
         const phx_instance& I = d->instances[k];
         phx_config c = d->params[I.param_index];
@@ -453,22 +335,18 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         b.dt = (R)c.dt;
         b.dt6 = (R)(c.dt / 6.0);
         tile0 += b.tiles_x * ((I.ny + BW * BR - 9) / (BW * BR - 8));
-        // the one-column and the wide work lists give each instance a range in one of
-        // them and an empty range in the other
-        // complex64 instances of even width take the wide walk, the others the
-        // one-column walk (on a second stream when both occur)
-        const bool wide = sizeof(R) == 4 && I.nx % 2 == 0;
-        b.w_strips = wide ? wide_strips(I.nx) : 0;
-        b.w_band = batch_wide_band(I.ny);
-        b.s_tile0 = (int)std::min<int64_t>(s_tile0, INT32_MAX);
-        b.w_tile0 = (int)std::min<int64_t>(w_tile0, INT32_MAX);
-        if (wide)
-            w_tile0 += (int64_t)b.w_strips * ((I.ny + b.w_band - 1) / b.w_band);
-        else
-            s_tile0 += (int64_t)((b.tiles_x + SG - 1) / SG) * ((I.ny + SB - 1) / SB);
+        // complex64 instances of even width take two columns per lane, the others one (on a
+        // second stream when both occur)
+        const int sw = sizeof(R) == 4 && I.nx % 2 == 0 ? 2 : 1;
+        b.s_strips = (I.nx + step_cols(sw) - 1) / step_cols(sw);
+        b.s_band = batch_step_band(I.ny, s_cap);
         int w = 1;
-        batch_pair_plan(sizeof(R) == 4, I.nx, I.ny, &w, &b.p_strips, &b.p_band);
-        for (int l = 0; l < 2; ++l) b.p_tile0[l] = (int)std::min<int64_t>(p_tile0[l], INT32_MAX);
+        batch_pair_plan(sizeof(R) == 4, I.nx, I.ny, p_cap, &w, &b.p_strips, &b.p_band);
+        for (int l = 0; l < 2; ++l) {
+            b.s_tile0[l] = (int)std::min<int64_t>(s_tile0[l], INT32_MAX);
+            b.p_tile0[l] = (int)std::min<int64_t>(p_tile0[l], INT32_MAX);
+        }
+        s_tile0[sw - 1] += (int64_t)b.s_strips * ((I.ny + b.s_band - 1) / b.s_band);
         p_tile0[w - 1] += (int64_t)b.p_strips * ((I.ny + b.p_band - 1) / b.p_band);
         use_stream = use_stream && (double)I.nx * I.ny * 2.0 * sizeof(R) < 2147483648.0 - 256.0;
         all_zero_y = all_zero_y && c.bc_y == PHX_BC_ZERO;
@@ -479,37 +357,38 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         b.noise_b = (R)(scale * c.gamma_c);
         b.key0 = (uint32_t)I.seed;
         b.key1 = (uint32_t)(I.seed >> 32);
-        b.block0 = (int)block_inst.size();
-        const int64_t nb = (((int64_t)I.nx * I.ny + 1) / 2 + 255) / 256;
-        block_inst.insert(block_inst.end(), (size_t)nb, k);
         noisy = noisy || c.noise > 0.0;
     }
     const int total = tile0;
-    use_stream = use_stream && (all_zero_y || all_periodic_y) && s_tile0 < INT32_MAX && w_tile0 < INT32_MAX;
-    const int s_total = (int)std::min<int64_t>(s_tile0, INT32_MAX);
-    const int w_total = (int)std::min<int64_t>(w_tile0, INT32_MAX);
+    use_stream = use_stream && (all_zero_y || all_periodic_y) && s_tile0[0] < INT32_MAX && s_tile0[1] < INT32_MAX;
+    // noise pass over the instances whose step does not draw the increments itself
+    for (int k = 0; noisy && k < d->count; ++k) {
+        const phx_instance& I = d->instances[k];
+        table[k].block0 = (int)block_inst.size();
+        if (use_stream && sizeof(R) == 4 && I.nx % 2 == 0) continue;
+        const int64_t nb = (((int64_t)I.nx * I.ny + 1) / 2 + 255) / 256;
+        block_inst.insert(block_inst.end(), (size_t)nb, k);
+    }
     hipError_t e = hipMemcpyAsync(ws + L.table, table.data(), table.size() * sizeof(BatchInst<R>),
                                   hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && noisy)
+    if (e == hipSuccess && !block_inst.empty())
         e = hipMemcpyAsync(ws + L.block_inst, block_inst.data(), block_inst.size() * sizeof(int),
                            hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemsetAsync(ws + L.flag, 0, 256, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);  // the host table may go out of scope
     if (e != hipSuccess) return fail(PHX_EHIP, "batch table upload: %s", hipGetErrorString(e));
 
-    // persistent grid: as many workgroups as fit on the device at once, a multiple
-    // of 8 so that every workgroup stays on one XCD's share of the work list
-    int dev = 0, cus = 256, per_cu = 1;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+    // persistent grid of the region form: as many workgroups as fit on the device at once,
+    // a multiple of 8 so that every workgroup stays on one XCD's share of the work list
+    int grid = 0;
+    if (!use_stream) {
+        int per_cu = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_step_kernel<R, true, false, false, BW, BR>,
+                                                         BW * 64, 0) != hipSuccess || per_cu < 1)
+            per_cu = 1;
+        grid = std::min(cus * per_cu, (total + 7) / 8 * 8);
+        grid = (grid + 7) / 8 * 8;
     }
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_step_kernel<R, true, false, false, BW, BR>,
-                                                     BW * 64, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int grid = cus * per_cu;
-    grid = std::min(grid, (total + 7) / 8 * 8);
-    grid = (grid + 7) / 8 * 8;
 
     const size_t rs = sizeof(R);
     void* S[2] = {d->psi, ws + L.alt};
@@ -531,7 +410,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     // first goes to the device's second stream
     hipStream_t side = nullptr;
     ForkJoin fj;
-    if (use_stream && ((w_total > 0 && s_total > 0) || (pairs > 0 && p_tile0[0] > 0 && p_tile0[1] > 0))) {
+    if (use_stream && ((s_tile0[0] > 0 && s_tile0[1] > 0) || (pairs > 0 && p_tile0[0] > 0 && p_tile0[1] > 0))) {
         side = side_stream(dev);
         if (side && (hipEventCreateWithFlags(&fj.fork, hipEventDisableTiming) != hipSuccess ||
                      hipEventCreateWithFlags(&fj.join, hipEventDisableTiming) != hipSuccess))
@@ -543,7 +422,11 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         const bool check = k + steps == n;
         if (use_stream) {
             e = hipSuccess;
-            const int first = pair ? (int)p_tile0[0] : s_total, second = pair ? (int)p_tile0[1] : w_total;
+            const int first = (int)(pair ? p_tile0[0] : s_tile0[0]), second = (int)(pair ? p_tile0[1] : s_tile0[1]);
+            using C = typename cvec<R>::type;
+            const BatchForm form{res != 0, d->V != nullptr, ghosts, all_zero_y};
+            const BatchState<R> b{(const C*)S[cur], (const R*)SN[cur], (C*)S[cur ^ 1], (R*)SN[cur ^ 1],
+                                  (const R*)d->V, (const R*)d->P, flag};
             const bool fork = side && first > 0 && second > 0;
             hipStream_t s_first = stream;
             if (fork) {
@@ -552,21 +435,16 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
                 if (e == hipSuccess) e = hipStreamWaitEvent(side, fj.fork, 0);
                 s_first = side;
             }
+            const uint64_t step = (uint64_t)(d->step0 + k);
             if constexpr (sizeof(R) == 4) {
                 if (e == hipSuccess && second > 0)
-                    e = pair ? launch_batch_pair<float>(2, res != 0, d->V != nullptr, ghosts, all_zero_y, second,
-                                                        (const BatchInst<float>*)dtab, d->count, S[cur], SN[cur],
-                                                        S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, check, stream)
-                             : launch_batch_wide(res != 0, d->V != nullptr, ghosts, all_zero_y, second,
-                                                 (const BatchInst<float>*)dtab, d->count, S[cur], SN[cur], S[cur ^ 1],
-                                                 SN[cur ^ 1], d->V, d->P, flag, check, stream);
+                    e = pair    ? launch_batch_pair_w<R, 2>(form, second, dtab, d->count, b, check, stream)
+                        : noisy ? launch_batch_step_w<R, 2, true>(form, second, dtab, d->count, b, step, check, stream)
+                                : launch_batch_step_w<R, 2, false>(form, second, dtab, d->count, b, step, check, stream);
             }
             if (e == hipSuccess && first > 0)
-                e = pair ? launch_batch_pair<R>(1, res != 0, d->V != nullptr, ghosts, all_zero_y, first, dtab, d->count,
-                                                S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, check,
-                                                s_first)
-                         : launch_batch_stream<R>(res != 0, d->V != nullptr, ghosts, all_zero_y, first, dtab, d->count,
-                                                  S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, s_first);
+                e = pair ? launch_batch_pair_w<R, 1>(form, first, dtab, d->count, b, check, s_first)
+                         : launch_batch_step_w<R, 1, false>(form, first, dtab, d->count, b, step, check, s_first);
             if (e == hipSuccess && fork) {
                 e = hipEventRecord(fj.join, side);
                 if (e == hipSuccess) e = hipStreamWaitEvent(stream, fj.join, 0);
@@ -576,7 +454,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
                                 S[cur ^ 1], SN[cur ^ 1], d->V, d->P, flag, stream);
         if (e != hipSuccess) return fail(PHX_EHIP, "batch step launch: %s", hipGetErrorString(e));
         cur ^= 1;
-        if (noisy) {
+        if (!block_inst.empty()) {
             using C = typename cvec<R>::type;
             const unsigned blocks = (unsigned)block_inst.size();
             const int* bi = (const int*)(ws + L.block_inst);

@@ -9,13 +9,12 @@ template <typename R>
 struct BatchInst {
     int nx, ny, bcx, bcy;
     int tiles_x, tile0;  // regions across x; first work item of this instance (region form)
-    int s_tile0;         // first work item of this instance in the streaming form
-    int w_strips;        // wide streaming form (complex64): strips of 120 columns, else 0
-    int w_band;          // wide streaming form: rows per band
-    int w_tile0;         // first work item of this instance in the wide streaming form
-    int p_strips;        // two-step form: strips, rows per band and first work item of this
-    int p_band;          // instance in the list of its column count (p_tile0[columns - 1]; in
-    int p_tile0[2];      // the other list its range is empty)
+    int s_strips;        // one-step walk: strips, rows per band and first work item of this
+    int s_band;          // instance in the list of its column count (s_tile0[columns - 1]; in
+    int s_tile0[2];      // the other list its range is empty)
+    int p_strips;        // the same of the two-step walk
+    int p_band;
+    int p_tile0[2];
     int64_t offset;      // element offset in the packed arrays
     Coef<R> c;
     R half_dt, dt, dt6;
@@ -26,14 +25,28 @@ struct BatchInst {
     int block0;
 };
 
-// Two steps per launch over all instances with `columns` columns per lane (batch_pair.h).
+// The packed arrays of one launch, and the terms that all instances share.
 template <typename R>
-hipError_t launch_batch_pair(int columns, bool res, bool hv, bool ghosts, bool yzero, int total,
-                             const BatchInst<R>* inst, int count, const void* pi, const void* ni, void* po, void* no,
-                             const void* V, const void* P, unsigned int* flag, bool check, hipStream_t s);
+struct BatchState {
+    const typename cvec<R>::type* psi_in;
+    const R* n_in;
+    typename cvec<R>::type* psi_out;
+    R* n_out;
+    const R *V, *P;
+    unsigned int* flag;
+};
+struct BatchForm {
+    bool res, hasv, ghosts, yzero;  // yzero: every instance has a zero y boundary, else none
+};
+
+// One step per launch over all instances with W columns per lane (batch_walk.h).
+template <typename R, int W, bool NOISE>
+hipError_t launch_batch_step_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
+                               const BatchState<R>& b, uint64_t step, bool check, hipStream_t s);
+
+// Two steps per launch over all instances with W columns per lane (batch_pair.h).
 template <typename R, int W>
-hipError_t launch_batch_pair_w(bool res, bool hv, bool ghosts, bool yzero, int total, const BatchInst<R>* inst,
-                               int count, const void* pi, const void* ni, void* po, void* no, const void* V,
-                               const void* P, unsigned int* flag, bool check, hipStream_t s);
+hipError_t launch_batch_pair_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
+                               const BatchState<R>& b, bool check, hipStream_t s);
 
 }  // namespace phx

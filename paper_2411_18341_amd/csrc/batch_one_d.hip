@@ -1,0 +1,7 @@
+// One-step batched walk, one column per lane, double.
+#include "batch_walk.h"
+
+namespace phx {
+template hipError_t launch_batch_step_w<double, 1, false>(const BatchForm&, int, const BatchInst<double>*, int,
+                                                       const BatchState<double>&, uint64_t, bool, hipStream_t);
+}  // namespace phx

@@ -10,9 +10,7 @@ namespace phx {
 
 template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
-void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, const typename cvec<R>::type* psi_in,
-                              const R* n_in, typename cvec<R>::type* psi_out, R* n_out, const R* V, const R* P,
-                              unsigned int* flag)
+void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, const BatchState<R> b)
 {
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     int lo = 0, hi = count - 1;
@@ -32,51 +30,48 @@ void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, 
     a.half_dt = I.half_dt;
     a.dt = I.dt;
     a.dt6 = I.dt6;
-    a.psi_in = psi_in + I.offset;
-    a.n_in = RES ? n_in + I.offset : nullptr;
-    a.psi_out = psi_out + I.offset;
-    a.n_out = RES ? n_out + I.offset : nullptr;
-    a.V = HASV ? V + I.offset : nullptr;
-    a.P = RES ? P + I.offset : nullptr;
-    stream_band_pair<R, W, RES, HASV, GHOSTS, YZERO, CHECK>(a, strip, band, I.p_band, (band & 1) ? -1 : 1,
+    a.psi_in = b.psi_in + I.offset;
+    a.n_in = RES ? b.n_in + I.offset : nullptr;
+    a.psi_out = b.psi_out + I.offset;
+    a.n_out = RES ? b.n_out + I.offset : nullptr;
+    a.V = HASV ? b.V + I.offset : nullptr;
+    a.P = RES ? b.P + I.offset : nullptr;
+    stream_band_pair<R, W, RES, HASV, GHOSTS, YZERO, CHECK, false>(a, strip, band, I.p_band, (band & 1) ? -1 : 1,
                                                            [&](bool bad) __attribute__((always_inline)) {
-                                                               if (bad) flag[0] = 1u;  // benign race
+                                                               if (bad) b.flag[0] = 1u;  // benign race
                                                            });
 }
 
 template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO>
-static void launch_batch_pair_t(int total, const BatchInst<R>* inst, int count, const void* pi, const void* ni,
-                                void* po, void* no, const void* V, const void* P, unsigned int* flag, bool check,
+static void launch_batch_pair_t(int total, const BatchInst<R>* inst, int count, const BatchState<R>& b, bool check,
                                 hipStream_t s)
 {
-    using C = typename cvec<R>::type;
-    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS);
+    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS, false);
     if (check)
-        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, true><<<total, 64, 0, s>>>(
-            inst, count, (const C*)pi, (const R*)ni, (C*)po, (R*)no, (const R*)V, (const R*)P, flag);
+        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, true><<<total, 64, 0, s>>>(inst, count, b);
     else
-        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, false><<<total, 64, 0, s>>>(
-            inst, count, (const C*)pi, (const R*)ni, (C*)po, (R*)no, (const R*)V, (const R*)P, flag);
+        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, false><<<total, 64, 0, s>>>(inst, count, b);
 }
 
 template <typename R, int W>
-hipError_t launch_batch_pair_w(bool res, bool hv, bool ghosts, bool yzero, int total, const BatchInst<R>* inst,
-                               int count, const void* pi, const void* ni, void* po, void* no, const void* V,
-                               const void* P, unsigned int* flag, bool check, hipStream_t s)
+hipError_t launch_batch_pair_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
+                               const BatchState<R>& b, bool check, hipStream_t s)
 {
 #define PHX_BP(RS, HV) \
-    if (res == RS && hv == HV) { \
-        if (yzero) \
-            launch_batch_pair_t<R, W, RS, HV, true, true>(total, inst, count, pi, ni, po, no, V, P, flag, check, s); \
-        else if (ghosts) \
-            launch_batch_pair_t<R, W, RS, HV, true, false>(total, inst, count, pi, ni, po, no, V, P, flag, check, s); \
+    if (f.res == RS && f.hasv == HV) { \
+        if (f.yzero) \
+            launch_batch_pair_t<R, W, RS, HV, true, true>(total, inst, count, b, check, s); \
+        else if (f.ghosts) \
+            launch_batch_pair_t<R, W, RS, HV, true, false>(total, inst, count, b, check, s); \
         else \
-            launch_batch_pair_t<R, W, RS, HV, false, false>(total, inst, count, pi, ni, po, no, V, P, flag, check, s); \
-        return hipGetLastError(); \
+            launch_batch_pair_t<R, W, RS, HV, false, false>(total, inst, count, b, check, s); \
     }
-    PHX_BP(true, false) PHX_BP(true, true) PHX_BP(false, false) PHX_BP(false, true)
+    PHX_BP(true, true)
+    PHX_BP(true, false)
+    PHX_BP(false, true)
+    PHX_BP(false, false)
 #undef PHX_BP
-    return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 }  // namespace phx

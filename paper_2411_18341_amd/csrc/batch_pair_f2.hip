@@ -2,7 +2,6 @@
 #include "batch_pair.h"
 
 namespace phx {
-template hipError_t launch_batch_pair_w<float, 2>(bool, bool, bool, bool, int, const BatchInst<float>*, int, const void*,
-                                                 const void*, void*, void*, const void*, const void*, unsigned int*,
-                                                 bool, hipStream_t);
+template hipError_t launch_batch_pair_w<float, 2>(const BatchForm&, int, const BatchInst<float>*, int,
+                                                  const BatchState<float>&, bool, hipStream_t);
 }  // namespace phx

@@ -11,7 +11,7 @@
 // written for n.  Its time is the floor that this access pattern sets for the step
 // kernel's 28 bytes per point.
 #include "runtime.h"
-#include "stream_wide.h"
+#include "stream_step.h"
 
 namespace phx {
 
@@ -42,7 +42,7 @@ void walk_pattern_kernel(const float2* psi_in, const float* n_in, const float* P
     const int band = t / strips, strip = t - band * strips;
     const int dir = (band & 1) ? -1 : 1;
     const int b0 = band * B, npos = B + 8;
-    const int gi = strip * kWideCols - 4 + 2 * lane;
+    const int gi = strip * step_cols(2) - 4 + 2 * lane;
     const int ci = ((gi % nx) + nx) % nx;
     const size_t cells = (size_t)nx * ny;
     const __amdgpu_buffer_rsrc_t rpi = buffer_of(psi_in, cells * 8), rni = buffer_of(n_in, cells * 4);
@@ -115,20 +115,16 @@ extern "C" phx_status phx_walk_pattern(void* psi_out, void* n_out, const void* p
                 return fail(PHX_EINVAL, "outputs must not overlap the inputs");
     if (psi_out < (char*)n_out + cells * 4 && n_out < (char*)psi_out + cells * 8)
         return fail(PHX_EINVAL, "psi_out and n_out overlap");
+    const int strips = (nx + step_cols(2) - 1) / step_cols(2);
     int B = band_rows;
     if (B == 0) {  // the device-filling height of the step kernel's 8-row ring
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             cus = 256;
-        phx_config c{};
-        c.nx = nx;
-        c.ny = ny;
-        c.reservoir = 1;
-        c.bc_x = c.bc_y = PHX_BC_PERIODIC;
-        B = wide_band_rows(c, StepShapeId{2, 0}, false, cus);
+        const int bands = std::max(1, cus * 12 / strips);  // 3 waves per SIMD
+        B = std::max(16, (ny + bands - 1) / bands);
     }
-    const int strips = wide_strips(nx);
     const int64_t tiles = (int64_t)strips * ((ny + B - 1) / B);
     if (tiles > 0x7fffffff) return fail(PHX_EINVAL, "too many tiles");
     walk_pattern_kernel<<<(unsigned)tiles, 64, 0, (hipStream_t)stream>>>(

@@ -2,7 +2,7 @@
 // solution and the embedded error of one attempted step in one pass over the state.
 //
 // One wave per strip of columns walks a band of rows, as the streaming RK4 step does
-// (stream_body.h): at row j stage s runs at row j - s, so the rows that a stage needs
+// (stream_step.h): at row j stage s runs at row j - s, so the rows that a stage needs
 // (r - 1, r, r + 1 of its argument) were finished by the stage before it at this or an
 // earlier row.  K_1..K_6 of the rows in flight stay in registers until the error of
 // their row is formed, so neither K_s nor a stage argument goes through memory: an

@@ -7,8 +7,9 @@
 // chunks per workgroup, a fixed lane and wave order inside it, then one workgroup
 // over the partials in index order.  The scale lives in device memory, so the step
 // sequence can be captured and replayed as a graph.  The streaming whole-step kernel
-// instead writes one partial per wave and applies the scale to its next input; the
-// finish kernel and the final scale pass are shared.  Passes: the partial sums read
+// instead writes one partial per wave and applies the scale to its next input (formed by
+// the finish kernel, or by the waves themselves from few partials); the finish kernel and
+// the final scale pass are shared.  Passes: the partial sums read
 // psi (8 B/pt complex64), the scale reads and writes it (16 B/pt); both are bound by
 // HBM.
 #include <hip/hip_runtime.h>
@@ -61,8 +62,9 @@ __global__ __launch_bounds__(256) void norm_partials_kernel(const typename phx::
 
 // mode 0: slots[0] = N (the target of the call) and slots[1] = 1; mode 1:
 // slots[1] = sqrt(slots[0] / N).
-__global__ __launch_bounds__(256) void norm_finish_kernel(const double* __restrict__ partials, int blocks,
-                                                          double cell_area, int mode, double* __restrict__ slots)
+__global__ __launch_bounds__(256) void norm_finish_kernel(const double* partials, int blocks,
+                                                          double cell_area, int mode, double* __restrict__ slots,
+                                                          double* fill, int fill_stride, int fill_count)
 {
     // eight independent accumulators per thread keep eight loads in flight (the
     // partials were just written by other XCDs: each load is a far miss); the order of
@@ -78,11 +80,15 @@ __global__ __launch_bounds__(256) void norm_finish_kernel(const double* __restri
         if (b + k * 256 < blocks) a[k] += partials[b + k * 256];
     double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
     s = block_sum_256(s);
+    // mode 0: partials that sum to the target in both arrays, for waves that sum them
+    for (int i = threadIdx.x; i < fill_count; i += 256)
+        if (i > 0) fill[i] = fill[fill_stride + i] = 0.0;
     if (threadIdx.x == 0) {
         const double N = cell_area * s;
         if (mode == 0) {
             slots[0] = N;
             slots[1] = 1.0;
+            if (fill_count) fill[0] = fill[fill_stride] = s;
         } else
             slots[1] = N > 0.0 ? sqrt(slots[0] / N) : 1.0;
     }
@@ -124,15 +130,16 @@ hipError_t launch_imag_norm(const phx_handle* h, const void* psi, int mode, hipS
     double* slots = (double*)(h->ws + h->L.imag);
     hipLaunchKernelGGL(norm_partials_kernel<R>, dim3(blocks), dim3(256), 0, s,
                        (const typename cvec<R>::type*)psi, M, chunk, partials);
+    const int fill = mode == 0 ? imag_self_sum(h) : 0;
     hipLaunchKernelGGL(norm_finish_kernel, dim3(1), dim3(256), 0, s, (const double*)partials, blocks, c.dx * c.dy,
-                       mode, slots);
+                       mode, slots, partials, (int)h->L.imag_slots, fill);
     return hipGetLastError();
 }
 
-hipError_t launch_imag_finish(const phx_handle* h, int count, hipStream_t s)
+hipError_t launch_imag_finish(const phx_handle* h, const double* partials, int count, hipStream_t s)
 {
-    hipLaunchKernelGGL(norm_finish_kernel, dim3(1), dim3(256), 0, s, (const double*)(h->ws + h->L.imag_partials),
-                       count, h->cfg.dx * h->cfg.dy, 1, (double*)(h->ws + h->L.imag));
+    hipLaunchKernelGGL(norm_finish_kernel, dim3(1), dim3(256), 0, s, partials, count, h->cfg.dx * h->cfg.dy, 1,
+                       (double*)(h->ws + h->L.imag), (double*)nullptr, 0, 0);
     return hipGetLastError();
 }
 

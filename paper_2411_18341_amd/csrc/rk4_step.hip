@@ -18,7 +18,6 @@
 // buffer (neighbouring regions still read the input's halo).
 #include "runtime.h"
 #include "step_body.h"
-#include "stream_body.h"
 
 namespace phx {
 
@@ -30,64 +29,15 @@ __global__ __launch_bounds__(WAVES * 64) void rk4_step_kernel(const StepArgs<R> 
     if (bad) a.flag[0] = 1u;  // benign race: every writer stores 1
 }
 
-// Streaming form: a workgroup is 4 adjacent strips of one band of B rows (their
-// x-halo columns are read through one L1); a.tiles_x counts strips, a.tiles
-// workgroups.  Waves past the last strip leave at once (the kernel has no barrier).
-// IMAG (imaginary time): wave w of tile t writes the FP64 norm partial of its cells
-// to a.imag_partials[4 t + w] (0 for a wave past the last strip), reduced over the
-// lanes in a fixed butterfly order.
-template <typename R, bool RES, bool HASV, bool GHOSTS, bool YZERO, int B, bool IMAG>
-__global__ __launch_bounds__(256) void rk4_stream_kernel(const StepArgs<R> a)
-{
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    const int groups_x = (a.tiles_x + 3) / 4;
-    const int band = t / groups_x, strip = (t - band * groups_x) * 4 + wave;
-    if (strip >= a.tiles_x) {
-        if (IMAG && (threadIdx.x & 63) == 0) a.imag_partials[4 * t + wave] = 0.0;
-        return;
-    }
-    double nrm = 0.0;
-    if (stream_band<R, RES, HASV, GHOSTS, YZERO, B, IMAG>(a, strip, band, (band & 1) ? -1 : 1, &nrm))
-        a.flag[0] = 1u;  // benign race
-    if constexpr (IMAG) {
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) nrm += __shfl_xor(nrm, m, 64);
-        if ((threadIdx.x & 63) == 0) a.imag_partials[4 * t + wave] = nrm;
-    }
-}
-
 // GHOSTS: some boundary is zero, so region cells outside the grid must be held at 0
 // after every stage; with periodic boundaries in both directions there are none.
-// WAVES == 1 selects the streaming kernel with bands of ROWS rows.
 template <typename R, bool RES, bool HASV, int WAVES, int ROWS>
 static hipError_t launch_step_t(const StepArgs<R>& a, hipStream_t s)
 {
-    const bool ghosts = a.bcx == PHX_BC_ZERO || a.bcy == PHX_BC_ZERO;
-    if constexpr (WAVES == 1) {
-        if constexpr (!RES) {
-            if (a.imag_partials) {  // imaginary time
-                if (a.bcy == PHX_BC_ZERO)
-                    rk4_stream_kernel<R, RES, HASV, true, true, ROWS, true><<<a.tiles, 256, 0, s>>>(a);
-                else if (ghosts)
-                    rk4_stream_kernel<R, RES, HASV, true, false, ROWS, true><<<a.tiles, 256, 0, s>>>(a);
-                else
-                    rk4_stream_kernel<R, RES, HASV, false, false, ROWS, true><<<a.tiles, 256, 0, s>>>(a);
-                return hipGetLastError();
-            }
-        }
-        if (a.bcy == PHX_BC_ZERO)
-            rk4_stream_kernel<R, RES, HASV, true, true, ROWS, false><<<a.tiles, 256, 0, s>>>(a);
-        else if (ghosts)
-            rk4_stream_kernel<R, RES, HASV, true, false, ROWS, false><<<a.tiles, 256, 0, s>>>(a);
-        else
-            rk4_stream_kernel<R, RES, HASV, false, false, ROWS, false><<<a.tiles, 256, 0, s>>>(a);
-    } else {
-        if (ghosts)
-            rk4_step_kernel<R, RES, HASV, true, WAVES, ROWS><<<a.tiles, WAVES * 64, 0, s>>>(a);
-        else
-            rk4_step_kernel<R, RES, HASV, false, WAVES, ROWS><<<a.tiles, WAVES * 64, 0, s>>>(a);
-    }
+    if (a.bcx == PHX_BC_ZERO || a.bcy == PHX_BC_ZERO)
+        rk4_step_kernel<R, RES, HASV, true, WAVES, ROWS><<<a.tiles, WAVES * 64, 0, s>>>(a);
+    else
+        rk4_step_kernel<R, RES, HASV, false, WAVES, ROWS><<<a.tiles, WAVES * 64, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -95,10 +45,9 @@ static hipError_t launch_step_t(const StepArgs<R>& a, hipStream_t s)
 // A region of WAVES*ROWS rows yields WAVES*ROWS - 8 output rows; taller regions
 // recompute less halo, shorter ones need fewer registers per lane (more waves
 // per SIMD).  The first entry is the default; phx_autotune measures them all.
-// Shapes {1, B} are the streaming kernel with bands of B rows (B + 8 a multiple of 24).
-// Shapes {2, B} and {3, B} are the wide streaming kernel (two columns per lane) with
-// bands of B rows, B = 0 choosing the height that fills the device in one wave of
-// workgroups (complex64 only).
+// Shapes {1, B} are the streaming walk with one column per lane and bands of B rows (64: the
+// height is chosen per grid), {2, B} and {3, B} the walk with two columns per lane (complex64,
+// even widths), B = 0 choosing the height that fills the device in one wave of workgroups.
 static const StepShapeId kFloatShapes[] = {{8, 4}, {16, 4}, {8, 8}, {12, 4}, {12, 6}, {8, 6}, {4, 8}, {16, 6},
                                            {1, 40}, {1, 64}, {1, 88}, {1, 112},
                                            {2, 0}, {3, 0}, {2, 40}, {2, 64}, {3, 64}, {3, 96}};
@@ -122,17 +71,15 @@ static hipError_t launch_step_shape(const StepShapeId& sh, const StepArgs<R>& a,
     if constexpr (sizeof(R) == 4) {
         PHX_SHAPE(8, 4); PHX_SHAPE(16, 4); PHX_SHAPE(8, 8); PHX_SHAPE(12, 4);
         PHX_SHAPE(12, 6); PHX_SHAPE(8, 6); PHX_SHAPE(4, 8); PHX_SHAPE(16, 6);
-        PHX_SHAPE(1, 40); PHX_SHAPE(1, 64); PHX_SHAPE(1, 88); PHX_SHAPE(1, 112);
     } else {
         PHX_SHAPE(8, 4); PHX_SHAPE(16, 2); PHX_SHAPE(8, 2); PHX_SHAPE(12, 4); PHX_SHAPE(4, 4);
-        PHX_SHAPE(1, 40); PHX_SHAPE(1, 64);
     }
 #undef PHX_SHAPE
     return hipErrorInvalidValue;
 }
 
-template <typename R>
-hipError_t launch_stream_drive(bool reservoir, bool has_v, int rows, const StepArgs<R>& a, hipStream_t s);
+bool drive_stream_rows(int rows) { return rows == 40 || rows == 64; }
+
 template <typename R>
 hipError_t launch_stream_spinor(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
 
@@ -140,17 +87,14 @@ template <typename R>
 hipError_t launch_rk4_step(bool reservoir, bool has_v, const StepShapeId& sh, const StepArgs<R>& a,
                            hipStream_t s)
 {
-    if (a.E && a.comps == 1)
-        return sh.waves == 1 ? launch_stream_drive<R>(reservoir, has_v, sh.rows, a, s) : hipErrorInvalidValue;
-    if (wide_shape(sh.waves)) {
-        if constexpr (sizeof(R) == 4) {
-            if (a.comps != 1) return hipErrorInvalidValue;
-            return launch_stream_wide(reservoir, has_v, sh.waves == 2 ? 8 : 12, a, s);
-        }
-        return hipErrorInvalidValue;
-    }
     if (a.comps == 2)
         return sh.waves == 1 ? launch_stream_spinor<R>(reservoir, has_v, a, s) : hipErrorInvalidValue;
+    if (a.E) return sh.waves == 1 ? launch_step_walk_drive<R>(reservoir, has_v, a, s) : hipErrorInvalidValue;
+    if (wide_shape(sh.waves)) {
+        if constexpr (sizeof(R) == 4) return launch_step_walk<R, 2>(reservoir, has_v, a, s);
+        return hipErrorInvalidValue;
+    }
+    if (sh.waves == 1) return launch_step_walk<R, 1>(reservoir, has_v, a, s);
     if (reservoir) return has_v ? launch_step_shape<R, true, true>(sh, a, s) : launch_step_shape<R, true, false>(sh, a, s);
     return has_v ? launch_step_shape<R, false, true>(sh, a, s) : launch_step_shape<R, false, false>(sh, a, s);
 }
@@ -158,6 +102,7 @@ hipError_t launch_rk4_step(bool reservoir, bool has_v, const StepShapeId& sh, co
 template <typename R>
 static hipError_t launch_pair(int columns, bool res, bool hv, const StepArgs<R>& a, hipStream_t s)
 {
+    if (a.E) return launch_stream_pair_drive<R>(res, hv, a, s);
     if constexpr (sizeof(R) == 4) {
         if (columns == 2) return launch_stream_pair<R, 2>(res, hv, a, s);
     }
@@ -168,7 +113,7 @@ static hipError_t launch_pair(int columns, bool res, bool hv, const StepArgs<R>&
 // shape sh.
 template <typename R>
 static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const void* src, const void* src_n,
-                             void* dst, void* dst_n, int pair = 0)
+                             void* dst, void* dst_n, int parity, int pair = 0)
 {
     using C = typename cvec<R>::type;
     const phx_config& c = h->cfg;
@@ -182,18 +127,17 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
         a.tiles_x = pair_strips(c.nx, pair);
         a.band_rows = pair_band_rows(c, pair, h->f.V != nullptr, h->cus);
         a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
-    } else if (wide_shape(sh.waves)) {  // wide streaming: strips of 120 columns, one wave per band of a strip
-        a.tiles_x = wide_strips(c.nx);
-        a.band_rows = wide_band_rows(c, sh, h->f.V != nullptr, h->cus);
-        a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
     } else if (c.components == 2) {  // the spinor walk: one wave per band of a strip
         const SpinorPlan p = spinor_plan(c, sh.rows == 64 ? 0 : sh.rows, h->cus);
         a.columns = p.columns;
         a.tiles_x = p.strips;
         a.band_rows = p.band_rows;
         a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
-    } else if (sh.waves == 1) {  // streaming: strips of 56 columns, workgroups of 4 strips x one band
-        a.tiles = ((a.tiles_x + 3) / 4) * ((c.ny + sh.rows - 1) / sh.rows);
+    } else if (sh.waves <= 3) {  // streaming: one wave per band of a strip
+        const StepPlan p = step_plan(c, sh, h->cus);
+        a.tiles_x = p.strips;
+        a.band_rows = p.band_rows;
+        a.tiles = a.tiles_x * ((c.ny + a.band_rows - 1) / a.band_rows);
     } else {
         const int oh = sh.waves * sh.rows - 8;
         a.tiles = a.tiles_x * ((c.ny + oh - 1) / oh);
@@ -210,9 +154,12 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
     a.psi_out = (C*)dst;
     a.n_out = (R*)dst_n;
     a.comps = c.components;
-    if (c.imag_time) {
+    if (c.imag_time) {  // buffer b of the partials belongs to state buffer b
         a.imag_slots = (const double*)(h->ws + h->L.imag);
-        a.imag_partials = (double*)(h->ws + h->L.imag_partials);
+        a.imag_prev = (const double*)(h->ws + h->L.imag_partials) + (parity ? h->L.imag_slots : 0);
+        a.imag_partials = (double*)(h->ws + h->L.imag_partials) + (parity ? 0 : h->L.imag_slots);
+        a.imag_count = a.tiles <= kImagSelfSum ? a.tiles : 0;
+        a.cell_area = c.dx * c.dy;
     }
     if (c.drive) {
         a.E = (const C*)h->f.E;
@@ -238,11 +185,11 @@ hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* step
     char* Bn = res ? h->ws + h->L.alt2_n : nullptr;
     StepArgs<R> a;
     if (k == 0)
-        a = step_args<R>(h, sh, h->f.psi, h->f.n, A, An, pair);
+        a = step_args<R>(h, sh, h->f.psi, h->f.n, A, An, 0, pair);
     else if (k & 1)
-        a = step_args<R>(h, sh, A, An, B, Bn, pair);
+        a = step_args<R>(h, sh, A, An, B, Bn, 1, pair);
     else
-        a = step_args<R>(h, sh, B, Bn, A, An, pair);
+        a = step_args<R>(h, sh, B, Bn, A, An, 0, pair);
     if (pair) return launch_pair<R>(pair, res, h->f.V != nullptr, a, h->stream);
     return launch_rk4_step<R>(res, h->f.V != nullptr, sh, a, h->stream);
 }
@@ -273,14 +220,14 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
     for (int64_t k = 0, steps = 1; k < n; k += steps) {
         const bool pair = pairs-- > 0;
         steps = pair ? 2 : 1;
-        StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], pair ? columns : 0);
+        StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], cur, pair ? columns : 0);
         a.check = k + steps == n;  // the wide forms test the last step of the run (values stay non-finite)
         if (fused_noise) {
             a.noise_step = (const uint64_t*)(h->ws + h->L.noise);
             a.noise_offset = k;
             noise_coefs<R>(c, a.noise_a, a.noise_b, a.noise_k0, a.noise_k1);
         }
-        if (c.drive && launch_drive_phasors<R>(h, k, s) != hipSuccess)
+        if (c.drive && launch_drive_phasors<R>(h, k, (int)steps, s) != hipSuccess)
             return fail(PHX_EHIP, "drive phasor launch failed");
         hipEvent_t t0 = nullptr;
         hipError_t e = timing_begin(h, &t0);
@@ -288,11 +235,9 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
         if (e == hipSuccess) e = timing_end(h, t0, pair ? K_RK4_PAIR : K_RK4_STEP);
         if (e != hipSuccess) return fail(PHX_EHIP, "RK4 step kernel launch: %s", hipGetErrorString(e));
         cur ^= 1;
-        if (c.imag_time) {  // the scale that restores the norm, applied by the next step
+        if (c.imag_time && a.imag_count == 0) {  // the scale that restores the norm, applied by the next step
             e = timing_begin(h, &t0);
-            // one norm partial per wave: 4 per workgroup of the one-column walk, else 1
-            const bool single = wide_shape(sh.waves) || c.components == 2;
-            if (e == hipSuccess) e = launch_imag_finish(h, single ? a.tiles : 4 * a.tiles, s);
+            if (e == hipSuccess) e = launch_imag_finish(h, a.imag_partials, a.tiles, s);
             if (e == hipSuccess) e = timing_end(h, t0, K_IMAG_NORM);
             if (e != hipSuccess) return fail(PHX_EHIP, "imaginary-time norm launch: %s", hipGetErrorString(e));
         }
@@ -311,6 +256,14 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
 
 template phx_status rk4_fused_launches<float>(phx_handle*, int64_t, hipStream_t);
 template phx_status rk4_fused_launches<double>(phx_handle*, int64_t, hipStream_t);
+
+// Partials that the waves of the next step sum themselves (0: a pass forms the scale).
+int imag_self_sum(const phx_handle* h)
+{
+    if (!h->cfg.imag_time || h->L.family != PHX_KERNEL_STEP) return 0;
+    return h->cfg.precision == PHX_C64 ? step_args<float>(h, h->step_shape, nullptr, nullptr, nullptr, nullptr, 0).imag_count
+                                       : step_args<double>(h, h->step_shape, nullptr, nullptr, nullptr, nullptr, 0).imag_count;
+}
 
 // n whole steps ending in the caller's arrays.  An odd count first copies the state
 // into the workspace and takes one step back (not where two-step launches make the

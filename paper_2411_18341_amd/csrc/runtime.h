@@ -35,9 +35,10 @@ struct Layout {
     size_t alt2, alt2_n;  // third state buffer (whole-step RK4: the tuner's trial launches)
     size_t noise;       // uint64 index of the next step, read by the noise and the drive
                         // (allocated when either is on)
-    size_t drive_ph;    // RK4 with drive: the four stage phasors of the current step
+    size_t drive_ph;    // RK4 with drive: the stage phasors of one launch (up to two steps)
     size_t imag;        // imaginary time: [0] target norm of the call, [1] restoring scale
-    size_t imag_partials;  // imaginary time: per-workgroup norm partials
+    size_t imag_partials;  // imaginary time: two arrays of imag_slots norm partials
+    size_t imag_slots;
     int family;         // PHX_KERNEL_STAGE or PHX_KERNEL_STEP for RK4
     size_t err;         // Dormand-Prince error partials
     int obs_blocks;
@@ -140,26 +141,31 @@ bool step_shape_fits(const phx_config& c, int waves);
 // the spinor on bands of 40 and 64 rows).
 bool step_shape_allowed(const phx_config& c, const StepShapeId& sh);
 bool drive_stream_rows(int rows);
-// Wide streaming form (shapes {2, B}: 8-row input ring, {3, B}: 12-row ring; B = 0
-// chooses the band height that fills the device): strips of 120 output columns and
-// the band height in rows for this grid on a device with `cus` compute units.
+// Streaming forms (stream_step.h): shapes {1, B} with one column per lane, {2, B} and {3, B}
+// with two; strips and band height for this grid on a device with `cus` compute units.
 template <typename R> struct StepArgs;
 bool wide_shape(int waves);
-int wide_strips(int nx);
-int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int cus);
-int wide_waves_per_simd(int ring, bool reservoir, bool has_v, bool ghosts, bool noise);
-hipError_t launch_stream_wide(bool reservoir, bool has_v, int ring, const StepArgs<float>& a, hipStream_t s);
+struct StepPlan {
+    int strips, band_rows;
+};
+StepPlan step_plan(const phx_config& c, const StepShapeId& sh, int cus);
+template <typename R, int W>
+hipError_t launch_step_walk(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
+template <typename R>
+hipError_t launch_step_walk_drive(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
+
 // Band height of a walk that is bound by its VALU issue: of the heights with which every
 // wave (one per band of a strip) is resident at once, the one whose busiest SIMD ends first.
 // A wave walks rows + halo positions, `skipped` of them without work; heights are
-// lo + k step.  n waves on a SIMD issue at a share of its rate that was measured on the
-// two-step walk: one wave 0.82 (63.6 us per step at 4096^2 with bands of 152 rows, against 59.4 with
-// two waves and bands of 80), two 0.97.
+// lo + k step.  One and two waves on a SIMD issue at the shares `one` and `two` of its rate,
+// measured on the two-step walk: one wave 0.82 (63.6 us per step at 4096^2 with bands of 152
+// rows, against 59.4 with two waves and bands of 80), two 0.97.
 struct BandFill {
     int rows;
     double cost;  // positions times waves on the busiest SIMD, over the issue rate
 };
-inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int step, int cus, int waves_per_simd)
+inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int step, int cus, int waves_per_simd,
+                          double one = 0.82, double two = 0.97)
 {
     const int simds = 4 * (cus > 0 ? cus : 256);
     BandFill best{0, 0.0};
@@ -170,7 +176,7 @@ inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int
         const int rows = need <= lo ? lo : lo + (need - lo + step - 1) / step * step;
         const int64_t waves = (int64_t)strips * ((ny + rows - 1) / rows);
         const int busy = (int)((waves + simds - 1) / simds);
-        const double rate = busy == 1 ? 0.82 : (busy == 2 ? 0.97 : 1.0);
+        const double rate = busy == 1 ? one : (busy == 2 ? two : 1.0);
         const double cost = busy * (double)(rows + halo - skipped) / rate;
         if (best.rows == 0 || cost < best.cost) best = BandFill{rows, cost};
     }
@@ -191,6 +197,8 @@ SpinorPlan spinor_plan(const phx_config& c, int rows, int cus);
 int pair_band_rows(const phx_config& c, int w, bool has_v, int cus);
 template <typename R, int W>
 hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
+template <typename R>
+hipError_t launch_stream_pair_drive(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s);
 int rk4_family(const phx_config& c);
 phx_status step_rk45(phx_handle* h, int64_t n, phx_info* out);
 phx_status set_info_rk45(phx_handle* h, const phx_info* in);
@@ -214,15 +222,20 @@ inline void noise_coefs(const phx_config& c, R& a, R& b, uint32_t& k0, uint32_t&
 // component, complex64, periodic in x and y); elsewhere a separate pass follows the step.
 bool noise_in_step(const phx_config& c, const StepShapeId& sh);
 hipError_t set_noise_step(const phx_handle* h, int64_t value, hipStream_t s);
-// Drive phasors exp(-i omega t_s) of the four RK4 stage times of the step with index
-// base + offset, written to the workspace (one thread; graph-replay safe).
-template <typename R> hipError_t launch_drive_phasors(const phx_handle* h, int64_t offset, hipStream_t s);
+// Drive phasors exp(-i omega t_s) of the four RK4 stage times of the `steps` (1 or 2) steps
+// from index base + offset on, written to the workspace (one thread; graph-replay safe).
+template <typename R> hipError_t launch_drive_phasors(const phx_handle* h, int64_t offset, int steps, hipStream_t s);
 bool uses_step_index(const phx_config& c);
 // Imaginary time: deterministic total norm of psi into the target (mode 0) or the
 // restoring scale (mode 1), and the pointwise scale pass.
 int imag_norm_blocks(int64_t M);
 template <typename R> hipError_t launch_imag_norm(const phx_handle* h, const void* psi, int mode, hipStream_t s);
 template <typename R> hipError_t launch_imag_scale(const phx_handle* h, void* psi, hipStream_t s);
-// Imaginary time, streaming form: the restoring scale from `count` per-wave partials.
-hipError_t launch_imag_finish(const phx_handle* h, int count, hipStream_t s);
+// Imaginary time, streaming forms: the restoring scale from `count` per-wave partials.  Up to
+// kImagSelfSum partials are summed by every wave of the next step itself, a few loads per
+// lane instead of a launch (256^2, 160 waves: 6.5 us per step; the launch alone took 4.5; 1024^2, about
+// 2400 waves: 13.7 summed by the waves, 12.3 with the launch).
+constexpr int kImagSelfSum = 512;
+int imag_self_sum(const phx_handle* h);
+hipError_t launch_imag_finish(const phx_handle* h, const double* partials, int count, hipStream_t s);
 }  // namespace phx

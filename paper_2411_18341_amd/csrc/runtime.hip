@@ -12,6 +12,7 @@
 #include "phx_kernels.h"
 #include "runtime.h"
 #include "stream_pair.h"
+#include "stream_step.h"
 
 namespace phx {
 
@@ -135,21 +136,16 @@ Layout make_layout(const phx_config& c)
     L.obs_blocks = L.tiles.tiles < 1024 ? L.tiles.tiles : 1024;
     L.partials = take((size_t)L.obs_blocks * OBS_SLOTS * sizeof(double));
     if (uses_step_index(c)) L.noise = take(sizeof(uint64_t));
-    if (c.drive && c.integrator == PHX_RK4) L.drive_ph = take(4 * 2 * rs);
+    if (c.drive && c.integrator == PHX_RK4) L.drive_ph = take(2 * 4 * 2 * rs);
     if (c.imag_time) {
-        // partials: one per workgroup of the stage-family reduction, or one per wave of
-        // the streaming kernel (bands of at least 40 rows)
         L.imag = take(2 * sizeof(double));
-        const int64_t stream_waves = 4 * (int64_t)((c.nx + 56 * 4 - 1) / (56 * 4)) * ((c.ny + 39) / 40);
-        // the wide walk: one wave per band of one strip, bands of at least 8 rows
-        const int64_t wide_waves = (int64_t)wide_strips(c.nx) * ((c.ny + 7) / 8);
+        // partials: one per workgroup of the norm reduction, or two arrays of one per wave of
+        // the streaming kernels (one component per band of at least 8 rows of one 56-column
+        // strip): a step reads one and writes the other
+        const int64_t waves = (int64_t)((c.nx + 55) / 56) * ((c.ny + 7) / 8);
         const int64_t blocks = imag_norm_blocks(c.nx * (int64_t)c.ny * c.components);
-        int64_t slots = stream_waves > blocks ? stream_waves : blocks;
-        if (wide_waves > slots) slots = wide_waves;
-        // the spinor walk: one wave per band of one 56-column strip, bands of at least 8 rows
-        const int64_t spinor_waves = c.components == 2 ? (int64_t)((c.nx + 55) / 56) * ((c.ny + 7) / 8) : 0;
-        if (spinor_waves > slots) slots = spinor_waves;
-        L.imag_partials = take((size_t)slots * sizeof(double));
+        L.imag_slots = (size_t)waves;
+        L.imag_partials = take((size_t)std::max<int64_t>(2 * waves, blocks) * sizeof(double));
     }
     if (c.integrator == PHX_RK4) {
         L.family = rk4_family(c);
@@ -196,26 +192,23 @@ bool wide_shape(int waves) { return waves == 2 || waves == 3; }
 
 bool noise_in_step(const phx_config& c, const StepShapeId& sh)
 {
-    return wide_shape(sh.waves) && c.precision == PHX_C64 && c.components == 1 && c.bc_x == PHX_BC_PERIODIC &&
-           c.bc_y == PHX_BC_PERIODIC && !c.drive && !c.imag_time && c.nx % 2 == 0;
+    return wide_shape(sh.waves) && c.precision == PHX_C64 && c.components == 1 && !c.drive && !c.imag_time &&
+           c.nx % 2 == 0;
 }
 
-int wide_strips(int nx) { return (nx + 119) / 120; }
-
-// Band height of a wide shape.  rows > 0 is taken as given; rows = 0 picks the
-// smallest height whose bands, one wave each, fit on the device at once (at the
-// kernel's waves per SIMD), at least 16 rows.
-int wide_band_rows(const phx_config& c, const StepShapeId& sh, bool has_v, int cus)
+// The height is the caller's, or chosen here (64 with one column per lane, 0 with two) from
+// the multiples of 8 rows.  A single wave on a SIMD waits for the results of its own chain
+// half of the time (four short stages per position), hence the low rates (imaginary time,
+// 1024^2: 13.7 us per step with one wave per SIMD and bands of 24 rows, 12.3 with three and 8).
+StepPlan step_plan(const phx_config& c, const StepShapeId& sh, int cus)
 {
-    if (sh.rows > 0) return sh.rows;
-    const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
+    const int w = wide_shape(sh.waves) ? 2 : 1;
+    const int strips = (c.nx + step_cols(w) - 1) / step_cols(w);
+    if (sh.rows > 0 && !(sh.waves == 1 && sh.rows == 64)) return StepPlan{strips, sh.rows};
     const bool noise = c.noise > 0.0 && noise_in_step(c, sh);
-    const int per_simd = wide_waves_per_simd(sh.waves == 2 ? 8 : 12, c.reservoir != 0, has_v, ghosts, noise);
-    const int slots = (cus > 0 ? cus : 256) * 4 * per_simd;
-    const int per_strip = slots / wide_strips(c.nx);
-    const int bands = per_strip > 0 ? per_strip : 1;
-    const int b = (c.ny + bands - 1) / bands;
-    return b < 16 ? 16 : b;
+    return StepPlan{strips, band_fill(strips, c.ny, 8, 4, 8, 8, cus,
+                                      step_waves_per_simd(w, c.precision == PHX_C128, c.reservoir != 0, c.drive != 0, noise),
+                                      0.5, 0.85).rows};
 }
 
 int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
@@ -227,19 +220,23 @@ int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
     const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
     const int words = w * (c.precision == PHX_C64 ? 1 : 2);
     return band_fill(pair_strips(c.nx, w), c.ny, 16, 9, 20, 12, cus,
-                     pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts)).rows;
+                     pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts, c.drive != 0)).rows;
 }
 
-// Two steps per launch where nothing has to happen between them (no noise or drive, no norm
-// to restore): the wide form whose band height the library chooses, with two columns per
+// Two steps per launch where nothing has to happen between them (no noise, no norm to
+// restore): the wide form whose band height the library chooses, with two columns per
 // lane, and the one-column form with tall bands (1 x 64; the two-step walk picks its own
 // height).  Faster than single steps at every size.  us per step, driven, one against two
 // steps per launch: wide 92.8 / 59.4 at 4096^2, 31.7 / 20.4 at 2048^2, 12.9 / 12.2 at
 // 1024^2; one column, complex64 115.7 / 72.6 at 4095^2, 22.6 / 11.9 at 1023^2; complex128
-// 190.6 / 130.4 at 4096^2, 63.7 / 37.7 at 2047^2, 33.0 / 17.0 at 1023^2.
+// 190.6 / 130.4 at 4096^2, 63.7 / 37.7 at 2047^2, 33.0 / 17.0 at 1023^2.  With the drive pairs
+// pay from 2^21 cells (one / two steps per launch, complex64: 9.2 / 11.5 at 513^2, 16.5 / 17.1
+// at 1024^2, 36.0 / 29.5 at 2048^2, 141 / 94 at 4096^2; complex128 20.2 / 31.6 at 1024^2, 57.9
+// / 44.6 at 2048^2): the profile's ring leaves registers for few waves.
 int pair_columns(const phx_config& c, const StepShapeId& sh)
 {
-    if (c.components != 1 || c.drive || c.imag_time || c.noise > 0.0) return 0;
+    if (c.components != 1 || c.imag_time || c.noise > 0.0) return 0;
+    if (c.drive && (int64_t)c.nx * c.ny < ((int64_t)1 << 21)) return 0;
     if (sh.waves == 2 && sh.rows == 0) return 2;
     return sh.waves == 1 && sh.rows == 64 ? 1 : 0;
 }
@@ -250,22 +247,23 @@ int pair_columns(const phx_config& c, const StepShapeId& sh)
 // 12.2 at 1024^2, 20.5 / 16.2 / 19.5 at 1536^2, 31.0 / 22.7 / 20.4 at 2048^2; complex128
 // (region / one column): 6.4 / 10.7 at 512^2, 23.5 / 17.0 at 1023^2, 75.8 / 37.7 at 2047^2;
 // without the reservoir 15.3 / 16.2 at 1023^2, 27.9 / 23.7 at 1531^2.  With the noise the
-// steps are single: the wide form, which draws the increments itself on periodic grids,
-// saves the separate pass; in complex128 the one-column form takes 62 against 76 us at 2047^2.
+// steps are single: the wide form, which draws the increments itself, saves the separate
+// pass (2048^2 45.1 -> 36.7 us); in complex128 the one-column form takes 62 against 76 us at
+// 2047^2.  Imaginary time, complex64: two columns per lane from 2^21 cells (25.9 us against
+// 44.2 at 2048^2 and 69 against 100.7 at 4096^2 with one column and bands of 40 rows).
 StepShapeId default_step_shape(const phx_config& c)
 {
-    // streaming only; 1 x 64 of the spinor walk lets it pick the band height itself
-    if (c.components == 2) return StepShapeId{1, 64};
-    if (c.imag_time || c.drive) return StepShapeId{1, 40};
     const int64_t cells = (int64_t)c.nx * c.ny, k = (int64_t)1 << 18;
     const bool c64 = c.precision == PHX_C64;
+    if (c.components == 2 || c.drive) return StepShapeId{1, 64};
+    if (c.imag_time) return c64 && cells >= 8 * k && step_shape_fits(c, 2) ? StepShapeId{2, 0} : StepShapeId{1, 64};
     const StepShapeId* shapes;
     step_shapes(c.precision, &shapes);
     const StepShapeId wide{2, 0}, one{1, 64};
     StepShapeId pick = shapes[0];
     if (c.noise > 0.0) {
         if (c64 && cells >= 4 * k && step_shape_fits(c, 2) && noise_in_step(c, wide)) pick = wide;
-        if (!c64 && cells >= 6 * k) pick = StepShapeId{1, 40};
+        if (!c64 && cells >= 6 * k) pick = one;
     } else if (c64) {
         if (cells >= 14 * k && step_shape_fits(c, 2))
             pick = wide;
@@ -422,8 +420,8 @@ phx_status phx_create(const phx_config* cfg, const phx_fields* f, void* stream,
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + L.flag, 0, 256, h->stream);
     if (e == hipSuccess && uses_step_index(*cfg)) e = set_noise_step(h, 0, h->stream);
     if (e == hipSuccess && cfg->drive && cfg->integrator == PHX_RK4)  // valid phasors before any launch
-        e = cfg->precision == PHX_C64 ? launch_drive_phasors<float>(h, 0, h->stream)
-                                      : launch_drive_phasors<double>(h, 0, h->stream);
+        e = cfg->precision == PHX_C64 ? launch_drive_phasors<float>(h, 0, 1, h->stream)
+                                      : launch_drive_phasors<double>(h, 0, 1, h->stream);
     if (e == hipSuccess && cfg->imag_time)  // valid norm target and scale before any launch
         e = cfg->precision == PHX_C64 ? launch_imag_norm<float>(h, f->psi, 0, h->stream)
                                       : launch_imag_norm<double>(h, f->psi, 0, h->stream);
@@ -501,7 +499,7 @@ phx_status rk4_stage_launches(phx_handle* h, int64_t n, hipStream_t stream)
     a.dt6 = (R)(c.dt / 6.0);
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
     for (int64_t k = 0; k < n; ++k) {
-        if (c.drive && launch_drive_phasors<R>(h, k, stream) != hipSuccess)
+        if (c.drive && launch_drive_phasors<R>(h, k, 1, stream) != hipSuccess)
             return fail(PHX_EHIP, "drive phasor launch failed");
         // stage 1: argument = state; stage s reads y written by stage s-1
         const C* yin[4] = {psi, Y[0], Y[1], Y[0]};
@@ -674,8 +672,11 @@ phx_status phx_step(phx_handle* h, int64_t n_steps, phx_info* out)
         if (h->cfg.imag_time && h->L.family == PHX_KERNEL_STEP) {
             // the streaming kernel applies each step's restoring scale to its input; the
             // last one is applied here so that the state ends normalized
-            const hipError_t e = c64 ? launch_imag_scale<float>(h, h->f.psi, h->stream)
-                                     : launch_imag_scale<double>(h, h->f.psi, h->stream);
+            const int count = imag_self_sum(h);
+            hipError_t e = count ? launch_imag_finish(h, (const double*)(h->ws + h->L.imag_partials), count, h->stream)
+                                 : hipSuccess;
+            if (e == hipSuccess)
+                e = c64 ? launch_imag_scale<float>(h, h->f.psi, h->stream) : launch_imag_scale<double>(h, h->f.psi, h->stream);
             if (e != hipSuccess) return fail(PHX_EHIP, "imaginary-time scale launch: %s", hipGetErrorString(e));
         }
         HIP_OR_FAIL(hipMemcpyAsync(&h->host[OBS_SLOTS], h->ws + h->L.flag, sizeof(unsigned int),

@@ -38,21 +38,39 @@ struct StepArgs {
     // as it is read, and each wave writes the FP64 norm partial of the cells it stores
     const double* imag_slots;
     double* imag_partials;
+    // imag_count > 0: no pass has formed the scale; each wave sums the imag_count partials
+    // of the step before (imag_prev) itself
+    const double* imag_prev;
+    int imag_count;
+    double cell_area;
     // coherent drive (streaming form only): profile [ny][nx] and the phasors
     // exp(-i omega t_s) of the four stage times of this step
     const C* E;
     const C* drive_ph;
     int comps;  // 2: the spinor streaming kernel (component stride nx*ny)
-    int band_rows;        // wide, two-step and spinor walks: rows per band (a launch argument)
-    int columns;          // spinor walk: columns per lane
-    int check;            // wide streaming form: test the stored values for non-finite ones
-    // wide streaming form with the Wiener increment added before the final store
+    int band_rows;        // streaming walks: rows per band (a launch argument)
+    int columns;          // streaming walks: columns per lane
+    int check;            // streaming walks: test the stored values for non-finite ones
+    // two columns per lane with the Wiener increment added before the final store
     // (null: no noise): step index *noise_step + noise_offset, variance a n + b, key
     const uint64_t* noise_step;
     int64_t noise_offset;
     R noise_a, noise_b;
     uint32_t noise_k0, noise_k1;
 };
+
+// Imaginary time: the scale that restores the norm, sqrt(target / norm of the step before).
+template <typename R>
+__device__ __forceinline__ R imag_scale(const StepArgs<R>& a)
+{
+    if (a.imag_count == 0) return (R)a.imag_slots[1];
+    double v = 0.0;
+    for (int i = threadIdx.x & 63; i < a.imag_count; i += 64) v += a.imag_prev[i];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+    const double norm = a.cell_area * v;
+    return (R)(norm > 0.0 ? sqrt(a.imag_slots[0] / norm) : 1.0);
+}
 
 // value held by lane-1 (lane 0 receives 0) and by lane+1 (lane 63 receives 0):
 // DPP wave shifts by one lane; out-of-range lanes read 0 (bound control).

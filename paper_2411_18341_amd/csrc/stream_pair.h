@@ -1,9 +1,9 @@
 // Device code of the two-step streaming RK4 kernel (one component): two whole steps of
 // Eqs. rk4_K1-rk4_final in one pass over the state.
 //
-// The band walk of stream_wide.h (W = 2 grid columns per lane: complex64 on even widths)
-// or of stream_body.h (W = 1: complex128, odd widths) with eight stages in the pipeline
-// instead of four: at row j the stages of the first step run at rows j - 1 ..
+// The band walk of stream_step.h (W = 2 grid columns per lane: complex64 on even widths;
+// W = 1: complex128, odd widths, the drive) with eight stages in the pipeline instead of
+// four: at row j the stages of the first step run at rows j - 1 ..
 // j - 4 and finish row j - 4 of the state in between, which stays in registers; the
 // stages of the second step run at rows j - 5 .. j - 8 on it, and row j - 8 is stored.
 // The state thus moves through HBM once for two steps.  The halo doubles: 8 columns on
@@ -31,8 +31,9 @@ namespace phx {
 
 // Waves per SIMD that the registers allow without scratch memory; words = 32-bit words of
 // the lane's real values per row (2: two complex64 columns or one complex128 column).
-constexpr int pair_waves_per_simd(int words, bool res, bool hasv, bool ghosts)
+constexpr int pair_waves_per_simd(int words, bool res, bool hasv, bool ghosts, bool drive)
 {
+    if (drive) return words == 1 ? 2 : 1;
     if (words == 1) return res && hasv ? 3 : 4;
     return res ? (hasv ? 1 : 2) : (hasv || ghosts ? 2 : 3);
 }
@@ -41,8 +42,9 @@ constexpr int kPairHalo = 8;
 constexpr int pair_cols(int w) { return 64 * w - 2 * kPairHalo; }  // output columns per strip
 
 // One band of `B` rows of strip `strip`; `finish(bad)` gets whether a stored value is not
-// finite (CHECK; else false without testing).
-template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, typename F>
+// finite (CHECK; else false without testing).  DRIVE: the coherent drive joins each stage's
+// derivative; a.drive_ph holds the eight phasors of the two steps.
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, bool DRIVE, typename F>
 __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip, int band, int B, int dir, F finish)
 {
     using C = typename cvec<R>::type;
@@ -63,6 +65,7 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
     const __amdgpu_buffer_rsrc_t rni = buffer_of(a.n_in, RES ? cells * sizeof(R) : 0);
     const __amdgpu_buffer_rsrc_t rP = buffer_of(a.P, RES ? cells * sizeof(R) : 0);
     const __amdgpu_buffer_rsrc_t rV = buffer_of(a.V, HASV ? cells * sizeof(R) : 0);
+    const __amdgpu_buffer_rsrc_t rE = buffer_of(a.E, DRIVE ? cells * sizeof(C) : 0);
     const __amdgpu_buffer_rsrc_t rpo = buffer_of(a.psi_out, cells * sizeof(C));
     const __amdgpu_buffer_rsrc_t rno = buffer_of(a.n_out, RES ? cells * sizeof(R) : 0);
     const __amdgpu_buffer_rsrc_t rnull = buffer_of(a.psi_out, 0);  // every access out of range
@@ -76,11 +79,13 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
     C sp[2][K][W], acc[2][4][W], w[2][3][3][W];  // w[.][q]: argument of stage q + 2
     R sn[2][K][W], accn[2][4][W], wn[2][3][3][W];
     R sP[K][W], sk[K][W];
+    C sE[K][W];
 #pragma unroll
     for (int e = 0; e < W; ++e) {
 #pragma unroll
         for (int s = 0; s < K; ++s) {
             sP[s][e] = R(0);
+            sE[s][e] = czero<C>();
             sk[s][e] = kdiag;
         }
 #pragma unroll
@@ -105,6 +110,12 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
         }
     }
 
+    C ph[8];
+    if constexpr (DRIVE) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) ph[s] = a.drive_ph[s];
+    }
+
     const int npos = B + 2 * kPairHalo;
     const int start = dir > 0 ? b0 - kPairHalo : b0 + B - 1 + kPairHalo;
     int g = start;
@@ -112,13 +123,17 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
     auto fetch = [&](int s, bool use) __attribute__((always_inline)) {
         const bool grow = YZERO && rw < 0;  // uniform: a ghost row reads 0 through the empty descriptor
         const int rr = grow ? 0 : rw;
-        if constexpr (W == 2) {
-            const wf4 v = wload4(grow ? rnull : rpi, vc, rr * rowc);
-            sp[0][s][0] = C{v.x, v.y};
-            sp[0][s][1] = C{v.z, v.w};
-        } else {
-            sp[0][s][0] = buf_load<C>(grow ? rnull : rpi, vc, rr * rowc);
-        }
+        auto load_complex = [&](__amdgpu_buffer_rsrc_t r, C (&v)[W]) __attribute__((always_inline)) {
+            if constexpr (W == 2) {
+                const wf4 x = wload4(r, vc, rr * rowc);
+                v[0] = C{x.x, x.y};
+                v[1] = C{x.z, x.w};
+            } else {
+                v[0] = buf_load<C>(r, vc, rr * rowc);
+            }
+        };
+        load_complex(grow ? rnull : rpi, sp[0][s]);
+        if constexpr (DRIVE) load_complex(grow ? rnull : rE, sE[s]);
         auto load_real = [&](__amdgpu_buffer_rsrc_t r, R (&v)[W]) __attribute__((always_inline)) {
             if constexpr (W == 2) {
                 const wf2 x = wload2(r, vr, rr * rowr);
@@ -170,6 +185,7 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
                     keep_here(sP[q][e]);
                 }
                 if (HASV) keep_here(sk[q][e]);
+                if constexpr (DRIVE) keep_here(sE[q][e]);
             }
 #pragma unroll
             for (int k = 1; k <= 8; ++k) {
@@ -211,6 +227,11 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
                     R fx, fy, fn;
                     cell_rhs<R, RES>(c, cur[e], lr[e].x, lr[e].y, up[e].x + dn[e].x, up[e].y + dn[e].y, nn[e],
                                          sP[q][e], sk[q][e], fx, fy, fn);
+                    if constexpr (DRIVE) {  // -(i/hbar) E ph
+                        const C d = sE[q][e], p = ph[k - 1];
+                        fx = fma(c.inv_hbar, d.x * p.y + d.y * p.x, fx);
+                        fy = fma(-c.inv_hbar, d.x * p.x - d.y * p.y, fy);
+                    }
                     C& ac = acc[h][a4][e];
                     R& an = accn[h][a4][e];
                     const C p0 = sp[h][q][e];
@@ -269,16 +290,16 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
     finish(CHECK && out_col && !(nf == R(0)));
 }
 
-template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK, bool DRIVE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
 void rk4_stream_pair_kernel(const StepArgs<R> a)
 {
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     const int band = t / a.tiles_x, strip = t - band * a.tiles_x;
-    stream_band_pair<R, W, RES, HASV, GHOSTS, YZERO, CHECK>(a, strip, band, a.band_rows, (band & 1) ? -1 : 1,
-                                                         [&](bool bad) __attribute__((always_inline)) {
-                                                             if (bad) a.flag[0] = 1u;  // benign race
-                                                         });
+    stream_band_pair<R, W, RES, HASV, GHOSTS, YZERO, CHECK, DRIVE>(a, strip, band, a.band_rows, (band & 1) ? -1 : 1,
+                                                                [&](bool bad) __attribute__((always_inline)) {
+                                                                    if (bad) a.flag[0] = 1u;  // benign race
+                                                                });
 }
 
 }  // namespace phx

@@ -4,7 +4,7 @@
 // the diagonal neighbours of the other component, and (RES) the reservoirs n_+-
 // with gain, reservoir interaction and pumps P_+-.
 //
-// The band walk is the one-component kernel's (stream_body.h): one wave per strip of
+// The band walk is the one-component kernel's (stream_step.h): one wave per strip of
 // columns plus a 4-column halo (W = 1 column per lane: 56 output columns; W = 2, complex64
 // without reservoirs on even widths: 120), rows walked once with the four stages pipelined
 // one row apart, inputs in an 8-row ring, running sums and stage arguments in rings of 4 --
@@ -97,7 +97,7 @@ constexpr int spinor_instructions(int w) { return w == 2 ? 532 : 297; }
 // One band of `B` rows (a multiple of 8) of strip `strip`; `finish(bad, norm)` gets whether
 // a stored value is not finite and the lane's norm partial.
 // IMAG: imaginary time (no reservoirs): each stage's derivative is rotated by -i, the
-// input is multiplied by the scale a.imag_slots[1] that restores the previous step's
+// input is multiplied by the scale that restores the previous step's
 // norm, and the norm partial is this lane's FP64 sum of |psi_out|^2 over both components
 // of the cells it stores.
 // DRIVE (no reservoirs, real time): the coherent drive -(i/hbar) E_s(r) exp(-i omega t_k)
@@ -113,7 +113,7 @@ __device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int str
     constexpr int K = 8;              // rows j - 4 .. j + PF are in flight
     // rows loaded ahead of their first use
     constexpr int PF = W == 2 ? 2 : 3;
-    const R sc = IMAG ? (R)a.imag_slots[1] : R(1);  // uniform
+    const R sc = IMAG ? imag_scale(a) : R(1);  // uniform
     double nrm = 0.0;
     const int lane = threadIdx.x & 63;
     const Coef<R>& c = a.c;
