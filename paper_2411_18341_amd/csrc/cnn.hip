@@ -13,10 +13,9 @@
 //                  and its one-pixel ring kept in LDS; layer 1 reads the float32 features
 //   backward-data  the forward kernel on dY with the weights flipped in the taps and
 //                  transposed in the channels, times the ReLU mask of the layer input
-//   backward-weight M = output channels, N = 9 taps x C_in, K = pixels: dY^T and three
-//                  x-shifted copies of X^T per tile in LDS; each workgroup accumulates
-//                  over its tiles and writes one set of partial sums, summed in a
-//                  fixed order.
+//   backward-weight M = output channels, N = 9 taps x C_in, K = pixels: dY and X per tile
+//                  in LDS, read transposed; each workgroup accumulates over its tiles and
+//                  writes one set of partial sums, summed in a fixed order.
 // Activations are NHWC bf16 with channels padded to a multiple of 8 (input) or 16
 // (output); weights are [c_out][K] with k = tap * C_in + c_in, tap = (dy+1)*3 + (dx+1),
 // K padded with zeros to a multiple of 32.
@@ -64,7 +63,8 @@ static LayerDims layer_dims(int cin, int cout)
 enum ConvMode { CONV_RELU_BF16 = 0, CONV_LINEAR_F32 = 1, CONV_MASK_BF16 = 2 };
 
 // Tiled forward convolution, persistent over tiles.  A workgroup of 4 waves keeps the
-// bf16 weights in LDS for all its tiles; a tile is TR rows x TW = 16*MT pixels of one
+// bf16 weights in LDS for all its tiles (in registers they cost a workgroup per CU, 36.7
+// against 31 us for 1M pixels, 32 -> 32 channels); a tile is TR rows x TW = 16*MT pixels of one
 // image, staged in LDS with a one-pixel circular halo.  Wave w computes rows w, w + 4,
 // ... of the tile as MT x NT MFMA blocks with the weights as operand A (16 output
 // channels x 32 k) and the input as operand B (32 k x 16 pixels), so each lane's
@@ -447,31 +447,67 @@ __global__ __launch_bounds__(PAIR_THREADS) void conv_pair_kernel(const void* __r
 // ----------------------------------------------------------- backward weights
 
 // dW[o][k] = sum_p dY[p][o] X[p + off(tap(k))][cin(k)] and db[o] = sum_p dY[p][o],
-// persistent over tiles of TR = 2 rows x TW = 16*MT pixels of one image.  Per tile the
-// workgroup stages dY^T [COUTP][TR*TW] and, for each x shift s = dx in {0, 1, 2}, X^T
-// [s][TR+2 rows][CINP][TW] with X at column x0 + c + s - 1, both written as pixel
-// pairs, so that both MFMA operands are 8 consecutive pixels per lane (K = pixels).
-// Wave w owns the N-tiles nt = w, w+4, ... of dW (16 columns of K each) for all
-// output channels and accumulates them over all tiles of the workgroup; at the end
-// the workgroup writes one set of COUTP*KP + COUTP partial sums.  Requires W % TW == 0.
-template <int CINP, int COUTP, int MT>
-__global__ __launch_bounds__(256) void conv_bwd_weight_kernel(const u16* __restrict__ x, const u16* __restrict__ dy,
-                                                              int H, int W, int images, float* __restrict__ partials)
+// persistent over tiles of TR rows x 32 pixels of one image.  X (with its one-pixel
+// circular ring) and dY go to LDS as they lie in memory, [row][pixel][channel], by loads
+// that write LDS directly; both MFMA operands want 8 consecutive pixels (K) of one channel
+// per lane, which the transposing LDS read gives: the 16 lanes of a group read 4 pixels x 16
+// channels, 8 bytes each, and lane i receives channel i of the 4 pixels.  A tap is then an
+// address offset of the one staged copy.
+// Wave w takes the tile's rows w RW .. w RW + RW - 1 for all taps and channels.  With 32
+// input channels it walks the rows of X once: each row's operands (3 x shifts x 2 channel
+// halves) meet the dY operands of the three rows above, at and below it.  The bias gradient
+// is one more product, with ones.  At the end the waves' sums are added in LDS, in a fixed
+// order, and the workgroup writes one set of COUTP*KP + COUTP partial sums.
+// Requires W % 32 == 0.
+//
+// Bound by HBM (X and dY are read once, 64 bytes per pixel each; two workgroups per CU, one
+// loading while the other computes): 1M pixels, 32 -> 32 channels 35.6 us, where copies of
+// X transposed on the way into LDS, one per x shift, took 90.8.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) const void glb_void;
+
+// pixels 0..3 and 4..7 (pixel stride `stride` elements) of this lane's channel
+__device__ __forceinline__ bf16x8 transposed8(const u16* p, int stride)
 {
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } r;
+    r.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    r.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * stride));
+    return r.v;
+}
+
+template <int CINP, int COUTP, int TR>
+__global__ __launch_bounds__(256, 2) void conv_bwd_weight_kernel(const u16* __restrict__ x, const u16* __restrict__ dy,
+                                                                 int H, int W, int images,
+                                                                 float* __restrict__ partials)
+{
+    static_assert(CINP == 32 || CINP == 8, "input channels of the corrector's layers");
     constexpr int KP = (9 * CINP + 31) / 32 * 32;
-    constexpr int MTN = COUTP / 16, NTILES = KP / 16, NPW = (NTILES + 3) / 4;
-    constexpr int TW = 16 * MT, TR = 2, NPX = TR * TW;
-    constexpr int XS = TW + 8, DS = NPX + 8;  // padded LDS row strides (16-byte multiples)
-    __shared__ __attribute__((aligned(16))) u16 sxt[3][TR + 2][CINP][XS];
-    __shared__ __attribute__((aligned(16))) u16 sdt[COUTP][DS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int MTN = COUTP / 16, NT = KP / 16, NB = (9 * CINP + 15) / 16;  // 16-column tiles of dW
+    constexpr int TW = 32, XW = TW + 2, XR = TR + 2, RW = TR / 4;
+    constexpr int NX = XR * XW * CINP / 8, ND = TR * TW * COUTP / 8;  // 16-byte chunks of a tile
+    constexpr int RN = 3;                                             // column tiles per pass of the final sum
+    constexpr int LDS_TILE = (NX + ND) * 16, LDS_RED = 4 * RN * MTN * 4 * 64 * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_TILE > LDS_RED ? LDS_TILE : LDS_RED];
+    u16* sx = (u16*)lds;
+    u16* sd = (u16*)(lds + NX * 16);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g = lane >> 4;
-    f32x4 acc[MTN][NPW];
+    f32x4 acc[NB][MTN], accb[MTN];
 #pragma unroll
-    for (int i = 0; i < MTN; ++i)
+    for (int i = 0; i < MTN; ++i) {
+        accb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < NPW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float dbias = 0.f;  // thread t < COUTP accumulates channel t
+        for (int j = 0; j < NB; ++j) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const __bf16 one = (__bf16)1.0f;
+    const bf16x8 ones = {one, one, one, one, one, one, one, one};
+    const int px = 8 * g + (m >> 2);  // pixel that this lane reads for its group
+    const u16* da = sd + (wave * RW * TW + px) * COUTP + 4 * (m & 3);
     const int tx_n = W / TW, ty_n = (H + TR - 1) / TR;
     const int tiles = images * ty_n * tx_n;
     for (int v = blockIdx.x; v < tiles; v += gridDim.x) {
@@ -479,98 +515,138 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_kernel(const u16* __restr
         const int img = t / (ty_n * tx_n);
         const int rt = t - img * (ty_n * tx_n);
         const int y0 = (rt / tx_n) * TR, x0 = (rt - (rt / tx_n) * tx_n) * TW;
-        __syncthreads();  // the previous tile's reads of the staging areas are done
-        for (int e = threadIdx.x; e < 3 * (TR + 2) * (TW / 2) * (CINP / 8); e += 256) {
-            const int c8 = e % (CINP / 8);
-            int rest = e / (CINP / 8);
-            const int c2 = rest % (TW / 2);
-            rest /= TW / 2;
-            const int r = rest % (TR + 2), sh = rest / (TR + 2);
-            int yy = y0 - 1 + r;
-            if (yy < 0) yy += H;
-            if (yy >= H) yy %= H;
-            int xa = x0 + 2 * c2 + sh - 1;
-            xa += (xa < 0) ? W : (xa >= W ? -W : 0);
-            const int xb = (xa + 1 == W) ? 0 : xa + 1;
-            const size_t row = (size_t)(img * H + yy) * W;
-            const uint4 va = *(const uint4*)&x[(row + xa) * CINP + 8 * c8];
-            const uint4 vb = *(const uint4*)&x[(row + xb) * CINP + 8 * c8];
-            const unsigned int aw[4] = {va.x, va.y, va.z, va.w}, bw[4] = {vb.x, vb.y, vb.z, vb.w};
+        __syncthreads();  // the previous tile's reads are done
+        // a wave's 64 chunks land at consecutive 16-byte places from its base on
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                *(unsigned int*)&sxt[sh][r][8 * c8 + 2 * j][2 * c2] = (aw[j] & 0xffffu) | (bw[j] << 16);
-                *(unsigned int*)&sxt[sh][r][8 * c8 + 2 * j + 1][2 * c2] = (aw[j] >> 16) | (bw[j] & 0xffff0000u);
+        for (int k = 0; k < (NX + 255) / 256; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            if (e < NX) {
+                const int c8 = e % (CINP / 8), pix = e / (CINP / 8);
+                const int r = pix / XW, c = pix - (pix / XW) * XW;
+                int yy = y0 - 1 + r;
+                if (yy < 0) yy += H;
+                if (yy >= H) yy %= H;
+                int xx = x0 - 1 + c;
+                xx += (xx < 0) ? W : (xx >= W ? -W : 0);
+                __builtin_amdgcn_global_load_lds((glb_void*)&x[((size_t)(img * H + yy) * W + xx) * CINP + 8 * c8],
+                                                 (lds_void*)(sx + 8 * (256 * k + 64 * wave)), 16, 0, 0);
             }
         }
-        for (int e = threadIdx.x; e < (NPX / 2) * (COUTP / 8); e += 256) {
-            const int c8 = e % (COUTP / 8), q = 2 * (e / (COUTP / 8));
-            const int rr = q / TW, cc = q - (q / TW) * TW;
-            uint4 va = uint4{0u, 0u, 0u, 0u}, vb = uint4{0u, 0u, 0u, 0u};
-            if (y0 + rr < H) {  // rows past the image bottom contribute nothing
-                const size_t base = ((size_t)(img * H + y0 + rr) * W + x0 + cc) * COUTP + 8 * c8;
-                va = *(const uint4*)&dy[base];
-                vb = *(const uint4*)&dy[base + COUTP];
-            }
-            const unsigned int aw[4] = {va.x, va.y, va.z, va.w}, bw[4] = {vb.x, vb.y, vb.z, vb.w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                *(unsigned int*)&sdt[8 * c8 + 2 * j][q] = (aw[j] & 0xffffu) | (bw[j] << 16);
-                *(unsigned int*)&sdt[8 * c8 + 2 * j + 1][q] = (aw[j] >> 16) | (bw[j] & 0xffff0000u);
+        for (int k = 0; k < (ND + 255) / 256; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            const int pix = e / (COUTP / 8), r = pix / TW;
+            if (e < ND) {
+                if (y0 + r < H)
+                    __builtin_amdgcn_global_load_lds(
+                        (glb_void*)&dy[((size_t)(img * H + y0) * W + (size_t)r * W + x0) * COUTP +
+                                       8 * (e - r * (TW * COUTP / 8))],
+                        (lds_void*)(sd + 8 * (256 * k + 64 * wave)), 16, 0, 0);
+                else  // rows past the image bottom contribute nothing
+                    *(uint4*)&sd[8 * e] = uint4{0u, 0u, 0u, 0u};
             }
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x < COUTP) {
-            float sacc = 0.f;
-            for (int q = 0; q < NPX; q += 8) {
-                const uint4 v = *(const uint4*)&sdt[threadIdx.x][q];
-                const unsigned int vw[4] = {v.x, v.y, v.z, v.w};
+        bf16x8 a[3][MTN];  // dY operands of rows R, R - 1, R - 2 of the wave
+        if constexpr (CINP == 32) {
+            const u16* xb = sx + (wave * RW * XW + px) * CINP + 4 * (m & 3);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) sacc += bf16_value((u16)(vw[j] & 0xffffu)) + bf16_value((u16)(vw[j] >> 16));
+            for (int R = 0; R < RW + 2; ++R) {
+                if (R < RW) {
+#pragma unroll
+                    for (int i = 0; i < MTN; ++i) {
+                        a[R % 3][i] = transposed8(da + R * TW * COUTP + 16 * i, COUTP);
+                        accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[R % 3][i], ones, accb[i], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {  // x shift q / 2, channel half q % 2
+                    const bf16x8 b = transposed8(xb + (R * XW + q / 2) * CINP + 16 * (q % 2), CINP);
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) {  // y shift: dY row R - s
+                        if (R - s < 0 || R - s >= RW) continue;
+                        f32x4(&c)[MTN] = acc[(3 * s + q / 2) * 2 + q % 2];
+#pragma unroll
+                        for (int i = 0; i < MTN; ++i)
+                            c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[(R - s) % 3][i], b, c[i], 0, 0, 0);
+                    }
+                }
             }
-            dbias += sacc;
-        }
+        } else {
+            // a column tile holds two taps: lanes with m % 4 < 2 read the first, the others the second
 #pragma unroll
-        for (int kc = 0; kc < NPX / 32; ++kc) {
-            const int rr = (kc * 32) / TW, cb = (kc * 32) % TW;
-            bf16x8 a[MTN];
+            for (int R = 0; R < RW; ++R) {
 #pragma unroll
-            for (int i = 0; i < MTN; ++i) a[i] = *(const bf16x8*)&sdt[i * 16 + m][kc * 32 + 8 * g];
+                for (int i = 0; i < MTN; ++i) {
+                    a[0][i] = transposed8(da + R * TW * COUTP + 16 * i, COUTP);
+                    accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], ones, accb[i], 0, 0, 0);
+                }
 #pragma unroll
-            for (int j = 0; j < NPW; ++j) {
-                const int nt = wave + 4 * j;
-                if (nt < NTILES) {
-                    const int k = nt * 16 + m;
-                    const int tap = k / CINP, ci = k - (k / CINP) * CINP;
-                    bf16x8 b = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                    if (tap < 9) b = *(const bf16x8*)&sxt[tap % 3][rr + tap / 3][ci][cb + 8 * g];
+                for (int j = 0; j < NB; ++j) {
+                    const int tap = 2 * j + ((m >> 1) & 1) < 9 ? 2 * j + ((m >> 1) & 1) : 8;
+                    const bf16x8 b = transposed8(
+                        sx + ((wave * RW + R + tap / 3) * XW + px + tap % 3) * CINP + 4 * (m & 1), CINP);
 #pragma unroll
-                    for (int i = 0; i < MTN; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < MTN; ++i)
+                        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b, acc[j][i], 0, 0, 0);
                 }
             }
         }
     }
     // lane holds C[4g + r][m]: dW[i*16 + 4g + r][nt*16 + m]
     float* part = partials + (size_t)blockIdx.x * (COUTP * KP + COUTP);
+    float* red = (float*)lds;
+    constexpr int RS = RN * MTN * 4 * 64;
 #pragma unroll
-    for (int j = 0; j < NPW; ++j) {
-        const int nt = wave + 4 * j;
-        if (nt < NTILES) {
+    for (int n0 = 0; n0 < NT; n0 += RN) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RN; ++j)
 #pragma unroll
             for (int i = 0; i < MTN; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) part[(size_t)(i * 16 + 4 * g + r) * KP + nt * 16 + m] = acc[i][j][r];
+                for (int r = 0; r < 4; ++r)
+                    red[wave * RS + ((j * MTN + i) * 4 + r) * 64 + lane] = n0 + j < NB ? acc[n0 + j < NB ? n0 + j : 0][i][r] : 0.f;
+        __syncthreads();
+        for (int e = threadIdx.x; e < RS; e += 256) {
+            const int l = e & 63, r = (e >> 6) & 3, i = (e >> 8) % MTN, nt = n0 + (e >> 8) / MTN;
+            const int k = nt * 16 + (l & 15);
+            const float sum = (red[e] + red[e + RS]) + (red[e + 2 * RS] + red[e + 3 * RS]);
+            if (nt < NT) part[(size_t)(i * 16 + 4 * (l >> 4) + r) * KP + k] = k < 9 * CINP ? sum : 0.f;
         }
     }
-    if (threadIdx.x < COUTP) part[COUTP * KP + threadIdx.x] = dbias;
+    __syncthreads();
+    if (m == 0) {
+#pragma unroll
+        for (int i = 0; i < MTN; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave * COUTP + i * 16 + 4 * g + r] = accb[i][r];
+    }
+    __syncthreads();
+    if (threadIdx.x < COUTP)
+        part[COUTP * KP + threadIdx.x] = (red[threadIdx.x] + red[COUTP + threadIdx.x]) +
+                                         (red[2 * COUTP + threadIdx.x] + red[3 * COUTP + threadIdx.x]);
 }
 
-// grads[e] = sum over workgroups of partials[wg][e].  A workgroup takes 64 entries;
+// grads[e] = sum over workgroups of partials[wg][e], all layers in one launch (blockIdx.y;
+// four launches took 34 us, 1M pixels).  A workgroup takes 64 entries;
 // its wave q sums the q-th quarter of the groups in eight interleaved running sums
 // (group g of the quarter goes to sum g mod 8), each wave keeping 8 loads per lane
 // in flight; the sums are combined in a fixed order, the quarters as (0 + 1) + (2 + 3).
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ partials, int n, int groups,
-                                                          float* __restrict__ out)
+struct PartialSums {
+    struct Layer {
+        const float* partials;
+        float* out;
+        int n, groups;
+    } layer[NLAYERS];
+};
+__global__ __launch_bounds__(256) void sum_partials_kernel(const PartialSums L)
 {
+    const float* __restrict__ partials = L.layer[blockIdx.y].partials;
+    float* __restrict__ out = L.layer[blockIdx.y].out;
+    const int n = L.layer[blockIdx.y].n, groups = L.layer[blockIdx.y].groups;
+    if ((int)blockIdx.x * 64 >= n) return;
     __shared__ float part[4][64];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + lane;
@@ -594,24 +670,37 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restri
 // tap-flipped, channel-transposed bf16 copy for backward-data:
 // wt[ci][k'] = w[o][tap * cinp + ci] with k' = (8 - tap) * coutp + o; every entry of
 // wt (cinp x kpt) is written, the K padding with zeros.
-__global__ __launch_bounds__(256) void pack_flipped_kernel(const float* __restrict__ w, int coutp, int cinp, int kp,
-                                                           int kpt, u16* __restrict__ wt)
+// All layers in one launch (blockIdx.y; four launches took 18 us).
+struct FlippedWeights {
+    struct Layer {
+        const float* w;
+        u16* wt;
+        int coutp, cinp, kp, kpt;
+    } layer[NLAYERS];
+};
+__global__ __launch_bounds__(256) void pack_flipped_kernel(const FlippedWeights L)
 {
+    const FlippedWeights::Layer& l = L.layer[blockIdx.y];
     const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= cinp * kpt) return;
-    const int ci = e / kpt, kk = e - (e / kpt) * kpt;
-    const int tp = kk / coutp, o = kk - (kk / coutp) * coutp;
-    wt[e] = tp < 9 ? bf16_bits(w[(size_t)o * kp + (8 - tp) * cinp + ci]) : (u16)0;
+    if (e >= l.cinp * l.kpt) return;
+    const int ci = e / l.kpt, kk = e - (e / l.kpt) * l.kpt;
+    const int tp = kk / l.coutp, o = kk - (kk / l.coutp) * l.coutp;
+    l.wt[e] = tp < 9 ? bf16_bits(l.w[(size_t)o * l.kp + (8 - tp) * l.cinp + ci]) : (u16)0;
 }
 
-// x_bf16[p][cinp] from x_f32[p][cin] (padded channels 0)
-__global__ __launch_bounds__(256) void pack_input_kernel(const float* __restrict__ x, int cin, int cinp, int P,
-                                                         u16* __restrict__ out)
+// x_bf16[p][8] from x_f32[p][4] (padded channels 0), one pixel per thread: one 16-byte read
+// where x is aligned, one 16-byte write (an element per thread took 19 us for 1M pixels).
+template <bool ALIGNED>
+__global__ __launch_bounds__(256) void pack_input_kernel(const float* __restrict__ x, int P, u16* __restrict__ out)
 {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= P * cinp) return;
-    const int p = e / cinp, c = e - (e / cinp) * cinp;
-    out[e] = c < cin ? bf16_bits(x[(size_t)p * cin + c]) : (u16)0;
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= P) return;
+    float4 v;
+    if constexpr (ALIGNED)
+        v = ((const float4*)x)[p];
+    else
+        v = make_float4(x[4 * (size_t)p], x[4 * (size_t)p + 1], x[4 * (size_t)p + 2], x[4 * (size_t)p + 3]);
+    ((chunk16*)out)[p] = chunk16{bf16_pair(v.x, v.y), bf16_pair(v.z, v.w), 0u, 0u};
 }
 
 // loss partial sums (one per workgroup; each thread takes pixels p, p + G, ... with G
@@ -762,7 +851,7 @@ struct phx_cnn {
     size_t w_off[NLAYERS], b_off[NLAYERS];  // element offsets into params
     int64_t n_params;
     // workspace regions (byte offsets)
-    size_t wt[NLAYERS], act[NLAYERS + 1], grad_act, grad_act2, out_f32, dy_last, partials,
+    size_t wt[NLAYERS], act[NLAYERS + 1], grad_act, grad_act2, out_f32, dy_last, partials[NLAYERS],
         loss_part, loss, grads_tmp;
     int bw_groups;
     size_t total;
@@ -808,7 +897,8 @@ static phx_status cnn_plan(const phx_cnn_config* c, phx_cnn* h)
     h->out_f32 = take((size_t)P * c->out_channels * 4);
     h->dy_last = take((size_t)P * h->dims[NLAYERS - 1].coutp * 2);
     h->bw_groups = 512;
-    h->partials = take((size_t)h->bw_groups * (32 * 288 + 32) * 4);
+    for (int l = 0; l < NLAYERS; ++l)
+        h->partials[l] = take((size_t)h->bw_groups * h->dims[l].coutp * (h->dims[l].kp + 1) * 4);
     h->loss_part = take((size_t)((P * 16 + 255) / 256) * 8);
     h->loss = take(8);
     h->grads_tmp = take((size_t)h->n_params * 4);
@@ -928,16 +1018,16 @@ static hipError_t launch_pair(const void* in, const float* wa, const float* ba, 
 static hipError_t cnn_pack_flipped(phx_cnn* h)
 {
     char* ws = (char*)h->buf.workspace;
+    FlippedWeights L;
+    int most = 0;
     for (int l = 0; l < NLAYERS; ++l) {
         const LayerDims& d = h->dims[l];
         const int kpt = (9 * d.coutp + 31) / 32 * 32;
-        const int nt = d.cinp * kpt;
-        pack_flipped_kernel<<<(nt + 255) / 256, 256, 0, h->stream>>>(h->buf.params + h->w_off[l], d.coutp, d.cinp,
-                                                                     d.kp, kpt, (u16*)(ws + h->wt[l]));
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        L.layer[l] = {h->buf.params + h->w_off[l], (u16*)(ws + h->wt[l]), d.coutp, d.cinp, d.kp, kpt};
+        if (d.cinp * kpt > most) most = d.cinp * kpt;
     }
-    return hipSuccess;
+    pack_flipped_kernel<<<dim3((most + 255) / 256, NLAYERS), 256, 0, h->stream>>>(L);
+    return hipGetLastError();
 }
 
 // Forward pass.  Training (keep_input) keeps every layer's input in the workspace for
@@ -960,9 +1050,10 @@ static phx_status cnn_forward_impl(phx_cnn* h, const float* x, int batch, float*
     }
     const bool aligned = ((uintptr_t)x & 15u) == 0;
     if (keep_input || !aligned) {
-        const int n0 = P * h->dims[0].cinp;
-        pack_input_kernel<<<(n0 + 255) / 256, 256, 0, s>>>(x, h->dims[0].cin, h->dims[0].cinp, P,
-                                                           (u16*)(ws + h->act[0]));
+        if (aligned)
+            pack_input_kernel<true><<<(P + 255) / 256, 256, 0, s>>>(x, P, (u16*)(ws + h->act[0]));
+        else
+            pack_input_kernel<false><<<(P + 255) / 256, 256, 0, s>>>(x, P, (u16*)(ws + h->act[0]));
         CNN_HIP(hipGetLastError());
     }
     if (!keep_input) {
@@ -1001,25 +1092,24 @@ phx_status phx_cnn_forward(phx_cnn* h, const float* x, int32_t batch, float* y)
     return cnn_forward_impl(h, x, batch, y, false);
 }
 
-// At most `groups` workgroups (the size of the partials buffer), no more than fit.
+// At most `groups` workgroups (the size of the partials buffer), no more than fit; `sums`
+// gets where the partial sums lie.
 template <int CINP, int COUTP>
 static hipError_t launch_bwd_weight(const u16* x, const u16* dy, int H, int W, int P, float* partials, int groups,
-                                    float* grads, hipStream_t s)
+                                    float* grads, PartialSums::Layer& sums, hipStream_t s)
 {
     static int per_cu[2] = {0, 0};
     const int images = P / (H * W);
-    const int mt4 = (W % 64 == 0) ? 1 : 0;
-    const int tiles = images * ((H + 1) / 2) * (W / (mt4 ? 64 : 32));
-    auto k = mt4 ? conv_bwd_weight_kernel<CINP, COUTP, 4> : conv_bwd_weight_kernel<CINP, COUTP, 2>;
-    int g = resident_groups(k, 256, per_cu[mt4]);
+    // tall tiles stage fewer halo rows; short ones when the tall would leave groups idle
+    const int tall = (int64_t)images * ((H + 15) / 16) * (W / 32) >= groups ? 1 : 0;
+    const int tiles = images * (tall ? (H + 15) / 16 : (H + 7) / 8) * (W / 32);
+    auto k = tall ? conv_bwd_weight_kernel<CINP, COUTP, 16> : conv_bwd_weight_kernel<CINP, COUTP, 8>;
+    int g = resident_groups(k, 256, per_cu[tall]);
     if (g <= 0 || g > groups) g = groups;
     if (g > tiles) g = tiles;
-    k<<<g, 256, 0, s>>>(x, dy, H, W, images, partials);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     constexpr int KP = (9 * CINP + 31) / 32 * 32;
-    const int n = COUTP * KP + COUTP;
-    sum_partials_kernel<<<(n + 63) / 64, 256, 0, s>>>(partials, n, g, grads);
+    sums = {partials, grads, COUTP * (KP + 1), g};
+    k<<<g, 256, 0, s>>>(x, dy, H, W, images, partials);
     return hipGetLastError();
 }
 
@@ -1047,26 +1137,33 @@ phx_status phx_cnn_gradients(phx_cnn* h, const float* x, const float* target, in
     sum_loss_kernel<<<1, 256, 0, s>>>((const double*)(ws + h->loss_part), lblocks, 1.0 / ((double)P * cout),
                                       loss ? loss : (double*)(ws + h->loss));
     CNN_HIP(hipGetLastError());
-    float* pp = (float*)(ws + h->partials);
+    PartialSums sums;
+    float* pp[NLAYERS];
+    for (int l = 0; l < NLAYERS; ++l) pp[l] = (float*)(ws + h->partials[l]);
     const u16* act[NLAYERS];
     for (int l = 0; l < NLAYERS; ++l) act[l] = (const u16*)(ws + h->act[l]);
     u16* ga = (u16*)(ws + h->grad_act);
     u16* gb = (u16*)(ws + h->grad_act2);
     // layer 4 (32 -> 16 padded): weights, then gradient into act[3]'s space
-    CNN_HIP((launch_bwd_weight<32, 16>(act[3], (const u16*)(ws + h->dy_last), H, W, P, pp, h->bw_groups,
-                                        grads + h->w_off[3], s)));
+    CNN_HIP((launch_bwd_weight<32, 16>(act[3], (const u16*)(ws + h->dy_last), H, W, P, pp[3], h->bw_groups,
+                                        grads + h->w_off[3], sums.layer[3], s)));
     CNN_HIP((launch_conv<16, 32, CONV_MASK_BF16>((const u16*)(ws + h->dy_last), (const u16*)(ws + h->wt[3]), nullptr,
                                                  H, W, P, ga, nullptr, 0, act[3], s)));
     // layer 3
-    CNN_HIP((launch_bwd_weight<32, 32>(act[2], ga, H, W, P, pp, h->bw_groups, grads + h->w_off[2], s)));
+    CNN_HIP((launch_bwd_weight<32, 32>(act[2], ga, H, W, P, pp[2], h->bw_groups, grads + h->w_off[2], sums.layer[2], s)));
     CNN_HIP((launch_conv<32, 32, CONV_MASK_BF16>(ga, (const u16*)(ws + h->wt[2]), nullptr, H, W, P, gb, nullptr, 0,
                                                  act[2], s)));
     // layer 2
-    CNN_HIP((launch_bwd_weight<32, 32>(act[1], gb, H, W, P, pp, h->bw_groups, grads + h->w_off[1], s)));
+    CNN_HIP((launch_bwd_weight<32, 32>(act[1], gb, H, W, P, pp[1], h->bw_groups, grads + h->w_off[1], sums.layer[1], s)));
     CNN_HIP((launch_conv<32, 32, CONV_MASK_BF16>(gb, (const u16*)(ws + h->wt[1]), nullptr, H, W, P, ga, nullptr, 0,
                                                  act[1], s)));
     // layer 1 (8 padded -> 32): weights only
-    CNN_HIP((launch_bwd_weight<8, 32>(act[0], ga, H, W, P, pp, h->bw_groups, grads + h->w_off[0], s)));
+    CNN_HIP((launch_bwd_weight<8, 32>(act[0], ga, H, W, P, pp[0], h->bw_groups, grads + h->w_off[0], sums.layer[0], s)));
+    int most = 0;
+    for (int l = 0; l < NLAYERS; ++l)
+        if (sums.layer[l].n > most) most = sums.layer[l].n;
+    sum_partials_kernel<<<dim3((most + 63) / 64, NLAYERS), 256, 0, s>>>(sums);
+    CNN_HIP(hipGetLastError());
     return PHX_OK;
 }
 
