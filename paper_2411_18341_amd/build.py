@@ -26,7 +26,7 @@ SOURCES = [
     "rk4_stream_spinor_drive_d.hip", "rk4_stream_spinor.hip", "runtime.hip", "rk4.hip",
     "reduce.hip", "dopri5.hip", "batch.hip", "batch_pair_f2.hip", "batch_pair_f1.hip",
     "batch_pair_d1.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive_f.hip", "rk4_stream_drive_d.hip", "rk4_stream_wide.hip", "rk4_stream_one_f.hip",
-    "rk4_stream_one_d.hip", "batch_one_f.hip", "batch_one_d.hip", "rk4_stream_pair_f2.hip",
+    "rk4_stream_one_d.hip", "batch_one_f.hip", "batch_one_d.hip", "batch_both.hip", "batch_both_noise.hip", "batch_pair_f3.hip", "rk4_stream_pair_f2.hip",
     "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip",
     "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip",
 ]
@@ -45,7 +45,8 @@ _FULL_UNROLL = ["-mllvm", "-pragma-unroll-threshold=40000"]
 EXTRA_FLAGS = {f"rk4_stream_spinor_{t}.hip": _FULL_UNROLL
                for t in ("f2", "f1", "d", "res_f", "res_d", "imag_f", "imag_d", "drive_f", "drive_d")}
 EXTRA_FLAGS.update({f"rk4_stream_{t}.hip": _FULL_UNROLL for t in ("wide", "one_f", "one_d", "drive_f", "drive_d")})
-EXTRA_FLAGS.update({u: _FULL_UNROLL for u in ("batch.hip", "batch_one_f.hip", "batch_one_d.hip")})
+EXTRA_FLAGS.update({u: _FULL_UNROLL for u in ("batch.hip", "batch_one_f.hip", "batch_one_d.hip", "batch_both.hip",
+                                                "batch_both_noise.hip", "batch_pair_f3.hip")})
 EXTRA_FLAGS.update({f"{u}_pair_{t}.hip": _FULL_UNROLL for u in ("rk4_stream", "batch") for t in ("f2", "f1", "d1")})
 EXTRA_FLAGS.update({f"dp_walk_{t}.hip": _FULL_UNROLL for t in ("f1", "f2", "d1", "d2")})
 # Units whose streaming kernels are checked for private (scratch) memory: a ring

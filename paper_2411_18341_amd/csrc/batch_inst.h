@@ -39,14 +39,13 @@ struct BatchForm {
     bool res, hasv, ghosts, yzero;  // yzero: every instance has a zero y boundary, else none
 };
 
-// One step per launch over all instances with W columns per lane (batch_walk.h).
-template <typename R, int W, bool NOISE>
-hipError_t launch_batch_step_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
-                               const BatchState<R>& b, uint64_t step, bool check, hipStream_t s);
-
-// Two steps per launch over all instances with W columns per lane (batch_pair.h).
-template <typename R, int W>
-hipError_t launch_batch_pair_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
-                               const BatchState<R>& b, bool check, hipStream_t s);
+// One step (batch_walk.h) or two (batch_pair.h) over all instances in one launch: total1
+// items with one column per lane, total2 with two.  FORMS: 1, 2, or 3 where both occur.
+template <typename R, int FORMS, bool NOISE>
+hipError_t launch_batch_step_forms(const BatchForm& f, int total1, int total2, const BatchInst<R>* inst, int count,
+                                   const BatchState<R>& b, uint64_t step, bool check, hipStream_t s);
+template <typename R, int FORMS>
+hipError_t launch_batch_pair_forms(const BatchForm& f, int total1, int total2, const BatchInst<R>* inst, int count,
+                                   const BatchState<R>& b, bool check, hipStream_t s);
 
 }  // namespace phx

@@ -1,6 +1,10 @@
-// Two-step form of the batched stepper (the walk of stream_pair.h) over the instances of
-// one column count per lane: a work item is one band of one strip of one instance, one
-// single-wave workgroup per item (consecutive items on one XCD).
+// Two-step form of the batched stepper (the walk of stream_pair.h): a work item is one band
+// of one strip of one instance, one single-wave workgroup per item (consecutive items on one
+// XCD).  The instances with two columns per lane form one list, those with one another; a
+// batch that has both runs them in one launch (FORMS = 3), the longer items of the first
+// list before the others, with the registers of the first.  (As two launches on two streams,
+// forked and joined by events, a pair of steps of 16 grids around 128^2 took 56 us, now 28; 256
+// grids of 128^2 to 1024^2, four steps, 1237 -> 1218.)
 #pragma once
 
 #include "batch_inst.h"
@@ -8,11 +12,10 @@
 
 namespace phx {
 
-template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, int WPE, bool CHECK>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
-void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, const BatchState<R> b)
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK>
+__device__ __forceinline__ void batch_pair_item(const BatchInst<R>* __restrict__ inst, int count,
+                                                const BatchState<R>& b, int t)
 {
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -42,29 +45,49 @@ void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, 
                                                            });
 }
 
-template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO>
-static void launch_batch_pair_t(int total, const BatchInst<R>* inst, int count, const BatchState<R>& b, bool check,
-                                hipStream_t s)
+// FORMS: column counts in the launch (1, 2, or 3 for both); total2: items with two columns
+template <typename R, int FORMS, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
+void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, const BatchState<R> b, int total2)
 {
-    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS, false);
-    if (check)
-        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, true><<<total, 64, 0, s>>>(inst, count, b);
-    else
-        batch_stream_pair_kernel<R, W, RES, HASV, GHOSTS, YZERO, WPE, false><<<total, 64, 0, s>>>(inst, count, b);
+    const int v = blockIdx.x;
+    if constexpr (FORMS != 1) {
+        if (FORMS == 2 || v < total2) {
+            batch_pair_item<R, 2, RES, HASV, GHOSTS, YZERO, CHECK>(inst, count, b, xcd_tile(v, total2));
+            return;
+        }
+    }
+    if constexpr (FORMS != 2)
+        batch_pair_item<R, 1, RES, HASV, GHOSTS, YZERO, CHECK>(inst, count, b,
+                                                              xcd_tile(v - total2, gridDim.x - total2));
 }
 
-template <typename R, int W>
-hipError_t launch_batch_pair_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
-                               const BatchState<R>& b, bool check, hipStream_t s)
+template <typename R, int FORMS, bool RES, bool HASV, bool GHOSTS, bool YZERO>
+static void launch_batch_pair_t(int total1, int total2, const BatchInst<R>* inst, int count, const BatchState<R>& b,
+                                bool check, hipStream_t s)
+{
+    constexpr int W = FORMS == 1 ? 1 : 2;
+    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS, false);
+    if (check)
+        batch_stream_pair_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, true, WPE>
+            <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2);
+    else
+        batch_stream_pair_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, false, WPE>
+            <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2);
+}
+
+template <typename R, int FORMS>
+hipError_t launch_batch_pair_forms(const BatchForm& f, int total1, int total2, const BatchInst<R>* inst, int count,
+                                   const BatchState<R>& b, bool check, hipStream_t s)
 {
 #define PHX_BP(RS, HV) \
     if (f.res == RS && f.hasv == HV) { \
         if (f.yzero) \
-            launch_batch_pair_t<R, W, RS, HV, true, true>(total, inst, count, b, check, s); \
+            launch_batch_pair_t<R, FORMS, RS, HV, true, true>(total1, total2, inst, count, b, check, s); \
         else if (f.ghosts) \
-            launch_batch_pair_t<R, W, RS, HV, true, false>(total, inst, count, b, check, s); \
+            launch_batch_pair_t<R, FORMS, RS, HV, true, false>(total1, total2, inst, count, b, check, s); \
         else \
-            launch_batch_pair_t<R, W, RS, HV, false, false>(total, inst, count, b, check, s); \
+            launch_batch_pair_t<R, FORMS, RS, HV, false, false>(total1, total2, inst, count, b, check, s); \
     }
     PHX_BP(true, true)
     PHX_BP(true, false)

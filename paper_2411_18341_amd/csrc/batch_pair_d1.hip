@@ -2,6 +2,6 @@
 #include "batch_pair.h"
 
 namespace phx {
-template hipError_t launch_batch_pair_w<double, 1>(const BatchForm&, int, const BatchInst<double>*, int,
-                                                  const BatchState<double>&, bool, hipStream_t);
+template hipError_t launch_batch_pair_forms<double, 1>(const BatchForm&, int, int, const BatchInst<double>*, int,
+                                                      const BatchState<double>&, bool, hipStream_t);
 }  // namespace phx

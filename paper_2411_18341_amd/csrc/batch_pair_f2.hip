@@ -2,6 +2,6 @@
 #include "batch_pair.h"
 
 namespace phx {
-template hipError_t launch_batch_pair_w<float, 2>(const BatchForm&, int, const BatchInst<float>*, int,
-                                                  const BatchState<float>&, bool, hipStream_t);
+template hipError_t launch_batch_pair_forms<float, 2>(const BatchForm&, int, int, const BatchInst<float>*, int,
+                                                      const BatchState<float>&, bool, hipStream_t);
 }  // namespace phx

@@ -1,6 +1,5 @@
-// One-step streaming form of the batched stepper (the walk of stream_step.h) over the
-// instances of one column count per lane: a work item is one band of one strip of one
-// instance, one single-wave workgroup per item (consecutive items on one XCD).
+// One-step streaming form of the batched stepper (the walk of stream_step.h), work items,
+// lists and launches as in batch_pair.h.
 #pragma once
 
 #include "batch_inst.h"
@@ -9,11 +8,10 @@
 namespace phx {
 
 // NOISE: the increment of step `step` joins the stored cells (two columns per lane)
-template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, bool NOISE, int WPE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
-void batch_stream_kernel(const BatchInst<R>* __restrict__ inst, int count, const BatchState<R> b, uint64_t step)
+template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, bool NOISE>
+__device__ __forceinline__ void batch_step_item(const BatchInst<R>* __restrict__ inst, int count,
+                                                const BatchState<R>& b, uint64_t step, int t)
 {
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -49,29 +47,49 @@ void batch_stream_kernel(const BatchInst<R>* __restrict__ inst, int count, const
         });
 }
 
-template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool NOISE>
-static void launch_batch_step_t(int total, const BatchInst<R>* inst, int count, const BatchState<R>& b, uint64_t step,
-                                bool check, hipStream_t s)
+// FORMS: column counts in the launch (1, 2, or 3 for both); total2: items with two columns
+template <typename R, int FORMS, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool CHECK, bool NOISE, int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
+void batch_stream_kernel(const BatchInst<R>* __restrict__ inst, int count, const BatchState<R> b, int total2,
+                         uint64_t step)
 {
-    constexpr int WPE = step_waves_per_simd(W, sizeof(R) == 8, RES, false, NOISE);
-    if (check)
-        batch_stream_kernel<R, W, RES, HASV, GHOSTS, YZERO, true, NOISE, WPE><<<total, 64, 0, s>>>(inst, count, b, step);
-    else
-        batch_stream_kernel<R, W, RES, HASV, GHOSTS, YZERO, false, NOISE, WPE><<<total, 64, 0, s>>>(inst, count, b, step);
+    const int v = blockIdx.x;
+    if constexpr (FORMS != 1) {
+        if (FORMS == 2 || v < total2) {
+            batch_step_item<R, 2, RES, HASV, GHOSTS, YZERO, CHECK, NOISE>(inst, count, b, step, xcd_tile(v, total2));
+            return;
+        }
+    }
+    if constexpr (FORMS != 2)
+        batch_step_item<R, 1, RES, HASV, GHOSTS, YZERO, CHECK, false>(inst, count, b, step,
+                                                                     xcd_tile(v - total2, gridDim.x - total2));
 }
 
-template <typename R, int W, bool NOISE>
-hipError_t launch_batch_step_w(const BatchForm& f, int total, const BatchInst<R>* inst, int count,
-                               const BatchState<R>& b, uint64_t step, bool check, hipStream_t s)
+template <typename R, int FORMS, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool NOISE>
+static void launch_batch_step_t(int total1, int total2, const BatchInst<R>* inst, int count, const BatchState<R>& b,
+                                uint64_t step, bool check, hipStream_t s)
+{
+    constexpr int WPE = step_waves_per_simd(FORMS == 1 ? 1 : 2, sizeof(R) == 8, RES, false, NOISE);
+    if (check)
+        batch_stream_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, true, NOISE, WPE>
+            <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2, step);
+    else
+        batch_stream_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, false, NOISE, WPE>
+            <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2, step);
+}
+
+template <typename R, int FORMS, bool NOISE>
+hipError_t launch_batch_step_forms(const BatchForm& f, int total1, int total2, const BatchInst<R>* inst, int count,
+                                   const BatchState<R>& b, uint64_t step, bool check, hipStream_t s)
 {
 #define PHX_BS(RS, HV) \
     if (f.res == RS && f.hasv == HV) { \
         if (f.yzero) \
-            launch_batch_step_t<R, W, RS, HV, true, true, NOISE>(total, inst, count, b, step, check, s); \
+            launch_batch_step_t<R, FORMS, RS, HV, true, true, NOISE>(total1, total2, inst, count, b, step, check, s); \
         else if (f.ghosts) \
-            launch_batch_step_t<R, W, RS, HV, true, false, NOISE>(total, inst, count, b, step, check, s); \
+            launch_batch_step_t<R, FORMS, RS, HV, true, false, NOISE>(total1, total2, inst, count, b, step, check, s); \
         else \
-            launch_batch_step_t<R, W, RS, HV, false, false, NOISE>(total, inst, count, b, step, check, s); \
+            launch_batch_step_t<R, FORMS, RS, HV, false, false, NOISE>(total1, total2, inst, count, b, step, check, s); \
     }
     PHX_BS(true, true)
     PHX_BS(true, false)
