@@ -100,26 +100,32 @@ static int batch_step_band(int ny, int cap)
     return ((ny + bands - 1) / bands + 7) / 8 * 8;
 }
 
-// Two-step form: columns per lane, strips and band height of one instance, the choice with
-// the fewest issued instructions: strips x bands x positions (B + 16 rows in chunks of 12,
-// nine positions' worth of stages left out at the start) x instructions per position.
+// Two-step form: columns per lane, strips and band height (up to `cap` rows, evened out
+// over the bands where any multiple of 4 will do) of one instance, the column count with the fewer issued
+// instructions: strips x bands x positions (B + 16 rows, nine positions' worth of stages left
+// out at the start) x instructions per position.
 // Tall bands save halo rows, but the last of them end late: up to 56 rows (256 driven grids
 // of 128^2 to 1024^2, four steps: 1264 us with bands of up to 44 rows, 1270 with 68, 1304 with 80, 1346
 // with 104; 2068 us with one step per launch), fewer where the device would not be full.
 static void batch_pair_plan(bool c64, int nx, int ny, int cap, int* w, int* strips, int* band)
 {
     double best = 0.0;
-    for (int k = 1; k <= (c64 && nx % 2 == 0 ? 2 : 1); ++k) {
+    auto consider = [&](int k, int b) {
         const int n = pair_strips(nx, k);
-        for (int b = 20; b <= cap; b += 12) {
-            const double cost = (double)n * ((ny + b - 1) / b) * (b + 7) * (k == 2 ? 397 : 215);
-            if (best == 0.0 || cost < best) {
-                best = cost;
-                *w = k;
-                *strips = n;
-                *band = b;
-            }
+        const double cost = (double)n * ((ny + b - 1) / b) * (b + 7) * (k == 2 ? 397 : 215);
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            *w = k;
+            *strips = n;
+            *band = b;
         }
+    };
+    for (int k = 1; k <= (c64 && nx % 2 == 0 ? 2 : 1); ++k) {
+        const int words = c64 ? k : 2, bands = (ny + cap - 1) / cap;
+        if (kPairStep[words] == 4)
+            consider(k, pair_band(words, (ny + bands - 1) / bands));
+        else
+            for (int b = kPairLow[words]; b <= std::max(cap, kPairLow[words]); b += kPairStep[words]) consider(k, b);
     }
 }
 
@@ -322,14 +328,16 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
             s_cap = cap;
         }
     }
-    for (int cap = 56; cap >= 20; cap -= 12) {
+    for (int cap = 56; cap >= 8; cap -= 12) {
         int64_t waves = 0;
+        int tallest = 0;
         for (int k = 0; k < d->count; ++k) {
-            int w = 1, strips = 1, band = 20;
+            int w, strips, band;
             batch_pair_plan(sizeof(R) == 4, d->instances[k].nx, d->instances[k].ny, cap, &w, &strips, &band);
             waves += (int64_t)strips * ((d->instances[k].ny + band - 1) / band);
+            tallest = std::max(tallest, band);
         }
-        const double cost = list_cost(waves, cap + 7, 4 * cus);
+        const double cost = list_cost(waves, tallest + 7, 4 * cus);
         if (p_best == 0.0 || cost < p_best) {
             p_best = cost;
             p_cap = cap;
@@ -358,7 +366,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         const int sw = sizeof(R) == 4 && I.nx % 2 == 0 ? 2 : 1;
         b.s_strips = (I.nx + step_cols(sw) - 1) / step_cols(sw);
         b.s_band = batch_step_band(I.ny, s_cap);
-        int w = 1;
+        int w;
         batch_pair_plan(sizeof(R) == 4, I.nx, I.ny, p_cap, &w, &b.p_strips, &b.p_band);
         for (int l = 0; l < 2; ++l) {
             b.s_tile0[l] = (int)std::min<int64_t>(s_tile0[l], INT32_MAX);

@@ -213,13 +213,12 @@ StepPlan step_plan(const phx_config& c, const StepShapeId& sh, int cus)
 
 int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
 
-// Band height of the two-step form with w columns per lane; the walk's B + 16 rows fill
-// whole chunks of 12 positions (B = 20, 32, 44, ...).
+// Band height of the two-step form with w columns per lane.
 int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 {
     const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
     const int words = w * (c.precision == PHX_C64 ? 1 : 2);
-    return band_fill(pair_strips(c.nx, w), c.ny, 16, 9, 20, 12, cus,
+    return band_fill(pair_strips(c.nx, w), c.ny, 16, 9, kPairLow[words], kPairStep[words], cus,
                      pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts, c.drive != 0)).rows;
 }
 
@@ -228,7 +227,7 @@ int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 // lane, and the one-column form with tall bands (1 x 64; the two-step walk picks its own
 // height).  Faster than single steps at every size.  us per step, driven, one against two
 // steps per launch: wide 92.8 / 59.4 at 4096^2, 31.7 / 20.4 at 2048^2, 12.9 / 12.2 at
-// 1024^2; one column, complex64 115.7 / 72.6 at 4095^2, 22.6 / 11.9 at 1023^2; complex128
+// 1024^2; one column, complex64 115.7 / 72.6 at 4095^2, 22.6 / 9.0 at 1024^2; complex128
 // 190.6 / 130.4 at 4096^2, 63.7 / 37.7 at 2047^2, 33.0 / 17.0 at 1023^2.  With the drive pairs
 // pay from 2^21 cells (one / two steps per launch, complex64: 9.2 / 11.5 at 513^2, 16.5 / 17.1
 // at 1024^2, 36.0 / 29.5 at 2048^2, 141 / 94 at 4096^2; complex128 20.2 / 31.6 at 1024^2, 57.9
@@ -243,8 +242,10 @@ int pair_columns(const phx_config& c, const StepShapeId& sh)
 
 // Shape used when the caller names none and does not tune: the region form on grids that
 // its many small workgroups fill better, the walks beyond.  us per step, driven: region
-// 8 x 4 / two steps with one column / with two columns per lane, complex64: 10.4 / 11.9 /
-// 12.2 at 1024^2, 20.5 / 16.2 / 19.5 at 1536^2, 31.0 / 22.7 / 20.4 at 2048^2; complex128
+// 8 x 4 / two steps with one column / with two columns per lane, complex64: 5.1 / 5.1 / - at
+// 512^2, 7.0 / 6.5 / 11.9 at 768^2, 10.4 / 9.0 / 12.1 at 1024^2, 20.5 / 13.7 / 16.7 at 1536^2,
+// 31.0 / 20.9 / 20.2 at 2048^2, - / 26.7 / 26.2 at 2400^2; with zero boundaries (region / one
+// column) 5.2 / 6.0 at 512^2, 10.8 / 10.9 at 1023^2, 20.7 / 14.9 at 1531^2; complex128
 // (region / one column): 6.4 / 10.7 at 512^2, 23.5 / 17.0 at 1023^2, 75.8 / 37.7 at 2047^2;
 // without the reservoir 15.3 / 16.2 at 1023^2, 27.9 / 23.7 at 1531^2.  With the noise the
 // steps are single: the wide form, which draws the increments itself, saves the separate
@@ -254,7 +255,7 @@ int pair_columns(const phx_config& c, const StepShapeId& sh)
 StepShapeId default_step_shape(const phx_config& c)
 {
     const int64_t cells = (int64_t)c.nx * c.ny, k = (int64_t)1 << 18;
-    const bool c64 = c.precision == PHX_C64;
+    const bool c64 = c.precision == PHX_C64, ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
     if (c.components == 2 || c.drive) return StepShapeId{1, 64};
     if (c.imag_time) return c64 && cells >= 8 * k && step_shape_fits(c, 2) ? StepShapeId{2, 0} : StepShapeId{1, 64};
     const StepShapeId* shapes;
@@ -267,7 +268,7 @@ StepShapeId default_step_shape(const phx_config& c)
     } else if (c64) {
         if (cells >= 14 * k && step_shape_fits(c, 2))
             pick = wide;
-        else if (cells >= 6 * k)
+        else if (cells >= (ghosts ? 5 : 2) * k)
             pick = one;
     } else if (cells >= (c.reservoir ? 3 : 5) * k) {
         pick = one;

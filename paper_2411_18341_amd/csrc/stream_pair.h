@@ -13,14 +13,18 @@
 //
 // Stage k = 1..8 of the pipeline starts at position 2 k: no stage after it needs its
 // earlier rows.  The first twelve positions are a copy of the loop body with the stages
-// left out that have not started.  The walk runs in whole chunks of twelve positions (an
-// exit inside a chunk would make every ring slot live to a common end).
+// left out that have not started.  The walk runs in whole chunks (an exit inside a
+// chunk costs 30 to 70 registers) except with one complex64 column, which leaves registers
+// for it: that walk ends at a multiple of four positions, inside a chunk by ending the
+// program there (a branch to a common end would make every ring slot live to it).
 //
 // Bound by the VALU issue: 24.8 instructions per cell and stage, and with the halo (128 x
 // (B + 10) cells evaluated for 112 x B stored) all SIMDs issue back to back: 118.8 us per
 // launch, 59.4 us per step, at 4096^2 driven (B 80, 1924 waves, 2 per SIMD); the one-step
 // wide form takes 92.8 us per step, bound by HBM (28 bytes per point and step).  One
-// wave per SIMD with bands of 152 rows takes 63.6 us, ragged fillings 66 to 95 us.
+// wave per SIMD with bands of 152 rows takes 63.6 us, ragged fillings 66 to 95 us.  One
+// complex64 column: with heights of any multiple of 4 rows 9.0 us per step at 1024^2, 13.7 at
+// 1536^2 and 20.9 at 2047^2; in whole chunks 11.9, 16.2 and 22.7.
 #pragma once
 
 #include <type_traits>
@@ -40,6 +44,14 @@ constexpr int pair_waves_per_simd(int words, bool res, bool hasv, bool ghosts, b
 
 constexpr int kPairHalo = 8;
 constexpr int pair_cols(int w) { return 64 * w - 2 * kPairHalo; }  // output columns per strip
+// Band heights whose positions the walk does not idle through, low + k step by `words` (as
+// above), and the smallest of at least `rows`.
+constexpr int kPairLow[3] = {0, 8, 20}, kPairStep[3] = {0, 4, 12};
+constexpr int pair_band(int words, int rows)
+{
+    const int lo = kPairLow[words], step = kPairStep[words];
+    return rows <= lo ? lo : lo + (rows - lo + step - 1) / step * step;
+}
 
 // One band of `B` rows of strip `strip`; `finish(bad)` gets whether a stored value is not
 // finite (CHECK; else false without testing).  DRIVE: the coherent drive joins each stage's
@@ -283,9 +295,14 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
                     }
                 }
             }
+            if (W == 1 && sizeof(R) == 4 && !FIRST && (u == 3 || u == 7) && base + u + 1 >= npos) {  // uniform
+                finish(CHECK && out_col && !(nf == R(0)));
+                __builtin_amdgcn_endpgm();
+            }
         }
     };
     positions(std::true_type{}, 0);
+    // npos > K: the bands have at least 8 rows
     for (int base = K; base < npos; base += K) positions(std::false_type{}, base);
     finish(CHECK && out_col && !(nf == R(0)));
 }

@@ -88,3 +88,14 @@ def test_imag_scale_forms(nx, ny, tile, precision):
     assert run.observables()["nonfinite"] == 0
     run.close()
     assert rel_l2(got, want) <= TOL[precision]
+
+
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("nx,ny", [(720, 724), (725, 728), (1144, 1143), (1146, 1146), (1024, 1024), (1000, 1301),
+                                   (1311, 1500), (1537, 1702), (999, 2011)])
+def test_pair_heights_bitwise(nx, ny, bc):
+    """Grids on which the two-step walk with one column per lane ends inside a chunk, and
+    around the sizes from which it is the default."""
+    region = end_state("driven", nx, ny, bc, C64, (8, 4), calls=(4, 3))
+    assert same(region, end_state("driven", nx, ny, bc, C64, (1, 64), calls=(4, 3)))
+    assert same(region, end_state("driven", nx, ny, bc, C64, (0, 0), calls=(4, 3)))
