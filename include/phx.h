@@ -282,8 +282,8 @@ phx_status phx_autotune(phx_handle *h, int32_t reps, phx_tune_result *out);
 /* ---------------------------------------------------------------- batches
  * Many independent one-component instances (Eq. 1, optionally with the pump-fed
  * reservoir of Eqs. PULSE_psi / PULSE_res) on grids of different sizes, advanced
- * together by one persistent whole-step RK4 kernel launch per step: workgroups
- * walk a list of (instance, region) work items.  Instance k uses
+ * together over one list of (instance, band or region) work items: two RK4 steps per
+ * launch where no noise is drawn, one otherwise.  Instance k uses
  * params[instances[k].param_index] for its physics, boundaries and dt (the nx,
  * ny, components, precision, integrator, kernel and tile fields of the params are
  * ignored), on its own slice of packed caller-owned device arrays. */
@@ -320,8 +320,9 @@ typedef struct phx_batch_desc {
 phx_status phx_batch_workspace_bytes(const phx_batch_desc *desc, size_t *out);
 
 /* Advance every instance by n_steps RK4 steps (Eqs. rk4_K1-rk4_final), enqueued on
- * hip_stream.  Uploads the instance table (synchronizing the stream once), then
- * one persistent launch per step.  With check_finite = 1 it waits for the stream
+ * hip_stream.  The instance table travels as launch arguments; a table too long for that
+ * (more than 96 to 150 instances) is copied, which synchronizes the stream once, as does
+ * noise on instances whose increments a pass of its own draws.  With check_finite = 1 it waits for the stream
  * at the end and returns PHX_ENONFINITE if any stored value was not finite.
  * Errors: PHX_EINVAL (bad descriptor, slice outside total_cells or overlapping,
  * unstable dt), PHX_EWORKSPACE, PHX_EUNSUPPORTED, PHX_EHIP, PHX_ENONFINITE. */

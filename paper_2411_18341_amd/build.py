@@ -20,15 +20,16 @@ INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libphx.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 SOURCES = [
-    "rk4_step.hip", "rk4_stream_spinor_f2.hip", "rk4_stream_spinor_f1.hip",
-    "rk4_stream_spinor_d.hip", "rk4_stream_spinor_res_f.hip", "rk4_stream_spinor_res_d.hip",
-    "rk4_stream_spinor_imag_f.hip", "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip",
-    "rk4_stream_spinor_drive_d.hip", "rk4_stream_spinor.hip", "runtime.hip", "rk4.hip",
-    "reduce.hip", "dopri5.hip", "batch.hip", "batch_pair_f2.hip", "batch_pair_f1.hip",
-    "batch_pair_d1.hip", "autotune.hip", "cnn.hip", "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive_f.hip", "rk4_stream_drive_d.hip", "rk4_stream_wide.hip", "rk4_stream_one_f.hip",
-    "rk4_stream_one_d.hip", "batch_one_f.hip", "batch_one_d.hip", "batch_both.hip", "batch_both_noise.hip", "batch_pair_f3.hip", "rk4_stream_pair_f2.hip",
-    "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip", "dp_walk_f2.hip",
-    "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip",
+    "rk4_step.hip", "rk4_stream_spinor_f2.hip", "rk4_stream_spinor_f1.hip", "rk4_stream_spinor_d.hip",
+    "rk4_stream_spinor_res_f.hip", "rk4_stream_spinor_res_d.hip", "rk4_stream_spinor_imag_f.hip",
+    "rk4_stream_spinor_imag_d.hip", "rk4_stream_spinor_drive_f.hip", "rk4_stream_spinor_drive_d.hip",
+    "rk4_stream_spinor.hip", "runtime.hip", "rk4.hip", "reduce.hip", "dopri5.hip", "batch.hip",
+    "batch_pair_f2.hip", "batch_pair_f1.hip", "batch_pair_d1.hip", "autotune.hip", "cnn.hip",
+    "noise.hip", "drive.hip", "imag.hip", "rk4_stream_drive_f.hip", "rk4_stream_drive_d.hip",
+    "rk4_stream_wide.hip", "rk4_stream_one_f.hip", "rk4_stream_one_d.hip", "batch_one_f.hip",
+    "batch_one_d.hip", "batch_both.hip", "batch_both_noise.hip", "batch_pair_f3.hip",
+    "rk4_stream_pair_f2.hip", "rk4_stream_pair_f1.hip", "rk4_stream_pair_d1.hip", "dp_walk_f1.hip",
+    "dp_walk_f2.hip", "dp_walk_d1.hip", "dp_walk_d2.hip", "copy.hip", "static_obs.hip",
 ]
 
 ARCH = "gfx950"

@@ -512,8 +512,8 @@ class Solver:
 
 
 class Batch:
-    """Packed torch buffers for many one-component instances and a persistent
-    batched stepper (phx_batch_step).
+    """Packed torch buffers for many one-component instances and their batched
+    stepper (phx_batch_step).
 
     grids: list of (nx, ny); params: list of phx_config (physics, boundaries, dt);
     param_index: per-instance index into params.  Instance k's cells are

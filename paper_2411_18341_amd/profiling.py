@@ -64,7 +64,8 @@ def kernel_kind(name: str) -> str:
     if m:  # streaming form (also with the drive or in imaginary time): shape 1 x band rows
         return f"rk4_step_1x{m.group(1)}"
     named = {"rk4_step_kernel": "rk4_step", "batch_step_kernel": "batch_step", "dp_restart_kernel": "dp_restart",
-             "dp_err_sum_kernel": "dp_error", "dp_stream_kernel": "dp_step", "rk4_stream_pair_kernel": "rk4_step_pair", "rk4_stream_step_kernel": "rk4_step_walk", "obs_pass1": "obs_pass1", "obs_pass2": "obs_pass2",
+             "dp_err_sum_kernel": "dp_error", "dp_stream_kernel": "dp_step",
+             "rk4_stream_pair_kernel": "rk4_step_pair", "rk4_stream_step_kernel": "rk4_step_walk", "obs_pass1": "obs_pass1", "obs_pass2": "obs_pass2",
              "conv_fwd_kernel": "conv_fwd", "conv_bwd_weight_kernel": "conv_bwd_weight",
              "wiener_noise_kernel": "wiener_noise"}
     for k, v in named.items():

@@ -15,7 +15,7 @@ smallest; large ones stream from HBM.
     python -m paper_2411_18341_amd.sweep --sizes 128 256 512 1024 2048 4096 8192 --out sweep.md
 
 With --batch it first measures the batched workload of 256 driven instances on
-grids of 128..1024 (one persistent launch per step) against stepping the same
+grids of 128..1024 (one launch per one or two steps) against stepping the same
 instances with one solver each; with --spinor the 4096^2 two-component workload
 with RK4 and with Dormand-Prince; with --noise the 4096^2 driven workload with the
 truncated-Wigner noise on and off; with --drive the stage-fused kernels with and without
@@ -82,7 +82,7 @@ def measure(n: int, family: str, precision=phx.PHX_C64, warmup: int = 20, tune_r
 def measure_batch(steps: int = 500, warmup: int = 20, count: int = 256, seed: int = 4, loop_steps: int = 50):
     """The batched sweep workload (inputs.batch_sizes / batch_pumps / batch_instance:
     `count` driven instances on square grids drawn log-uniformly in [128, 1024],
-    complex64) stepped by one persistent launch per step, against the same instances
+    complex64) stepped together, one launch per one or two steps, against the same instances
     stepped one solver at a time (each with its own whole-step launches, graph
     chunks and default region shape)."""
     import torch
