@@ -84,18 +84,17 @@ typedef struct phx_config {
                                whole-step kernel: waves per workgroup of the region form
                                (4, 8, 12, 16), 1 for the streaming form, 2 or 3 for the wide
                                streaming form (two columns per lane; complex64, one
-                               component, no drive, even nx; 2: 8-row input ring, 3: 12-row
-                               ring; with the noise on periodic grids the increment is
-                               drawn in the step, with imaginary time the norm partials are
-                               written per wave)                                           */
+                               component, no drive, even nx; 3 runs as 2; with the noise
+                               the increment is drawn in the step, with imaginary time the
+                               norm partials are written per wave)                         */
     int32_t tile_rows;      /* rows per wave (stage-fused: 1..64); streaming form: rows per
                                band (40, 64, 88, 112); wide streaming form: rows per band
                                (8..4096), or 0 for the height that fills the device with
                                one wave per band (2 x 0 then takes two steps per launch where
-                               neither noise, drive nor imaginary time comes between them);
-                               1 x 64 does so with one column per lane, and lets the library
-                               pick the band height for two steps per launch and for the
-                               spinor; streaming forms need a state under 2 GiB;
+                               neither noise nor imaginary time comes between them); 1 x 64
+                               does so with one column per lane (with the drive from 2^21
+                               cells on), and lets the library pick the band height, also
+                               for the spinor; streaming forms need a state under 2 GiB;
                                0 with tile_wx 0 = automatic                                 */
     int32_t graph_steps;    /* RK4 steps per captured hipGraph chunk replayed by phx_step:
                                0 = default (64), < 0 = launch every kernel directly        */
@@ -127,7 +126,7 @@ typedef struct phx_config {
                                drive all off, else PHX_EINVAL): RK4 steps of
                                d psi/d tau = -(1/hbar) H psi (the streaming whole-step
                                kernel when the state is under 2 GiB: one component on the
-                               one-column or wide walk, two on the spinor walk; else, or
+                               streaming walk, two on the spinor walk; else, or
                                on request, the stage-fused kernels), each
                                followed by scaling psi so that its total norm
                                dx dy sum_s,cells |psi_s|^2 equals the value it had when the

@@ -90,6 +90,8 @@ static double list_cost(int64_t waves, int positions, int simds)
     return positions * (std::max(1.2, (double)waves / simds) + 0.5);
 }
 
+constexpr int kFullLists = 6;  // waves per SIMD from which shorter bands cannot help
+
 // Band height of the one-step walk, a multiple of 8 rows evened out over an instance's
 // bands; the tallest is the cheapest by list_cost (16 grids of 256^2: bands of 8 rows, 1536
 // waves; the step took 31.6 us with bands of 48 and takes 14).  Drawing the increments in
@@ -312,10 +314,16 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    // tallest bands of the walks: the candidates that give the shortest list
+    // tallest bands of the walks: the candidates that give the shortest list; the search ends
+    // at once where tall bands already make kFullLists waves per SIMD (45 us of host time for
+    // 256 instances), and a walk that the call does not use is not planned
+    bool any_noise = false;
+    for (int k = 0; k < d->n_params; ++k) any_noise = any_noise || d->params[k].noise > 0.0;
+    const bool plan_pairs = !any_noise && pair_launches(n) > 0, plan_steps = any_noise || 2 * pair_launches(n) < n;
+    const int64_t full = (int64_t)kFullLists * 4 * cus;
     int s_cap = 64, p_cap = 56;
     double s_best = 0.0, p_best = 0.0;
-    for (int cap = 64; cap >= 8; cap -= 8) {
+    for (int cap = 64; plan_steps && cap >= 8; cap -= 8) {
         int64_t waves = 0;
         for (int k = 0; k < d->count; ++k) {
             const phx_instance& I = d->instances[k];
@@ -327,8 +335,9 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
             s_best = cost;
             s_cap = cap;
         }
+        if (waves >= full) break;
     }
-    for (int cap = 56; cap >= 8; cap -= 12) {
+    for (int cap = 56; plan_pairs && cap >= 8; cap -= 12) {
         int64_t waves = 0;
         int tallest = 0;
         for (int k = 0; k < d->count; ++k) {
@@ -342,6 +351,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
             p_best = cost;
             p_cap = cap;
         }
+        if (waves >= full) break;
     }
     int64_t s_tile0[2] = {0, 0}, p_tile0[2] = {0, 0};  // work items with one and two columns per lane
     for (int k = 0; k < d->count; ++k) {

@@ -218,7 +218,7 @@ inline void noise_coefs(const phx_config& c, R& a, R& b, uint32_t& k0, uint32_t&
     k0 = (uint32_t)c.seed;
     k1 = (uint32_t)(c.seed >> 32);
 }
-// The wide streaming step adds the increment itself before its final store (one
+// The two-column step adds the increment itself before its final store (one
 // component, complex64, periodic in x and y); elsewhere a separate pass follows the step.
 bool noise_in_step(const phx_config& c, const StepShapeId& sh);
 hipError_t set_noise_step(const phx_handle* h, int64_t value, hipStream_t s);
