@@ -219,7 +219,7 @@ inline void noise_coefs(const phx_config& c, R& a, R& b, uint32_t& k0, uint32_t&
     k1 = (uint32_t)(c.seed >> 32);
 }
 // The two-column step adds the increment itself before its final store (one
-// component, complex64, periodic in x and y); elsewhere a separate pass follows the step.
+// component, complex64, even widths); elsewhere a separate pass follows the step.
 bool noise_in_step(const phx_config& c, const StepShapeId& sh);
 hipError_t set_noise_step(const phx_handle* h, int64_t value, hipStream_t s);
 // Drive phasors exp(-i omega t_s) of the four RK4 stage times of the `steps` (1 or 2) steps
