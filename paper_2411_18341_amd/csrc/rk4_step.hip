@@ -176,7 +176,7 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
 template <typename R>
 hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* steps)
 {
-    const int pair = pair_columns(h->cfg, sh);
+    const int pair = pair_columns(h->cfg, sh, h->f.V != nullptr);
     *steps = pair ? 2 : 1;
     const bool res = h->cfg.reservoir != 0;
     char* A = h->ws + h->L.alt;
@@ -214,7 +214,7 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
     const StepShapeId sh = h->step_shape;
     const bool fused_noise = c.noise > 0.0 && noise_in_step(c, sh);
-    const int columns = pair_columns(c, sh);
+    const int columns = pair_columns(c, sh, hv);
     int64_t pairs = columns ? pair_launches(n) : 0;
     int cur = h->step_parity;
     for (int64_t k = 0, steps = 1; k < n; k += steps) {
@@ -278,7 +278,7 @@ phx_status rk4_fused_steps(phx_handle* h, int64_t n)
     h->step_parity = 0;
     const int G = graph_chunk(c);
     const int64_t direct = h->timing || G == 0 || n < G ? n : n % G;  // steps after the graph replays
-    if ((n & 1) && !(pair_columns(c, h->step_shape) && pair_launches(direct) > 0)) {
+    if ((n & 1) && !(pair_columns(c, h->step_shape, h->f.V != nullptr) && pair_launches(direct) > 0)) {
         void* alt = h->ws + h->L.alt;
         if (hipMemcpyAsync(alt, h->f.psi, cells * c.components * 2 * rs, hipMemcpyDeviceToDevice, h->stream) !=
                 hipSuccess ||

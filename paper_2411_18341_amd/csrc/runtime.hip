@@ -231,11 +231,13 @@ int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 // 190.6 / 130.4 at 4096^2, 63.7 / 37.7 at 2047^2, 33.0 / 17.0 at 1023^2.  With the drive pairs
 // pay from 2^21 cells (one / two steps per launch, complex64: 9.2 / 11.5 at 513^2, 16.5 / 17.1
 // at 1024^2, 36.0 / 29.5 at 2048^2, 141 / 94 at 4096^2; complex128 20.2 / 31.6 at 1024^2, 57.9
-// / 44.6 at 2048^2): the profile's ring leaves registers for few waves.
-int pair_columns(const phx_config& c, const StepShapeId& sh)
+// / 44.6 at 2048^2): the profile's ring leaves registers for few waves.  In complex128 with
+// a potential as well they never do (2048^2, us per step, one / two steps per launch: 62 /
+// 68 with the reservoir, 44 / 45 to 49 without).
+int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v)
 {
     if (c.components != 1 || c.imag_time || c.noise > 0.0) return 0;
-    if (c.drive && (int64_t)c.nx * c.ny < ((int64_t)1 << 21)) return 0;
+    if (c.drive && ((int64_t)c.nx * c.ny < ((int64_t)1 << 21) || (c.precision == PHX_C128 && has_v))) return 0;
     if (sh.waves == 2 && sh.rows == 0) return 2;
     return sh.waves == 1 && sh.rows == 64 ? 1 : 0;
 }

@@ -68,7 +68,7 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
     const int gi = strip * pair_cols(W) - kPairHalo + W * lane;  // first column of the lane
     const int ci = wrap_any(gi, a.nx, a.bcx);                     // -1: ghost (zero x boundary)
     const bool gcol = GHOSTS && ci < 0;
-    const R keep = gcol ? R(0) : R(1);
+    R keep = gcol ? R(0) : R(1);
     const int b0 = band * B;
     const R kdiag = R(2) * (c.ax + c.ay);
     const int rowc = a.nx * (int)sizeof(C), rowr = a.nx * (int)sizeof(R);
@@ -186,6 +186,14 @@ __device__ __forceinline__ void stream_band_pair(const StepArgs<R>& a, int strip
         for (int u = 0; u < K; ++u) {
             const int j = start + dir * (base + u);        // newest row of this position
             fetch(slot<K>(u, -PF), base + u + PF < npos);  // row j + PF
+            if constexpr (DRIVE && sizeof(R) == 8 && RES && GHOSTS) {
+                park(keep);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    park(ph[s].x);
+                    park(ph[s].y);
+                }
+            }
             // Row j arrives: its values leave the four- and two-register groups that the
             // loads write (kept there for their whole life they fragment the register file).
 #pragma unroll

@@ -36,13 +36,15 @@ hipError_t launch_stream_pair(bool reservoir, bool has_v, const StepArgs<R>& a, 
     return has_v ? launch_pair_v<R, W, false, true>(a, s) : launch_pair_v<R, W, false, false>(a, s);
 }
 
-// with the coherent drive (one column per lane)
+// with the coherent drive (one column per lane; complex128 without a potential)
 template <typename R>
 hipError_t launch_stream_pair_drive(bool reservoir, bool has_v, const StepArgs<R>& a, hipStream_t s)
 {
-    if (reservoir)
-        return has_v ? launch_pair_v<R, 1, true, true, true>(a, s) : launch_pair_v<R, 1, true, false, true>(a, s);
-    return has_v ? launch_pair_v<R, 1, false, true, true>(a, s) : launch_pair_v<R, 1, false, false, true>(a, s);
+    if constexpr (sizeof(R) == 4) {
+        if (has_v) return reservoir ? launch_pair_v<R, 1, true, true, true>(a, s) : launch_pair_v<R, 1, false, true, true>(a, s);
+    }
+    if (has_v) return hipErrorInvalidValue;
+    return reservoir ? launch_pair_v<R, 1, true, false, true>(a, s) : launch_pair_v<R, 1, false, false, true>(a, s);
 }
 
 }  // namespace phx

@@ -123,8 +123,8 @@ __device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int str
     // Ghost columns and rows stay 0 in every stage: their inputs read as 0, so the stage
     // argument p0 + h f is 0 there when the step h is taken as 0 (the lane's h values,
     // and per row a uniform choice between them and 0).
-    const R kh2 = gcol ? R(0) : a.half_dt;
-    const R kh = gcol ? R(0) : a.dt;
+    R kh2 = gcol ? R(0) : a.half_dt;
+    R kh = gcol ? R(0) : a.dt;
     const int b0 = band * B;
     const R kdiag = R(2) * (c.ax + c.ay);
     const R bxyd = dir > 0 ? c.bxy : -c.bxy;  // uniform over the wave
@@ -268,6 +268,10 @@ __device__ __forceinline__ void stream_band_spinor(const StepArgs<R>& a, int str
             const int j = start + dir * (base + u);
             fetch(slot<K>(u, -PF), base + u + PF < npos);
             arrive(slot<K>(u, 0));
+            if constexpr (sizeof(R) == 8 && RES) {
+                park(kh);
+                park(kh2);
+            }
 #pragma unroll
             for (int s = 1; s <= 4; ++s) {
                 if (FIRST && u < 2 * s) continue;

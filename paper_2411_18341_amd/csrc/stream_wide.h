@@ -18,6 +18,18 @@ __device__ __forceinline__ void keep_here(double& v) { asm volatile("" : "+v"(v)
 __device__ __forceinline__ void keep_here(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 __device__ __forceinline__ void keep_here(double2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
 
+// Moves a value that is constant over the walk to accumulation registers, where it stays to
+// its next use.  The walks with one wave per SIMD have room there; left to itself the
+// compiler keeps two or three such values in scratch memory and reads them at every position
+// (driven complex128 pairs with zero boundaries, 2048^2: 86 us per step, parked 54).
+__device__ __forceinline__ void park(double& v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    int lo = (int)b, hi = (int)(b >> 32);
+    asm volatile("" : "+a"(lo), "+a"(hi));
+    v = __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
 __device__ __forceinline__ wf4 wload4(__amdgpu_buffer_rsrc_t r, int voff, int soff)
 {
     return __builtin_bit_cast(wf4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));

@@ -36,6 +36,10 @@ def test_scratch_check_reads_the_remarks():
     assert build._scratch_kernels("") == []
 
 
+def test_scratch_of_a_few_bytes_is_reported():
+    assert build._scratch_kernels(REMARKS.replace("288", "4")) == [("_ZN3phx24rk4_stream_spinor_kernelIfLb1EEEvv", 4)]
+
+
 ASM = """\
 _Z1kv:                                  ; @_Z1kv
 ; %bb.0:
