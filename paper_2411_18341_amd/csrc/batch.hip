@@ -109,7 +109,8 @@ static int batch_step_band(int ny, int cap)
 // Tall bands save halo rows, but the last of them end late: up to 56 rows (256 driven grids
 // of 128^2 to 1024^2, four steps: 1264 us with bands of up to 44 rows, 1270 with 68, 1304 with 80, 1346
 // with 104; 2068 us with one step per launch), fewer where the device would not be full.
-static void batch_pair_plan(bool c64, int nx, int ny, int cap, int* w, int* strips, int* band)
+// `two`: two columns per lane may be taken (complex64).
+static void batch_pair_plan(bool c64, bool two, int nx, int ny, int cap, int* w, int* strips, int* band)
 {
     double best = 0.0;
     auto consider = [&](int k, int b) {
@@ -122,7 +123,7 @@ static void batch_pair_plan(bool c64, int nx, int ny, int cap, int* w, int* stri
             *band = b;
         }
     };
-    for (int k = 1; k <= (c64 && nx % 2 == 0 ? 2 : 1); ++k) {
+    for (int k = 1; k <= (two && nx % 2 == 0 ? 2 : 1); ++k) {
         const int words = c64 ? k : 2, bands = (ny + cap - 1) / cap;
         if (kPairStep[words] == 4)
             consider(k, pair_band(words, (ny + bands - 1) / bands));
@@ -306,7 +307,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     std::vector<BatchInst<R>> table(d->count);
     int tile0 = 0;
     std::vector<int> block_inst;
-    bool ghosts = false, noisy = false;
+    bool ghosts = false, noisy = false;  // some instance's
     // the streaming forms need every instance's state under 2 GiB (32-bit buffer
     // offsets) and one y boundary rule for all instances
     bool use_stream = true, all_zero_y = true, all_periodic_y = true;
@@ -317,9 +318,30 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     // tallest bands of the walks: the candidates that give the shortest list; the search ends
     // at once where tall bands already make kFullLists waves per SIMD (45 us of host time for
     // 256 instances), and a walk that the call does not use is not planned
-    bool any_noise = false;
-    for (int k = 0; k < d->n_params; ++k) any_noise = any_noise || d->params[k].noise > 0.0;
-    const bool plan_pairs = !any_noise && pair_launches(n) > 0, plan_steps = any_noise || 2 * pair_launches(n) < n;
+    for (int k = 0; k < d->count; ++k) {
+        const phx_instance& I = d->instances[k];
+        const phx_config& c = d->params[I.param_index];
+        use_stream = use_stream && (double)I.nx * I.ny * 2.0 * sizeof(R) < 2147483648.0 - 256.0;
+        all_zero_y = all_zero_y && c.bc_y == PHX_BC_ZERO;
+        all_periodic_y = all_periodic_y && c.bc_y == PHX_BC_PERIODIC;
+        ghosts = ghosts || c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
+        noisy = noisy || c.noise > 0.0;
+    }
+    use_stream = use_stream && (all_zero_y || all_periodic_y);
+    // Pairs of steps where they are built.  Without the reservoir complex128 pairs are still
+    // the slower ones on grids whose halos they enlarge too much (64 lanes store 48 columns
+    // instead of 56): a position of the pair's walk takes 1.45 times one of the one-step walk,
+    // 1.65 times with a potential, so pairs run where their list has so many fewer positions
+    // than two of the other (us per step, one / two steps per launch: 2 x 2048^2 48.6 / 45.9,
+    // 256 x 200^2 73.6 / 72.3 and with zero boundaries 67.2 / 73.8; with a potential 58.7 /
+    // 54.9 and 76.5 / 88.7).
+    const bool f64 = sizeof(R) == 8, hasv = d->V != nullptr;
+    const bool two = !f64 && batch_pair_built(2, false, res != 0, hasv, ghosts, all_zero_y);
+    const bool plan_pairs = use_stream && !noisy && pair_launches(n) > 0 &&
+                            batch_pair_built(f64 ? 2 : 1, f64, res != 0, hasv, ghosts, all_zero_y);
+    const bool weigh = plan_pairs && f64 && !res;
+    const bool plan_steps = !plan_pairs || weigh || 2 * pair_launches(n) < n;
+    double s_work = 0.0, p_work = 0.0;  // positions of all items
     const int64_t full = (int64_t)kFullLists * 4 * cus;
     int s_cap = 64, p_cap = 56;
     double s_best = 0.0, p_best = 0.0;
@@ -342,7 +364,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         int tallest = 0;
         for (int k = 0; k < d->count; ++k) {
             int w, strips, band;
-            batch_pair_plan(sizeof(R) == 4, d->instances[k].nx, d->instances[k].ny, cap, &w, &strips, &band);
+            batch_pair_plan(sizeof(R) == 4, two, d->instances[k].nx, d->instances[k].ny, cap, &w, &strips, &band);
             waves += (int64_t)strips * ((d->instances[k].ny + band - 1) / band);
             tallest = std::max(tallest, band);
         }
@@ -376,27 +398,27 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         const int sw = sizeof(R) == 4 && I.nx % 2 == 0 ? 2 : 1;
         b.s_strips = (I.nx + step_cols(sw) - 1) / step_cols(sw);
         b.s_band = batch_step_band(I.ny, s_cap);
-        int w;
-        batch_pair_plan(sizeof(R) == 4, I.nx, I.ny, p_cap, &w, &b.p_strips, &b.p_band);
+        int w = 1;
+        b.p_strips = b.p_band = 1;
+        if (plan_pairs) batch_pair_plan(sizeof(R) == 4, two, I.nx, I.ny, p_cap, &w, &b.p_strips, &b.p_band);
         for (int l = 0; l < 2; ++l) {
             b.s_tile0[l] = (int)std::min<int64_t>(s_tile0[l], INT32_MAX);
             b.p_tile0[l] = (int)std::min<int64_t>(p_tile0[l], INT32_MAX);
         }
-        s_tile0[sw - 1] += (int64_t)b.s_strips * ((I.ny + b.s_band - 1) / b.s_band);
-        p_tile0[w - 1] += (int64_t)b.p_strips * ((I.ny + b.p_band - 1) / b.p_band);
-        use_stream = use_stream && (double)I.nx * I.ny * 2.0 * sizeof(R) < 2147483648.0 - 256.0;
-        all_zero_y = all_zero_y && c.bc_y == PHX_BC_ZERO;
-        all_periodic_y = all_periodic_y && c.bc_y == PHX_BC_PERIODIC;
-        ghosts = ghosts || c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
+        const int64_t s_items = (int64_t)b.s_strips * ((I.ny + b.s_band - 1) / b.s_band);
+        const int64_t p_items = (int64_t)b.p_strips * ((I.ny + b.p_band - 1) / b.p_band);
+        s_tile0[sw - 1] += s_items;
+        p_tile0[w - 1] += p_items;
+        s_work += (double)s_items * (b.s_band + 4);
+        p_work += (double)p_items * (b.p_band + 7);
         const double scale = c.noise * c.dt / (4.0 * c.dx * c.dy);  // as the single-grid pass forms it
         b.noise_a = (R)(scale * c.R);
         b.noise_b = (R)(scale * c.gamma_c);
         b.key0 = (uint32_t)I.seed;
         b.key1 = (uint32_t)(I.seed >> 32);
-        noisy = noisy || c.noise > 0.0;
     }
     const int total = tile0;
-    use_stream = use_stream && (all_zero_y || all_periodic_y) && s_tile0[0] + s_tile0[1] < INT32_MAX;
+    use_stream = use_stream && s_tile0[0] + s_tile0[1] < INT32_MAX;
     // noise pass over the instances whose step does not draw the increments itself
     for (int k = 0; noisy && k < d->count; ++k) {
         const phx_instance& I = d->instances[k];
@@ -447,7 +469,8 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     int cur = 0;
     // pairs of steps per launch where no increment is drawn in between; then an odd n >= 3
     // ends in the caller's arrays without a copy
-    int64_t pairs = use_stream && !noisy && p_tile0[0] + p_tile0[1] < INT32_MAX ? pair_launches(n) : 0;
+    const bool use_pairs = plan_pairs && (!weigh || p_work <= (hasv ? 0.605 : 0.69) * 2.0 * s_work);
+    int64_t pairs = use_pairs && use_stream && p_tile0[0] + p_tile0[1] < INT32_MAX ? pair_launches(n) : 0;
     if ((n & 1) && pairs == 0) {
         e = hipMemcpyAsync(S[1], S[0], (size_t)d->total_cells * 2 * rs, hipMemcpyDeviceToDevice, stream);
         if (e == hipSuccess && res)

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "phx_kernels.h"
+#include "runtime.h"
 
 namespace phx {
 
@@ -38,6 +39,16 @@ struct BatchState {
 struct BatchForm {
     bool res, hasv, ghosts, yzero;  // yzero: every instance has a zero y boundary, else none
 };
+
+// Variants whose pairs of steps are built (and run, see batch_run); words as in pair_pays.
+// In complex128 a potential leaves registers for one wave per SIMD with the reservoir or a
+// zero y boundary, and the pairs are slower than single steps: us per step, one / two steps
+// per launch, 256 grids of 200^2: with the reservoir 138 / 179, zero boundaries 126 / 199,
+// without the reservoir and zero in y 73 / 99.
+constexpr bool batch_pair_built(int words, bool f64, bool res, bool hasv, bool ghosts, bool yzero)
+{
+    return f64 ? !(hasv && (res || yzero)) : pair_pays(words, res, hasv, ghosts);
+}
 
 // One step (batch_walk.h) or two (batch_pair.h) over all instances in one launch: total1
 // items with one column per lane, total2 with two.  FORMS: 1, 2, or 3 where both occur.

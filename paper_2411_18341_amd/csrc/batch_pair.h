@@ -63,17 +63,22 @@ void batch_stream_pair_kernel(const BatchInst<R>* __restrict__ inst, int count, 
 }
 
 template <typename R, int FORMS, bool RES, bool HASV, bool GHOSTS, bool YZERO>
-static void launch_batch_pair_t(int total1, int total2, const BatchInst<R>* inst, int count, const BatchState<R>& b,
+static hipError_t launch_batch_pair_t(int total1, int total2, const BatchInst<R>* inst, int count, const BatchState<R>& b,
                                 bool check, hipStream_t s)
 {
     constexpr int W = FORMS == 1 ? 1 : 2;
-    constexpr int WPE = pair_waves_per_simd(W * (int)sizeof(R) / 4, RES, HASV, GHOSTS, false);
-    if (check)
-        batch_stream_pair_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, true, WPE>
-            <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2);
-    else
-        batch_stream_pair_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, false, WPE>
-            <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2);
+    constexpr int words = W * (int)sizeof(R) / 4;
+    constexpr int WPE = pair_waves_per_simd(words, RES, HASV, GHOSTS, false);
+    if constexpr (batch_pair_built(words, sizeof(R) == 8, RES, HASV, GHOSTS, YZERO)) {
+        if (check)
+            batch_stream_pair_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, true, WPE>
+                <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2);
+        else
+            batch_stream_pair_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, false, WPE>
+                <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename R, int FORMS>
@@ -83,18 +88,18 @@ hipError_t launch_batch_pair_forms(const BatchForm& f, int total1, int total2, c
 #define PHX_BP(RS, HV) \
     if (f.res == RS && f.hasv == HV) { \
         if (f.yzero) \
-            launch_batch_pair_t<R, FORMS, RS, HV, true, true>(total1, total2, inst, count, b, check, s); \
+            return launch_batch_pair_t<R, FORMS, RS, HV, true, true>(total1, total2, inst, count, b, check, s); \
         else if (f.ghosts) \
-            launch_batch_pair_t<R, FORMS, RS, HV, true, false>(total1, total2, inst, count, b, check, s); \
+            return launch_batch_pair_t<R, FORMS, RS, HV, true, false>(total1, total2, inst, count, b, check, s); \
         else \
-            launch_batch_pair_t<R, FORMS, RS, HV, false, false>(total1, total2, inst, count, b, check, s); \
+            return launch_batch_pair_t<R, FORMS, RS, HV, false, false>(total1, total2, inst, count, b, check, s); \
     }
     PHX_BP(true, true)
     PHX_BP(true, false)
     PHX_BP(false, true)
     PHX_BP(false, false)
 #undef PHX_BP
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 }  // namespace phx

@@ -188,6 +188,15 @@ inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int
 int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v);
 StepShapeId default_step_shape(const phx_config& c);
 int pair_strips(int nx, int w);
+// With the reservoir, a potential and a zero boundary, pairs of two complex64 columns or one
+// complex128 column per lane (words = 2) run one wave per SIMD and are slower than single
+// steps at every size: us per step, one / two steps per launch, complex64 10.7 / 15.2 at
+// 1024^2, 55 / 62 at 3000^2, 105 / 108 at 4096^2; complex128 16.4 / 21.4, 118 / 115 and
+// 211 / 226.  Pairs with one complex64 column per lane (words = 1) take 11.9, 55 and 86.
+constexpr bool pair_pays(int words, bool res, bool has_v, bool ghosts)
+{
+    return words == 1 || !(res && has_v && ghosts);
+}
 int64_t pair_launches(int64_t n);  // two-step launches among n steps
 // Columns per lane, strips and band height of the spinor walk (stream_spinor.h).
 struct SpinorPlan {

@@ -233,13 +233,21 @@ int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 // at 1024^2, 36.0 / 29.5 at 2048^2, 141 / 94 at 4096^2; complex128 20.2 / 31.6 at 1024^2, 57.9
 // / 44.6 at 2048^2): the profile's ring leaves registers for few waves.  In complex128 with
 // a potential as well they never do (2048^2, us per step, one / two steps per launch: 62 /
-// 68 with the reservoir, 44 / 45 to 49 without).
+// 68 with the reservoir, 44 / 45 to 49 without).  Undriven complex128 with a potential: from
+// 2^23 cells, where HBM bounds the single steps (without the reservoir 20.1 / 24.3 at 1536^2,
+// 26.4 / 28.0 at 2048^2, 62.3 / 59.1 at 3000^2, 127 / 105 at 4096^2; with it 28.8 / 31.8,
+// 52.0 / 52.3, 120 / 106, 216 / 209); see also pair_pays.
 int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v)
 {
     if (c.components != 1 || c.imag_time || c.noise > 0.0) return 0;
-    if (c.drive && ((int64_t)c.nx * c.ny < ((int64_t)1 << 21) || (c.precision == PHX_C128 && has_v))) return 0;
-    if (sh.waves == 2 && sh.rows == 0) return 2;
-    return sh.waves == 1 && sh.rows == 64 ? 1 : 0;
+    const int64_t cells = (int64_t)c.nx * c.ny;
+    const bool c64 = c.precision == PHX_C64, ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
+    if (c.drive && (cells < ((int64_t)1 << 21) || (!c64 && has_v))) return 0;
+    if (!c64 && has_v && cells < ((int64_t)1 << 23)) return 0;
+    const bool two = sh.waves == 2 && sh.rows == 0;
+    if (!two && !(sh.waves == 1 && sh.rows == 64)) return 0;
+    if (pair_pays(two || !c64 ? 2 : 1, c.reservoir != 0, has_v, ghosts)) return two ? 2 : 1;
+    return c64 ? 1 : 0;
 }
 
 // Shape used when the caller names none and does not tune: the region form on grids that

@@ -20,12 +20,16 @@ static void launch_pair_t(const StepArgs<R>& a, hipStream_t s)
 template <typename R, int W, bool RES, bool HASV, bool DRIVE = false>
 static hipError_t launch_pair_v(const StepArgs<R>& a, hipStream_t s)
 {
-    if (a.bcy == PHX_BC_ZERO)
-        launch_pair_t<R, W, RES, HASV, true, true, DRIVE>(a, s);
-    else if (a.bcx == PHX_BC_ZERO)
-        launch_pair_t<R, W, RES, HASV, true, false, DRIVE>(a, s);
-    else
+    if (a.bcy == PHX_BC_PERIODIC && a.bcx == PHX_BC_PERIODIC) {
         launch_pair_t<R, W, RES, HASV, false, false, DRIVE>(a, s);
+    } else if constexpr (pair_pays(W * (int)sizeof(R) / 4, RES, HASV, true)) {
+        if (a.bcy == PHX_BC_ZERO)
+            launch_pair_t<R, W, RES, HASV, true, true, DRIVE>(a, s);
+        else
+            launch_pair_t<R, W, RES, HASV, true, false, DRIVE>(a, s);
+    } else {
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

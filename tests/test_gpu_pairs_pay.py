@@ -61,3 +61,64 @@ def test_driven_double_bitwise(bc):
     kw = dict(drive=True, calls=(4, 3))
     assert same(end_state("driven", 1447, 1450, bc, C128, (1, 40), **kw),
                 end_state("driven", 1447, 1450, bc, C128, (1, 64), **kw))
+
+
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1), (0, 1), (1, 0)])
+@pytest.mark.parametrize("reservoir", [False, True])
+@pytest.mark.parametrize("precision,nx", [(C64, 3000), (C64, 2047), (C128, 1536)])
+def test_with_a_potential(precision, nx, reservoir, bc):
+    assert check(solver(nx, nx, precision, bc, reservoir, True)) == (precision == C64)
+
+
+@pytest.mark.parametrize("bc", [(1, 1), (0, 1), (1, 0)])
+def test_zero_boundaries_and_a_potential_bitwise(bc):
+    """The wide shape's pairs, which take one column per lane here."""
+    for nx, ny in ((114, 21), (2, 7), (128, 64)):
+        kw = dict(calls=(4, 3))
+        assert same(end_state("driven_v", nx, ny, bc, C64, (8, 4), **kw), end_state("driven_v", nx, ny, bc, C64, (2, 0), **kw))
+
+
+@pytest.mark.parametrize("reservoir,bc", [(False, (0, 0)), (False, (1, 1)), (True, (0, 0))])
+def test_large_double_with_a_potential(reservoir, bc):
+    """From 2^23 cells complex128 pairs run with a potential: the same bits as single steps of
+    bands of 40 rows on a ragged grid."""
+    import torch
+    states = []
+    for tile in ((1, 64), (1, 40)):
+        s = solver(4097, 2049, C128, bc, reservoir, True, tile=tile)
+        assert ("rk4_step_pair" in launch_us(s, 4)) == (tile == (1, 64))
+        s.step(3)
+        states.append((s.psi.clone(), s.n))
+        s.close()
+    assert torch.equal(states[0][0], states[1][0])
+    assert not reservoir or torch.equal(states[0][1], states[1][1])
+
+
+def batch_us(grids, precision, bc, reservoir, has_v, steps):
+    import time
+    import torch
+    terms = dict(g_r=0.02, R=0.01, gamma_c=0.15, gamma_r=0.225) if reservoir else {}
+    cfg = phx.make_config(8, 8, 0.2, bc_x=bc[0], bc_y=bc[1], reservoir=reservoir, g=0.01, dt=0.02, **terms)
+    b = phx.Batch(grids, [cfg], precision=precision, with_v=has_v)
+    b.psi.normal_().mul_(0.1)
+    best = float("inf")
+    for _ in range(12):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        b.step(steps)
+        torch.cuda.synchronize()
+        best = min(best, 1e6 * (time.perf_counter() - t))
+    return best
+
+
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1), (0, 1), (1, 0)])
+@pytest.mark.parametrize("reservoir", [False, True])
+@pytest.mark.parametrize("precision,grids", [(C128, [(200, 200)] * 256), (C64, [(2048, 2048)] * 2),
+                                             (C64, [(200, 200)] * 128 + [(201, 200)] * 128)])
+def test_batches(precision, grids, reservoir, bc):
+    """16 batched steps with a potential take no longer than eight calls of two (which run
+    single steps)."""
+    two = batch_us(grids, precision, bc, reservoir, True, 2)
+    sixteen = batch_us(grids, precision, bc, reservoir, True, 16)
+    print(f"16 steps {sixteen:.0f} us, 8 calls of two {8 * two:.0f}")
+    assert sixteen <= 8 * two
