@@ -93,8 +93,8 @@ typedef struct phx_config {
                                one wave per band (2 x 0 then takes two steps per launch where
                                neither noise nor imaginary time comes between them); 1 x 64
                                does so with one column per lane (with the drive from 2^21
-                               cells on), and lets the library pick the band height, also
-                               for the spinor; streaming forms need a state under 2 GiB;
+                               cells on); 1 x 64, 88 and 112 let the library pick the band
+                               height, 1 x 64 also for the spinor; streaming forms need a state under 2 GiB;
                                0 with tile_wx 0 = automatic                                 */
     int32_t graph_steps;    /* RK4 steps per captured hipGraph chunk replayed by phx_step:
                                0 = default (64), < 0 = launch every kernel directly        */

@@ -56,7 +56,7 @@ static phx_status tune_step(phx_handle* h, int reps, phx_tune_result* out)
             best = sh;
         }
     }
-    h->step_shape = best;
+    h->step_shape = h->lone_shape = best;
     h->graph_dirty = true;
     *out = phx_tune_result{PHX_KERNEL_STEP, best.waves, best.rows, timed, best_us, before_us};
     return PHX_OK;

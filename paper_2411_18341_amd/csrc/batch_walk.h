@@ -69,7 +69,7 @@ template <typename R, int FORMS, bool RES, bool HASV, bool GHOSTS, bool YZERO, b
 static void launch_batch_step_t(int total1, int total2, const BatchInst<R>* inst, int count, const BatchState<R>& b,
                                 uint64_t step, bool check, hipStream_t s)
 {
-    constexpr int WPE = step_waves_per_simd(FORMS == 1 ? 1 : 2, sizeof(R) == 8, RES, false, NOISE);
+    constexpr int WPE = step_waves_per_simd(FORMS == 1 ? 1 : 2, sizeof(R) == 8, RES, false);
     if (check)
         batch_stream_kernel<R, FORMS, RES, HASV, GHOSTS, YZERO, true, NOISE, WPE>
             <<<total1 + total2, 64, 0, s>>>(inst, count, b, total2, step);

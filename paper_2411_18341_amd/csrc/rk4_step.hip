@@ -201,18 +201,17 @@ template hipError_t rk4_step_trial<double>(phx_handle*, const StepShapeId&, int,
 // steps would: the n - pairs launches are even in number exactly when n is.
 int64_t pair_launches(int64_t n) { return n & 1 ? (n >= 3 ? 2 * ((n + 1) / 4) - 1 : 0) : 2 * (n / 4); }
 
-// Enqueues n whole steps on stream s, alternating between the caller's arrays
+// Enqueues n whole steps with shape sh on stream s, alternating between the caller's arrays
 // (buffer 0) and the workspace copy (buffer 1); h->step_parity is the buffer that
 // holds the state before the first of them.  With the two-step form an odd n >= 3 ends
 // in the buffer it began in, like an even n.
 template <typename R>
-phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
+phx_status rk4_fused_launches(phx_handle* h, const StepShapeId& sh, int64_t n, hipStream_t s)
 {
     const phx_config& c = h->cfg;
     void* S[2] = {h->f.psi, h->ws + h->L.alt};
     void* SN[2] = {h->f.n, c.reservoir ? h->ws + h->L.alt_n : nullptr};
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
-    const StepShapeId sh = h->step_shape;
     const bool fused_noise = c.noise > 0.0 && noise_in_step(c, sh);
     const int columns = pair_columns(c, sh, hv);
     int64_t pairs = columns ? pair_launches(n) : 0;
@@ -254,8 +253,8 @@ phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s)
     return PHX_OK;
 }
 
-template phx_status rk4_fused_launches<float>(phx_handle*, int64_t, hipStream_t);
-template phx_status rk4_fused_launches<double>(phx_handle*, int64_t, hipStream_t);
+template phx_status rk4_fused_launches<float>(phx_handle*, const StepShapeId&, int64_t, hipStream_t);
+template phx_status rk4_fused_launches<double>(phx_handle*, const StepShapeId&, int64_t, hipStream_t);
 
 // Partials that the waves of the next step sum themselves (0: a pass forms the scale).
 int imag_self_sum(const phx_handle* h)
@@ -286,7 +285,7 @@ phx_status rk4_fused_steps(phx_handle* h, int64_t n)
                                            h->stream) != hipSuccess))
             return fail(PHX_EHIP, "state copy failed");
         h->step_parity = 1;
-        phx_status st = rk4_fused_launches<R>(h, 1, h->stream);
+        phx_status st = rk4_fused_launches<R>(h, n == 1 ? h->lone_shape : h->step_shape, 1, h->stream);
         if (st != PHX_OK) return st;
         --n;
     }

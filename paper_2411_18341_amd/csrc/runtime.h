@@ -76,7 +76,8 @@ struct phx_handle {
     void* other;
     void* cur_n;
     void* other_n;
-    phx::StepShapeId step_shape;  // whole-step RK4 region shape in use
+    phx::StepShapeId step_shape;  // whole-step RK4 shape in use
+    phx::StepShapeId lone_shape;  // the shape for a call of one step
     int cus;                      // compute units of the handle's device
     phx::TilePlan stage_tiles;    // stage-fused RK4 tile plan in use
     int step_parity;              // whole-step family: buffer holding the state (0 = caller's)
@@ -128,7 +129,7 @@ phx_status create_rk45(phx_handle* h);
 template <typename R> struct DpWalkArgs;
 template <typename R, int COMPS> hipError_t launch_dp_walk(bool res, const DpWalkArgs<R>& a, hipStream_t s);
 template <typename R> phx_status rk4_fused_steps(phx_handle* h, int64_t n);
-template <typename R> phx_status rk4_fused_launches(phx_handle* h, int64_t n, hipStream_t s);
+template <typename R> phx_status rk4_fused_launches(phx_handle* h, const StepShapeId& sh, int64_t n, hipStream_t s);
 template <typename R> phx_status rk4_stage_launches(phx_handle* h, int64_t n, hipStream_t s);
 int graph_chunk(const phx_config& c);
 template <typename R> phx_status rk4_run_graph(phx_handle* h, int64_t n);
@@ -187,6 +188,7 @@ inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int
 // strips and the band height.
 int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v);
 StepShapeId default_step_shape(const phx_config& c);
+StepShapeId default_lone_shape(const phx_config& c);
 int pair_strips(int nx, int w);
 // With the reservoir, a potential and a zero boundary, pairs of two complex64 columns or one
 // complex128 column per lane (words = 2) run one wave per SIMD and are slower than single

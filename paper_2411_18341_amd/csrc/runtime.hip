@@ -196,19 +196,24 @@ bool noise_in_step(const phx_config& c, const StepShapeId& sh)
            c.nx % 2 == 0;
 }
 
-// The height is the caller's, or chosen here (64 with one column per lane, 0 with two) from
-// the multiples of 8 rows.  A single wave on a SIMD waits for the results of its own chain
-// half of the time (four short stages per position), hence the low rates (imaginary time,
-// 1024^2: 13.7 us per step with one wave per SIMD and bands of 24 rows, 12.3 with three and 8).
+// The height is the caller's, or chosen here (64, 88 and 112 with one column per lane, 0 with
+// two) from the multiples of 8 rows.  A single wave on a SIMD waits for the results of its own
+// chain half of the time (four short stages per position), hence the low rates (imaginary time,
+// 1024^2: 13.7 us per step with one wave per SIMD and bands of 24 rows, 12.3 with three and 8);
+// the generator of the noise fills much of that time (us per position of the busiest SIMD's
+// waves: 0.78 with one, 0.60 with two, 0.585 with three; 1400^2: 23.8 us per step with bands
+// of 16 rows, which the rates without the noise pick, 21.0 with 8).  Bands as tall as 88 rows
+// leave one wave per SIMD (2048^2 with the noise: 54.6 us per step, 39.4 with the height
+// chosen here).
 StepPlan step_plan(const phx_config& c, const StepShapeId& sh, int cus)
 {
     const int w = wide_shape(sh.waves) ? 2 : 1;
     const int strips = (c.nx + step_cols(w) - 1) / step_cols(w);
-    if (sh.rows > 0 && !(sh.waves == 1 && sh.rows == 64)) return StepPlan{strips, sh.rows};
+    if (sh.rows > 0 && !(sh.waves == 1 && sh.rows >= 64)) return StepPlan{strips, sh.rows};
     const bool noise = c.noise > 0.0 && noise_in_step(c, sh);
     return StepPlan{strips, band_fill(strips, c.ny, 8, 4, 8, 8, cus,
-                                      step_waves_per_simd(w, c.precision == PHX_C128, c.reservoir != 0, c.drive != 0, noise),
-                                      0.5, 0.85).rows};
+                                      step_waves_per_simd(w, c.precision == PHX_C128, c.reservoir != 0, c.drive != 0),
+                                      noise ? 0.76 : 0.5, noise ? 0.97 : 0.85).rows};
 }
 
 int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
@@ -284,6 +289,18 @@ StepShapeId default_step_shape(const phx_config& c)
         pick = one;
     }
     return step_shape_fits(c, pick.waves) ? pick : shapes[0];
+}
+
+// The same for a call of one step.  With the noise up to 9 2^18 cells the region form and the
+// pass: us per call of one / two steps 33 / 41 at 1024^2 (the wide form 35 / 37), 40 / 54 at
+// 1400^2 (43 / 50), 44 / 58 at 1500^2 (45 / 52); 51 / 69 against 51 / 59 at 1700^2.
+StepShapeId default_lone_shape(const phx_config& c)
+{
+    const StepShapeId sh = default_step_shape(c);
+    if (!(c.noise > 0.0) || !wide_shape(sh.waves) || (int64_t)c.nx * c.ny >= ((int64_t)9 << 18)) return sh;
+    const StepShapeId* shapes;
+    step_shapes(c.precision, &shapes);
+    return shapes[0];
 }
 
 bool step_shape_allowed(const phx_config& c, const StepShapeId& sh)
@@ -447,7 +464,9 @@ phx_status phx_create(const phx_config* cfg, const phx_fields* f, void* stream,
     h->stage_tiles = L.tiles;
     {
         h->step_shape = default_step_shape(*cfg);
-        if (cfg->tile_wx != 0 && L.family == PHX_KERNEL_STEP) h->step_shape = StepShapeId{cfg->tile_wx, cfg->tile_rows};
+        h->lone_shape = default_lone_shape(*cfg);
+        if (cfg->tile_wx != 0 && L.family == PHX_KERNEL_STEP)
+            h->step_shape = h->lone_shape = StepShapeId{cfg->tile_wx, cfg->tile_rows};
     }
     if (cfg->integrator == PHX_RK45) {
         s = create_rk45(h);
@@ -612,7 +631,7 @@ static phx_status rk4_run(phx_handle* h, int64_t n)
 {
     const bool step = h->L.family == PHX_KERNEL_STEP;
     auto direct = [&](hipStream_t s, int64_t k) {
-        return step ? rk4_fused_launches<R>(h, k, s) : rk4_stage_launches<R>(h, k, s);
+        return step ? rk4_fused_launches<R>(h, h->step_shape, k, s) : rk4_stage_launches<R>(h, k, s);
     };
     const int G = graph_chunk(h->cfg);
     if (h->timing || G == 0 || n < G) return direct(h->stream, n);

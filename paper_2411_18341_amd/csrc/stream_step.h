@@ -46,10 +46,10 @@ namespace phx {
 constexpr int step_cols(int w) { return 64 * w - 8; }  // output columns per strip
 
 // Waves per SIMD that the registers allow without scratch memory.
-constexpr int step_waves_per_simd(int w, bool f64, bool res, bool drive, bool noise)
+constexpr int step_waves_per_simd(int w, bool f64, bool res, bool drive)
 {
     if (w == 1 && !f64) return drive ? 4 : 5;
-    return drive || (res && (noise || f64)) ? 2 : 3;
+    return drive || (res && f64) ? 2 : 3;
 }
 
 // One band of `B` rows of strip `strip`; `finish(bad, norm)` gets whether a stored value
@@ -266,6 +266,16 @@ __device__ __forceinline__ void stream_band_step(const StepArgs<R>& a, int strip
                     // goes to the empty descriptor, whose stores are dropped.
                     const bool st = r >= b0 && r < b0 + B && r < a.ny;  // uniform
                     const int rr = st ? r : 0;
+                    if (CHECK) {  // (NOISE: and again where the increment is added; only there: 40 more VGPRs)
+                        R t = nf;   // stays 0 while the values are finite
+#pragma unroll
+                        for (int e = 0; e < W; ++e) {
+                            t = fma(y[e].x, R(0), t);
+                            t = fma(y[e].y, R(0), t);
+                            if (RES) t = fma(yn[e], R(0), t);
+                        }
+                        nf = st ? t : nf;
+                    }
                     if constexpr (NOISE) {
                         if (st && noisy) {
                             const uint32_t pair = (uint32_t)(r * a.nx + gi) >> 1;  // nx and gi even
@@ -275,6 +285,8 @@ __device__ __forceinline__ void stream_band_step(const StepArgs<R>& a, int strip
                             for (int e = 0; e < W; ++e)
                                 y[e] = noise::add_noise<R, RES>(y[e], RES ? yn[e] : R(0), a.noise_a, a.noise_b,
                                                                 x.x[2 * e], x.x[2 * e + 1]);
+#pragma unroll
+                            for (int e = 0; CHECK && e < W; ++e) nf = fma(y[e].y, R(0), fma(y[e].x, R(0), nf));
                         }
                     }
                     if constexpr (W == 2) {
@@ -288,16 +300,6 @@ __device__ __forceinline__ void stream_band_step(const StepArgs<R>& a, int strip
 #pragma unroll
                         for (int e = 0; e < W; ++e)
                             nrm += st && out_col ? (double)y[e].x * y[e].x + (double)y[e].y * y[e].y : 0.0;
-                    }
-                    if (CHECK) {
-                        R t = nf;  // stays 0 while the stored values are finite
-#pragma unroll
-                        for (int e = 0; e < W; ++e) {
-                            t = fma(y[e].x, R(0), t);
-                            t = fma(y[e].y, R(0), t);
-                            if (RES) t = fma(yn[e], R(0), t);
-                        }
-                        nf = st ? t : nf;
                     }
                 }
             }

@@ -34,7 +34,7 @@ void rk4_stream_step_kernel(const StepArgs<R> a)
 template <typename R, int W, bool RES, bool HASV, bool GHOSTS, bool YZERO, bool IMAG, bool DRIVE, bool NOISE>
 static void launch_step_walk_t(const StepArgs<R>& a, hipStream_t s)
 {
-    constexpr int WPE = step_waves_per_simd(W, sizeof(R) == 8, RES, DRIVE, NOISE);
+    constexpr int WPE = step_waves_per_simd(W, sizeof(R) == 8, RES, DRIVE);
     if (a.check)
         rk4_stream_step_kernel<R, W, RES, HASV, GHOSTS, YZERO, true, IMAG, DRIVE, NOISE, WPE><<<a.tiles, 64, 0, s>>>(a);
     else

@@ -13,7 +13,7 @@ from test_gpu_step_walk import end_state, same
 pytestmark = pytest.mark.gpu
 
 
-def solver(nx, ny, precision, bc, reservoir, has_v, drive=False, tile=(0, 0)):
+def solver(nx, ny, precision, bc, reservoir, has_v, drive=False, tile=(0, 0), **kw):
     import torch
     cdt, rdt = phx.torch_dtypes(precision)
     g = torch.Generator(device="cuda:0")
@@ -22,7 +22,7 @@ def solver(nx, ny, precision, bc, reservoir, has_v, drive=False, tile=(0, 0)):
     psi = torch.randn((1, ny, nx), generator=g, dtype=cdt, device="cuda:0")
     terms = dict(g_r=0.02, R=0.01, gamma_c=0.15, gamma_r=0.225) if reservoir else {}
     cfg = phx.make_config(nx, ny, 0.2, bc_x=bc[0], bc_y=bc[1], reservoir=reservoir, precision=precision, g=0.01,
-                          dt=0.02, drive=drive, drive_omega=1.3, tile_wx=tile[0], tile_rows=tile[1], **terms)
+                          dt=0.02, drive=drive, drive_omega=1.3, tile_wx=tile[0], tile_rows=tile[1], **terms, **kw)
     return phx.Solver(cfg, psi, real(1, ny, nx) if reservoir else None, real(ny, nx) if has_v else None,
                       real(1, ny, nx) if reservoir else None, E=0.01 * psi if drive else None)
 
