@@ -18,7 +18,7 @@ static phx_status time_launches(phx_handle* h, int reps, F launch, double* us)
         (void)hipEventDestroy(e0);
         return fail(PHX_EHIP, "hipEventCreate failed");
     }
-    hipError_t e = launch(0);  // warm-up
+    hipError_t e = launch(0);  // warm-up, and what the trials need
     if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
     for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch(r + 1);
     if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
@@ -30,6 +30,14 @@ static phx_status time_launches(phx_handle* h, int reps, F launch, double* us)
     if (e != hipSuccess) return fail(PHX_EHIP, "tuning launch failed: %s", hipGetErrorString(e));
     *us = 1e3 * ms / reps;
     return PHX_OK;
+}
+
+// The shape of the same launches that the tuner times: {1, 112} is {1, 88} (the height is
+// chosen per grid), {3, B} is {2, B}.
+StepShapeId run_as(const StepShapeId& sh)
+{
+    if (sh.waves == 1 && sh.rows == 112) return StepShapeId{1, 88};
+    return sh.waves == 3 ? StepShapeId{2, sh.rows} : sh;
 }
 
 template <typename R>
@@ -44,13 +52,18 @@ static phx_status tune_step(phx_handle* h, int reps, phx_tune_result* out)
     for (int k = 0; k < n; ++k) {
         const StepShapeId sh = shapes[k];
         if (!step_shape_allowed(h->cfg, sh)) continue;
+        if (run_as(sh) != sh) continue;
         ++timed;
         double us;
-        int steps = 1;  // of one launch
+        int steps = 1;  // of one trial
+        h->step_shape = sh;
         phx_status s = time_launches(h, reps, [&](int k) { return rk4_step_trial<R>(h, sh, k, &steps); }, &us);
-        if (s != PHX_OK) return s;
+        if (s != PHX_OK) {
+            h->step_shape = before;
+            return s;
+        }
         us /= steps;
-        if (sh.waves == before.waves && sh.rows == before.rows) before_us = us;
+        if (sh == run_as(before)) before_us = us;
         if (us < best_us) {
             best_us = us;
             best = sh;

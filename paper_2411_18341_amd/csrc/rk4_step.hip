@@ -45,12 +45,12 @@ static hipError_t launch_step_t(const StepArgs<R>& a, hipStream_t s)
 // A region of WAVES*ROWS rows yields WAVES*ROWS - 8 output rows; taller regions
 // recompute less halo, shorter ones need fewer registers per lane (more waves
 // per SIMD).  The first entry is the default; phx_autotune measures them all.
-// Shapes {1, B} are the streaming walk with one column per lane and bands of B rows (64: the
-// height is chosen per grid), {2, B} and {3, B} the walk with two columns per lane (complex64,
+// Shapes {1, B} are the streaming walk with one column per lane and bands of B rows (from 64
+// on the height is chosen per grid), {2, B} (and {3, B}, which runs as it) the walk with two columns per lane (complex64,
 // even widths), B = 0 choosing the height that fills the device in one wave of workgroups.
 static const StepShapeId kFloatShapes[] = {{8, 4}, {16, 4}, {8, 8}, {12, 4}, {12, 6}, {8, 6}, {4, 8}, {16, 6},
                                            {1, 40}, {1, 64}, {1, 88}, {1, 112},
-                                           {2, 0}, {3, 0}, {2, 40}, {2, 64}, {3, 64}, {3, 96}};
+                                           {2, 0}, {2, 40}, {2, 64}, {2, 96}};
 static const StepShapeId kDoubleShapes[] = {{8, 4}, {16, 2}, {8, 2}, {12, 4}, {4, 4}, {1, 40}, {1, 64}};
 
 int step_shapes(int precision, const StepShapeId** out)
@@ -168,17 +168,31 @@ static StepArgs<R> step_args(const phx_handle* h, const StepShapeId& sh, const v
     return a;
 }
 
-// Trial launch k of the tuner.  k = 0 steps the caller's state into the workspace
+// The noise arguments of a step that draws the increments itself; false if it does not.
+template <typename R>
+static bool set_noise_args(const phx_config& c, const StepShapeId& sh, const void* step_index, int64_t offset, StepArgs<R>& a)
+{
+    if (!(c.noise > 0.0) || !noise_in_step(c, sh)) return false;
+    a.noise_step = (const uint64_t*)step_index;
+    a.noise_offset = offset;
+    noise_coefs<R>(c, a.noise_a, a.noise_b, a.noise_k0, a.noise_k1);
+    return true;
+}
+
+// Trial k of the tuner with shape sh = h->step_shape: one launch and what a step takes beside
+// it (the phasors of the drive, the increments of the noise or their pass, the norm of
+// imaginary time or its pass).  k = 0 steps the caller's state into the workspace
 // copy; later trials alternate between the two workspace copies, so that each one
 // reads the state the previous one wrote, as real steps do (a launch that re-read one
 // unchanged input would find part of it in the Infinity Cache).  The caller's state
-// is never written.  *steps is the number of steps of the launch.
+// is never written.  *steps is the number of steps of the trial.
 template <typename R>
 hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* steps)
 {
-    const int pair = pair_columns(h->cfg, sh, h->f.V != nullptr);
+    const phx_config& c = h->cfg;
+    const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
+    const int pair = pair_columns(c, sh, hv);
     *steps = pair ? 2 : 1;
-    const bool res = h->cfg.reservoir != 0;
     char* A = h->ws + h->L.alt;
     char* An = res ? h->ws + h->L.alt_n : nullptr;
     char* B = h->ws + h->L.alt2;
@@ -190,8 +204,15 @@ hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* step
         a = step_args<R>(h, sh, A, An, B, Bn, 1, pair);
     else
         a = step_args<R>(h, sh, B, Bn, A, An, 0, pair);
-    if (pair) return launch_pair<R>(pair, res, h->f.V != nullptr, a, h->stream);
-    return launch_rk4_step<R>(res, h->f.V != nullptr, sh, a, h->stream);
+    hipError_t e = hipSuccess;
+    if (k == 0 && c.imag_time)  // the target, and partials that sum to it for this shape's waves
+        e = launch_imag_norm<R>(h, h->f.psi, 0, h->stream);
+    if (e == hipSuccess && c.drive) e = launch_drive_phasors<R>(h, 0, *steps, h->stream);
+    const bool fused_noise = set_noise_args<R>(c, sh, h->ws + h->L.noise, 0, a);
+    if (e == hipSuccess) e = pair ? launch_pair<R>(pair, res, hv, a, h->stream) : launch_rk4_step<R>(res, hv, sh, a, h->stream);
+    if (e == hipSuccess && c.imag_time && a.imag_count == 0) e = launch_imag_finish(h, a.imag_partials, a.tiles, h->stream);
+    if (e == hipSuccess && c.noise > 0.0 && !fused_noise) e = launch_noise<R>(h, a.psi_out, a.n_out, 0, h->stream);
+    return e;
 }
 
 template hipError_t rk4_step_trial<float>(phx_handle*, const StepShapeId&, int, int*);
@@ -212,7 +233,6 @@ phx_status rk4_fused_launches(phx_handle* h, const StepShapeId& sh, int64_t n, h
     void* S[2] = {h->f.psi, h->ws + h->L.alt};
     void* SN[2] = {h->f.n, c.reservoir ? h->ws + h->L.alt_n : nullptr};
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
-    const bool fused_noise = c.noise > 0.0 && noise_in_step(c, sh);
     const int columns = pair_columns(c, sh, hv);
     int64_t pairs = columns ? pair_launches(n) : 0;
     int cur = h->step_parity;
@@ -221,11 +241,7 @@ phx_status rk4_fused_launches(phx_handle* h, const StepShapeId& sh, int64_t n, h
         steps = pair ? 2 : 1;
         StepArgs<R> a = step_args<R>(h, sh, S[cur], SN[cur], S[cur ^ 1], SN[cur ^ 1], cur, pair ? columns : 0);
         a.check = k + steps == n;  // the wide forms test the last step of the run (values stay non-finite)
-        if (fused_noise) {
-            a.noise_step = (const uint64_t*)(h->ws + h->L.noise);
-            a.noise_offset = k;
-            noise_coefs<R>(c, a.noise_a, a.noise_b, a.noise_k0, a.noise_k1);
-        }
+        const bool fused_noise = set_noise_args<R>(c, sh, h->ws + h->L.noise, k, a);
         if (c.drive && launch_drive_phasors<R>(h, k, (int)steps, s) != hipSuccess)
             return fail(PHX_EHIP, "drive phasor launch failed");
         hipEvent_t t0 = nullptr;

@@ -14,6 +14,8 @@ namespace phx {
 struct StepShapeId {
     int waves, rows;
 };
+inline bool operator==(const StepShapeId& a, const StepShapeId& b) { return a.waves == b.waves && a.rows == b.rows; }
+inline bool operator!=(const StepShapeId& a, const StepShapeId& b) { return !(a == b); }
 
 struct TilePlan {
     TileShape ts;
