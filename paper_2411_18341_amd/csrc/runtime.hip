@@ -445,11 +445,19 @@ phx_status phx_create(const phx_config* cfg, const phx_fields* f, void* stream,
         else
             h->cus = 256;
     }
+    h->cur = f->psi;
+    h->stage_tiles = L.tiles;
+    {
+        h->step_shape = default_step_shape(*cfg);
+        h->lone_shape = default_lone_shape(*cfg);
+        if (cfg->tile_wx != 0 && L.family == PHX_KERNEL_STEP)
+            h->step_shape = h->lone_shape = StepShapeId{cfg->tile_wx, cfg->tile_rows};
+    }
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + L.flag, 0, 256, h->stream);
     if (e == hipSuccess && uses_step_index(*cfg)) e = set_noise_step(h, 0, h->stream);
     if (e == hipSuccess && cfg->drive && cfg->integrator == PHX_RK4)  // valid phasors before any launch
-        e = cfg->precision == PHX_C64 ? launch_drive_phasors<float>(h, 0, 1, h->stream)
-                                      : launch_drive_phasors<double>(h, 0, 1, h->stream);
+        e = cfg->precision == PHX_C64 ? launch_drive_phasors<float>(h, 0, 2, h->stream)
+                                      : launch_drive_phasors<double>(h, 0, 2, h->stream);
     if (e == hipSuccess && cfg->imag_time)  // valid norm target and scale before any launch
         e = cfg->precision == PHX_C64 ? launch_imag_norm<float>(h, f->psi, 0, h->stream)
                                       : launch_imag_norm<double>(h, f->psi, 0, h->stream);
@@ -460,14 +468,6 @@ phx_status phx_create(const phx_config* cfg, const phx_fields* f, void* stream,
         return fail(PHX_EHIP, "phx_create: %s", hipGetErrorString(e));
     }
     memset(h->host, 0, (OBS_SLOTS + 2) * sizeof(double));
-    h->cur = f->psi;
-    h->stage_tiles = L.tiles;
-    {
-        h->step_shape = default_step_shape(*cfg);
-        h->lone_shape = default_lone_shape(*cfg);
-        if (cfg->tile_wx != 0 && L.family == PHX_KERNEL_STEP)
-            h->step_shape = h->lone_shape = StepShapeId{cfg->tile_wx, cfg->tile_rows};
-    }
     if (cfg->integrator == PHX_RK45) {
         s = create_rk45(h);
         if (s != PHX_OK) {
