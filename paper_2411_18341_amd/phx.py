@@ -380,9 +380,15 @@ def tune_cache_path() -> str:
     return os.environ.get("PHX_TUNE_CACHE") or os.path.join(os.path.expanduser("~"), ".cache", "phx_tune.json")
 
 
+# Counts the changes of what a shape runs as; records of another revision are not used.
+TUNE_REVISION = 2
+
+
 def tune_key(cfg: phx_config, has_v: bool, device_name: str = "") -> str:
-    return (f"{device_name}|k{cfg.kernel}|p{cfg.precision}|{cfg.nx}x{cfg.ny}|c{cfg.components}|"
-            f"r{cfg.reservoir}|v{int(has_v)}|bc{cfg.bc_x}{cfg.bc_y}")
+    """What the fastest shape depends on: the device, the grid and every term of the step."""
+    return (f"{device_name}|rev{TUNE_REVISION}|k{cfg.kernel}|p{cfg.precision}|i{cfg.integrator}|{cfg.nx}x{cfg.ny}|"
+            f"c{cfg.components}|r{cfg.reservoir}|v{int(has_v)}|bc{cfg.bc_x}{cfg.bc_y}|"
+            f"noise{int(cfg.noise > 0)}|drive{cfg.drive}|imag{cfg.imag_time}")
 
 
 def _read_cache(path):
@@ -488,16 +494,27 @@ class Solver:
             if shp is not None and shp != (self.cfg.tile_wx, self.cfg.tile_rows):
                 cfg = phx_config.from_buffer_copy(self.cfg)
                 cfg.tile_wx, cfg.tile_rows = shp
-                phx_destroy(self.handle)
-                self.cfg = cfg
-                self.handle = phx_create(cfg, self.fields, self.stream.cuda_stream)
-                return {"tile_wx": shp[0], "tile_rows": shp[1], "cached": True}
+                if self._recreate(cfg):
+                    return {"tile_wx": shp[0], "tile_rows": shp[1], "cached": True}
         r = phx_autotune(self.handle, reps)
         if use_cache:
             store_shape(self.cfg, has_v, r, dev)
         d = r.as_dict()
         d["cached"] = False
         return d
+
+    def _recreate(self, cfg: phx_config) -> bool:
+        """Bind a new handle with configuration cfg and this one's progress; False, with this
+        handle still in place, if the library refuses cfg."""
+        info = phx_get_info(self.handle)
+        try:
+            handle = phx_create(cfg, self.fields, self.stream.cuda_stream)
+        except PhxError:
+            return False
+        old, self.handle, self.cfg = self.handle, handle, cfg
+        phx_destroy(old)
+        phx_set_info(handle, info)
+        return True
 
     def close(self):
         if getattr(self, "handle", None):
