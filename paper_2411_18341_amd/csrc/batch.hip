@@ -298,6 +298,14 @@ __global__ __launch_bounds__(256) void batch_table_kernel(const TableChunk<R> c,
     if (c.first == 0 && threadIdx.x < 64) flag[threadIdx.x] = 0u;
 }
 
+// Consecutive instances on grids of one size: the band heights are planned once per run (400
+// grids of 65^2, one step: 82 us per call with the plan of each, 65 now), and from at most 512
+// of many runs (2000 different complex128 grids of 20 to 60 rows, one step: 179 us per call
+// with all of them).
+struct GridRun {
+    int nx, ny, count;
+};
+
 template <typename R>
 static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stream)
 {
@@ -318,8 +326,13 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     // tallest bands of the walks: the candidates that give the shortest list; the search ends
     // at once where tall bands already make kFullLists waves per SIMD (45 us of host time for
     // 256 instances), and a walk that the call does not use is not planned
+    std::vector<GridRun> runs;
     for (int k = 0; k < d->count; ++k) {
         const phx_instance& I = d->instances[k];
+        if (runs.empty() || I.nx != runs.back().nx || I.ny != runs.back().ny)
+            runs.push_back(GridRun{I.nx, I.ny, 1});
+        else
+            ++runs.back().count;
         const phx_config& c = d->params[I.param_index];
         use_stream = use_stream && (double)I.nx * I.ny * 2.0 * sizeof(R) < 2147483648.0 - 256.0;
         all_zero_y = all_zero_y && c.bc_y == PHX_BC_ZERO;
@@ -342,16 +355,20 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     const bool weigh = plan_pairs && f64 && !res;
     const bool plan_steps = !plan_pairs || weigh || 2 * pair_launches(n) < n;
     double s_work = 0.0, p_work = 0.0;  // positions of all items
-    const int64_t full = (int64_t)kFullLists * 4 * cus;
-    int s_cap = 64, p_cap = 56;
+    const int64_t full = (int64_t)kFullLists * 4 * cus, every = 1 + (int64_t)runs.size() / 256;  // of the runs looked at
+    // complex128: 256 noisy grids of 100^2 to 600^2, four steps, 1083 us with bands of up to 64
+    // rows, 1045 with 40
+    const int s_tallest = f64 ? 40 : 64;
+    int s_cap = s_tallest, p_cap = 56;
     double s_best = 0.0, p_best = 0.0;
-    for (int cap = 64; plan_steps && cap >= 8; cap -= 8) {
+    for (int cap = s_tallest; plan_steps && cap >= 8; cap -= 8) {
         int64_t waves = 0;
-        for (int k = 0; k < d->count; ++k) {
-            const phx_instance& I = d->instances[k];
-            const int cols = step_cols(sizeof(R) == 4 && I.nx % 2 == 0 ? 2 : 1), band = batch_step_band(I.ny, cap);
-            waves += (int64_t)((I.nx + cols - 1) / cols) * ((I.ny + band - 1) / band);
+        for (size_t i = 0; i < runs.size(); i += every) {
+            const GridRun& g = runs[i];
+            const int cols = step_cols(sizeof(R) == 4 && g.nx % 2 == 0 ? 2 : 1), band = batch_step_band(g.ny, cap);
+            waves += (int64_t)g.count * ((g.nx + cols - 1) / cols) * ((g.ny + band - 1) / band);
         }
+        waves *= every;
         const double cost = list_cost(waves, cap + 4, 4 * cus);
         if (s_best == 0.0 || cost < s_best) {
             s_best = cost;
@@ -362,12 +379,14 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     for (int cap = 56; plan_pairs && cap >= 8; cap -= 12) {
         int64_t waves = 0;
         int tallest = 0;
-        for (int k = 0; k < d->count; ++k) {
+        for (size_t i = 0; i < runs.size(); i += every) {
+            const GridRun& g = runs[i];
             int w, strips, band;
-            batch_pair_plan(sizeof(R) == 4, two, d->instances[k].nx, d->instances[k].ny, cap, &w, &strips, &band);
-            waves += (int64_t)strips * ((d->instances[k].ny + band - 1) / band);
+            batch_pair_plan(sizeof(R) == 4, two, g.nx, g.ny, cap, &w, &strips, &band);
+            waves += (int64_t)g.count * strips * ((g.ny + band - 1) / band);
             tallest = std::max(tallest, band);
         }
+        waves *= every;
         const double cost = list_cost(waves, tallest + 7, 4 * cus);
         if (p_best == 0.0 || cost < p_best) {
             p_best = cost;
@@ -376,6 +395,7 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         if (waves >= full) break;
     }
     int64_t s_tile0[2] = {0, 0}, p_tile0[2] = {0, 0};  // work items with one and two columns per lane
+    int w = 1, p_strips = 1, p_band = 1;
     for (int k = 0; k < d->count; ++k) {
         const phx_instance& I = d->instances[k];
         phx_config c = d->params[I.param_index];
@@ -398,9 +418,10 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
         const int sw = sizeof(R) == 4 && I.nx % 2 == 0 ? 2 : 1;
         b.s_strips = (I.nx + step_cols(sw) - 1) / step_cols(sw);
         b.s_band = batch_step_band(I.ny, s_cap);
-        int w = 1;
-        b.p_strips = b.p_band = 1;
-        if (plan_pairs) batch_pair_plan(sizeof(R) == 4, two, I.nx, I.ny, p_cap, &w, &b.p_strips, &b.p_band);
+        if (plan_pairs && (k == 0 || I.nx != table[k - 1].nx || I.ny != table[k - 1].ny))
+            batch_pair_plan(sizeof(R) == 4, two, I.nx, I.ny, p_cap, &w, &p_strips, &p_band);
+        b.p_strips = p_strips;
+        b.p_band = p_band;
         for (int l = 0; l < 2; ++l) {
             b.s_tile0[l] = (int)std::min<int64_t>(s_tile0[l], INT32_MAX);
             b.p_tile0[l] = (int)std::min<int64_t>(p_tile0[l], INT32_MAX);
