@@ -149,10 +149,21 @@ def hipcc() -> str:
     return path
 
 
+def _check_listing(src: str, asm: str) -> None:
+    """Raises if a store of the unit's device assembly can lose its data (see above)."""
+    found = store_data_hazards(asm)
+    if found:
+        raise RuntimeError(f"{src}: stores whose data the next instruction rewrites: {found}")
+
+
 def _compile(src: str) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
+    """Object file of one source; its device assembly and its kernels' resources are checked."""
+    stem = os.path.splitext(src)[0]
+    work = os.path.join(BUILD_DIR, stem + ".tmp")  # -save-temps leaves a dozen files beside the object
+    os.makedirs(work, exist_ok=True)
+    obj = os.path.join(work, stem + ".o")
     extra = EXTRA_FLAGS.get(src, []) + ([_USAGE] if src in STREAM_SOURCES else [])
-    cmd = [hipcc(), *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [hipcc(), *FLAGS, *extra, "-save-temps=obj", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
@@ -166,7 +177,12 @@ def _compile(src: str) -> str:
                  and not re.match(r"^\s*\d*\s*\|", l) and not l.startswith("In file included")]
         if lines:
             sys.stderr.write("\n".join(lines) + "\n")
-    return obj
+    with open(os.path.join(work, f"{stem}-hip-amdgcn-amd-amdhsa-{ARCH}.s")) as f:
+        _check_listing(src, f.read())
+    out = os.path.join(BUILD_DIR, stem + ".o")
+    os.replace(obj, out)
+    shutil.rmtree(work)
+    return out
 
 
 def build(jobs: int = 8) -> str:

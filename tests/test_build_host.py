@@ -71,6 +71,18 @@ def test_store_hazard_scan_on_a_listing():
     assert [st.split()[1] for _, st, _ in wider] == ["v[8:11],", "v[12:15],", "v[24:27],"]
 
 
+def test_the_build_refuses_such_a_store(monkeypatch, tmp_path):
+    """Every unit's listing is checked as it is compiled."""
+    with pytest.raises(RuntimeError, match="rewrites"):
+        build._check_listing("x.hip", ASM)
+    build._check_listing("x.hip", ASM.replace("s4 offen nt", "0 offen nt\n\ts_nop 0"))
+    checked = []
+    monkeypatch.setattr(build, "_check_listing", lambda src, asm: checked.append((src, "s_endpgm" in asm)))
+    monkeypatch.setattr(build, "BUILD_DIR", str(tmp_path))
+    assert os.path.exists(build._compile("drive.hip"))
+    assert checked == [("drive.hip", True)] and os.listdir(tmp_path) == ["drive.o"]
+
+
 @pytest.mark.parametrize("unit", ["rk4_stream_wide.hip", "batch.hip"])
 def test_wide_kernel_stores_keep_their_data(unit):
     """Every 128-bit store of the wide streaming walk (single grid and batched) has at
