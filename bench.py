@@ -203,7 +203,7 @@ def main():
     import numpy as np
     import torch
 
-    from paper_2411_18341_amd import bytemodel, inputs, phx
+    from paper_2411_18341_amd import bytemodel, inputs, phx, profiling
 
     if not torch.cuda.is_available():
         print("bench.py needs a GPU", file=sys.stderr)
@@ -295,11 +295,8 @@ def main():
                          "GBps": nbytes / (avg_ms * 1e-3) / 1e9}
     dom = max(kernels, key=lambda k: kernels[k]["avg_us"] * kernels[k]["launches"])
     d = kernels[dom]
-    # counter measurements of the whole-step kernel are kept per region shape
-    shape_key = dom
-    if dom == "rk4_step" and tune is not None:
-        wx, rows = tune["tile_wx"], tune["tile_rows"]
-        shape_key = f"rk4_step_wide{8 if wx == 2 else 12}" if wx in (2, 3) else f"rk4_step_{wx}x{rows}"
+    # counter measurements of the whole-step kernel are kept per kernel, and per region shape
+    shape_key = dom if tune is None else profiling.step_kernel_kind(dom, tune["tile_wx"], tune["tile_rows"])
     # the drive and imaginary time change what the stage kernels read: their counter records
     # are separate files
     traffic = measured_traffic(shape_key, step_workload) if args.drive is None and not args.imag else None

@@ -47,31 +47,33 @@ def kernel_source_hash(sources=None) -> str:
 
 def kernel_kind(name: str) -> str:
     """Kernel kind as the solver's timing API names it (rk4_stage2, dp_stage7, ...),
-    the whole-step kernel with its shape (rk4_step_8x6: 8 waves x 6 rows; the
-    streaming form rk4_step_1x40: bands of 40 rows; the wide streaming form
-    rk4_step_wide8 / rk4_step_wide12 by its input ring, whatever its band height),
-    or a shortened name for other kernels."""
+    the region form of the whole-step kernel with its shape (rk4_step_8x6: 8 waves x
+    6 rows), the streaming walks whatever their columns and band height (rk4_step_walk,
+    rk4_step_pair, rk4_step_spinor), or a shortened name for other kernels."""
     m = re.search(r"(rk4_stage_kernel|dp_stage_kernel)<[^>]*?(\d+)>", name)
     if m:
         return ("rk4_stage" if m.group(1).startswith("rk4") else "dp_stage") + m.group(2)
-    m = re.search(r"rk4_stream_wide_kernel<[^>]*?, (\d+), \d+, \d+(?:, (?:true|false))*>", name)
-    if m:  # wide streaming form: named by its input ring (8: shapes 2 x B, 12: shapes 3 x B)
-        return f"rk4_step_wide{m.group(1)}"
     m = re.search(r"rk4_step_kernel<[^>]*?(\d+), (\d+)>", name)
     if m:
         return f"rk4_step_{m.group(1)}x{m.group(2)}"
-    m = re.search(r"rk4_stream(?:_drive)?_kernel<[^>]*?, (\d+)(?:, (?:true|false))?>", name)
-    if m:  # streaming form (also with the drive or in imaginary time): shape 1 x band rows
-        return f"rk4_step_1x{m.group(1)}"
     named = {"rk4_step_kernel": "rk4_step", "batch_step_kernel": "batch_step", "dp_restart_kernel": "dp_restart",
              "dp_err_sum_kernel": "dp_error", "dp_stream_kernel": "dp_step",
-             "rk4_stream_pair_kernel": "rk4_step_pair", "rk4_stream_step_kernel": "rk4_step_walk", "obs_pass1": "obs_pass1", "obs_pass2": "obs_pass2",
+             "rk4_stream_pair_kernel": "rk4_step_pair", "rk4_stream_step_kernel": "rk4_step_walk",
+             "rk4_stream_spinor_kernel": "rk4_step_spinor", "obs_pass1": "obs_pass1", "obs_pass2": "obs_pass2",
              "conv_fwd_kernel": "conv_fwd", "conv_bwd_weight_kernel": "conv_bwd_weight",
              "wiener_noise_kernel": "wiener_noise"}
     for k, v in named.items():
         if k in name:
             return v
     return name[:60]
+
+
+def step_kernel_kind(timing_kind: str, tile_wx: int, tile_rows: int) -> str:
+    """The kind (as kernel_kind names it) of the kernel that the timing API reports as
+    timing_kind for a one-component solver of this shape."""
+    if timing_kind != "rk4_step":
+        return timing_kind
+    return "rk4_step_walk" if tile_wx in (1, 2, 3) else f"rk4_step_{tile_wx}x{tile_rows}"
 
 
 def read_stats(path: str):
