@@ -93,3 +93,13 @@ def test_walk_and_stage_kernels_take_turns():
         run.close()
     assert abs(out[0][1] / out[1][1] - 1) <= 1e-10
     assert rel_l2(out[0][0], out[1][0]) <= 1e-9
+
+
+@pytest.mark.parametrize("bc", [(0, 0), (1, 1), (0, 1), (1, 0)])
+def test_spinor_reservoirs_without_a_potential(bc):
+    for nx, ny in ((51, 5), (101, 33), (7, 5)):
+        ph, *fields = case(2, True, False, nx, ny, bc, seed=nx)
+        q = quantize(C64, *fields)
+        psi, n, _ = one_step(ph, q, C64, phx.PHX_KERNEL_AUTO)
+        s_psi, s_n, _ = one_step(ph, q, C64, phx.PHX_KERNEL_STAGE)
+        assert rel_l2(psi, s_psi) <= 20 * EPS[C64] and rel_l2(n, s_n) <= 20 * EPS[C64], (nx, ny)
