@@ -451,7 +451,9 @@ static phx_status batch_run(const phx_batch_desc* d, int64_t n, hipStream_t stre
     hipError_t e = hipSuccess;
     unsigned int* flag = (unsigned int*)(ws + L.flag);
     constexpr int TN = TableChunk<R>::N;
-    const bool by_launch = d->count <= kTableLaunches * TN;
+    // a call that copies and waits for the list of the noise pass anyway copies a longer table
+    // too (64 noisy complex128 grids, one step: 156 us with four launches, 145 with the copy)
+    const bool by_launch = d->count <= (block_inst.empty() ? kTableLaunches : 1) * TN;
     for (int k = 0; by_launch && k < d->count; k += TN) {
         TableChunk<R> c;
         c.first = k;
