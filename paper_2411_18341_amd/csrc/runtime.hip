@@ -230,18 +230,17 @@ int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 // Two steps per launch where nothing has to happen between them (no noise, no norm to
 // restore): the wide form whose band height the library chooses, with two columns per
 // lane, and the one-column form with tall bands (1 x 64; the two-step walk picks its own
-// height).  Faster than single steps at every size.  us per step, driven, one against two
-// steps per launch: wide 92.8 / 59.4 at 4096^2, 31.7 / 20.4 at 2048^2, 12.9 / 12.2 at
-// 1024^2; one column, complex64 115.7 / 72.6 at 4095^2, 22.6 / 9.0 at 1024^2; complex128
-// 190.6 / 130.4 at 4096^2, 63.7 / 37.7 at 2047^2, 33.0 / 17.0 at 1023^2.  With the drive pairs
-// pay from 2^21 cells (one / two steps per launch, complex64: 9.2 / 11.5 at 513^2, 16.5 / 17.1
-// at 1024^2, 36.0 / 29.5 at 2048^2, 141 / 94 at 4096^2; complex128 20.2 / 31.6 at 1024^2, 57.9
-// / 44.6 at 2048^2): the profile's ring leaves registers for few waves.  In complex128 with
-// a potential as well they never do (2048^2, us per step, one / two steps per launch: 62 /
-// 68 with the reservoir, 44 / 45 to 49 without).  Undriven complex128 with a potential: from
-// 2^23 cells, where HBM bounds the single steps (without the reservoir 20.1 / 24.3 at 1536^2,
-// 26.4 / 28.0 at 2048^2, 62.3 / 59.1 at 3000^2, 127 / 105 at 4096^2; with it 28.8 / 31.8,
-// 52.0 / 52.3, 120 / 106, 216 / 209); see also pair_pays.
+// height).  us per step, driven, one / two steps per launch: two columns 9.3 / 11.9 at 1024^2,
+// 25.1 / 19.4 at 2048^2, 86.3 / 58.3 at 4096^2; one column, complex64 8.7 / 8.9 at 1024^2,
+// 26.0 / 20.4 at 2047^2, 114 / 69.5 at 4095^2; complex128 14.0 / 12.3 at 1023^2, 41.7 / 31.6 at
+// 2047^2, 179 / 112 at 4096^2.  With the drive pairs pay from 2^21 cells (complex64 23.6 / 23.3
+// at 1448^2, 30.7 / 26.7 at 2048^2, 141 / 89 at 4096^2; complex128 26.4 / 24.3 at 1449^2, 47.9 /
+// 42.9 at 2048^2, 235 / 161 at 4096^2): the profile's ring leaves registers for few waves.  In
+// complex128 with a potential as well they never do (2048^2: 62 / 68 with the reservoir, 44 /
+// 45 to 49 without).  Undriven complex128 with a potential: from 2^23 cells, where HBM bounds
+// the single steps (without the reservoir 20.1 / 24.3 at 1536^2, 26.4 / 28.0 at 2048^2, 62.3 /
+// 59.1 at 3000^2, 127 / 105 at 4096^2; with it 28.8 / 31.8, 52.0 / 52.3, 120 / 106, 216 / 209);
+// see also pair_pays.
 int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v)
 {
     if (c.components != 1 || c.imag_time || c.noise > 0.0) return 0;
@@ -257,16 +256,20 @@ int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v)
 
 // Shape used when the caller names none and does not tune: the region form on grids that
 // its many small workgroups fill better, the walks beyond.  us per step, driven: region
-// 8 x 4 / two steps with one column / with two columns per lane, complex64: 5.1 / 5.1 / - at
-// 512^2, 7.0 / 6.5 / 11.9 at 768^2, 10.4 / 9.0 / 12.1 at 1024^2, 20.5 / 13.7 / 16.7 at 1536^2,
-// 31.0 / 20.9 / 20.2 at 2048^2, - / 26.7 / 26.2 at 2400^2; with zero boundaries (region / one
-// column) 5.2 / 6.0 at 512^2, 10.8 / 10.9 at 1023^2, 20.7 / 14.9 at 1531^2; complex128
-// (region / one column): 6.4 / 10.7 at 512^2, 23.5 / 17.0 at 1023^2, 75.8 / 37.7 at 2047^2;
-// without the reservoir 15.3 / 16.2 at 1023^2, 27.9 / 23.7 at 1531^2.  With the noise the
-// steps are single: the wide form, which draws the increments itself, saves the separate
-// pass (2048^2 45.1 -> 36.7 us); in complex128 the one-column form takes 62 against 76 us at
-// 2047^2.  Imaginary time, complex64: two columns per lane from 2^21 cells (25.9 us against
-// 44.2 at 2048^2 and 69 against 100.7 at 4096^2 with one column and bands of 40 rows).
+// 8 x 4 / two steps with one column / with two columns per lane, complex64: 5.1 / 5.0 / 11.8 at
+// 512^2, 6.7 / 6.1 / 12.0 at 768^2, 10.2 / 8.9 / 12.1 at 1024^2, 20.3 / 13.6 / 17.0 at 1536^2,
+// 31.2 / 20.8 / 20.2 at 2048^2, 41.0 / 26.5 / 26.2 at 2400^2; with zero boundaries (region / one
+// column) 5.2 / 5.9 at 512^2, 10.6 / 10.8 at 1024^2, 20.0 / 14.7 at 1536^2; complex128
+// (region / one column): 6.1 / 9.1 at 512^2, 17.2 / 9.8 at 888^2, 22.6 / 12.9 at 1023^2, 72.6 /
+// 32.6 at 2047^2; without the reservoir 10.9 / 10.5 at 1023^2, 15.7 / 12.8 at 1254^2, with zero
+// boundaries 11.5 / 12.3 and 16.0 / 13.9.  A call of one or two steps takes the one-step walk
+// there, which is no slower than the region form: us per call, region / walk, 28 / 26 and 25 /
+// 23 at 1024^2, 36 / 35 and 46 / 42 at 1536^2; complex128 43 / 35 and 50 / 39 at 1023^2.  With
+// the noise the steps are single: the wide form, which draws the increments itself, saves the
+// separate pass (1024^2 16.1 -> 14.1, 2048^2 41.8 -> 34.2 us); in complex128 the one-column form
+// takes 34.6 against 41.2 us at 1254^2 and 77.7 against 91.9 at 2048^2.  Imaginary time,
+// complex64: two columns per lane from 2^21 cells (one / two columns 15.8 / 15.9 us at 1448^2,
+// 23.6 / 23.7 at 2048^2, 65.6 / 61.4 at 4096^2).
 StepShapeId default_step_shape(const phx_config& c)
 {
     const int64_t cells = (int64_t)c.nx * c.ny, k = (int64_t)1 << 18;
