@@ -218,13 +218,17 @@ StepPlan step_plan(const phx_config& c, const StepShapeId& sh, int cus)
 
 int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
 
-// Band height of the two-step form with w columns per lane.
+// Band height of the two-step form with w columns per lane.  With the reservoir and a potential
+// one wave on a SIMD issues at 0.67 of the rate (one complex64 column; us per position 0.77
+// with one wave, 0.53 per wave with two), so two waves with lower bands are the faster plan
+// (16 steps: 1024^2 190 -> 164 us, 1400^2 315 -> 260; with zero boundaries 221 -> 186, 362 -> 290).
 int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 {
     const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
     const int words = w * (c.precision == PHX_C64 ? 1 : 2);
     return band_fill(pair_strips(c.nx, w), c.ny, 16, 9, kPairLow[words], kPairStep[words], cus,
-                     pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts, c.drive != 0)).rows;
+                     pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts, c.drive != 0),
+                     words == 1 && c.reservoir && has_v ? 0.67 : 0.82).rows;
 }
 
 // Two steps per launch where nothing has to happen between them (no noise, no norm to
