@@ -191,7 +191,7 @@ hipError_t rk4_step_trial(phx_handle* h, const StepShapeId& sh, int k, int* step
 {
     const phx_config& c = h->cfg;
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
-    const int pair = pair_columns(c, sh, hv);
+    const int pair = pair_columns(c, sh, hv, h->cus);
     *steps = pair ? 2 : 1;
     char* A = h->ws + h->L.alt;
     char* An = res ? h->ws + h->L.alt_n : nullptr;
@@ -233,7 +233,7 @@ phx_status rk4_fused_launches(phx_handle* h, const StepShapeId& sh, int64_t n, h
     void* S[2] = {h->f.psi, h->ws + h->L.alt};
     void* SN[2] = {h->f.n, c.reservoir ? h->ws + h->L.alt_n : nullptr};
     const bool res = c.reservoir != 0, hv = h->f.V != nullptr;
-    const int columns = pair_columns(c, sh, hv);
+    const int columns = pair_columns(c, sh, hv, h->cus);
     int64_t pairs = columns ? pair_launches(n) : 0;
     int cur = h->step_parity;
     for (int64_t k = 0, steps = 1; k < n; k += steps) {
@@ -293,7 +293,7 @@ phx_status rk4_fused_steps(phx_handle* h, int64_t n)
     h->step_parity = 0;
     const int G = graph_chunk(c);
     const int64_t direct = h->timing || G == 0 || n < G ? n : n % G;  // steps after the graph replays
-    if ((n & 1) && !(pair_columns(c, h->step_shape, h->f.V != nullptr) && pair_launches(direct) > 0)) {
+    if ((n & 1) && !(pair_columns(c, h->step_shape, h->f.V != nullptr, h->cus) && pair_launches(direct) > 0)) {
         void* alt = h->ws + h->L.alt;
         if (hipMemcpyAsync(alt, h->f.psi, cells * c.components * 2 * rs, hipMemcpyDeviceToDevice, h->stream) !=
                 hipSuccess ||

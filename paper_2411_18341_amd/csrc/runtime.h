@@ -188,7 +188,7 @@ inline BandFill band_fill(int strips, int ny, int halo, int skipped, int lo, int
 // Two steps per launch of the streaming forms (stream_pair.h): the columns per lane with
 // which shape sh runs this way for this configuration (0: it takes single steps), the
 // strips and the band height.
-int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v);
+int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v, int cus);
 StepShapeId default_step_shape(const phx_config& c);
 StepShapeId default_lone_shape(const phx_config& c);
 int pair_strips(int nx, int w);

@@ -205,15 +205,19 @@ bool noise_in_step(const phx_config& c, const StepShapeId& sh)
 // of 16 rows, which the rates without the noise pick, 21.0 with 8).  Bands as tall as 88 rows
 // leave one wave per SIMD (2048^2 with the noise: 54.6 us per step, 39.4 with the height
 // chosen here).
+static BandFill step_fill(const phx_config& c, int w, bool noise, int cus)
+{
+    return band_fill((c.nx + step_cols(w) - 1) / step_cols(w), c.ny, 8, 4, 8, 8, cus,
+                     step_waves_per_simd(w, c.precision == PHX_C128, c.reservoir != 0, c.drive != 0),
+                     noise ? 0.76 : 0.5, noise ? 0.97 : 0.85);
+}
+
 StepPlan step_plan(const phx_config& c, const StepShapeId& sh, int cus)
 {
     const int w = wide_shape(sh.waves) ? 2 : 1;
     const int strips = (c.nx + step_cols(w) - 1) / step_cols(w);
     if (sh.rows > 0 && !(sh.waves == 1 && sh.rows >= 64)) return StepPlan{strips, sh.rows};
-    const bool noise = c.noise > 0.0 && noise_in_step(c, sh);
-    return StepPlan{strips, band_fill(strips, c.ny, 8, 4, 8, 8, cus,
-                                      step_waves_per_simd(w, c.precision == PHX_C128, c.reservoir != 0, c.drive != 0),
-                                      noise ? 0.76 : 0.5, noise ? 0.97 : 0.85).rows};
+    return StepPlan{strips, step_fill(c, w, c.noise > 0.0 && noise_in_step(c, sh), cus).rows};
 }
 
 int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); }
@@ -222,14 +226,16 @@ int pair_strips(int nx, int w) { return (nx + pair_cols(w) - 1) / pair_cols(w); 
 // one wave on a SIMD issues at 0.67 of the rate (one complex64 column; us per position 0.77
 // with one wave, 0.53 per wave with two), so two waves with lower bands are the faster plan
 // (16 steps: 1024^2 190 -> 164 us, 1400^2 315 -> 260; with zero boundaries 221 -> 186, 362 -> 290).
-int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
+static BandFill pair_fill(const phx_config& c, int w, bool has_v, int cus)
 {
     const bool ghosts = c.bc_x == PHX_BC_ZERO || c.bc_y == PHX_BC_ZERO;
     const int words = w * (c.precision == PHX_C64 ? 1 : 2);
     return band_fill(pair_strips(c.nx, w), c.ny, 16, 9, kPairLow[words], kPairStep[words], cus,
                      pair_waves_per_simd(words, c.reservoir != 0, has_v, ghosts, c.drive != 0),
-                     words == 1 && c.reservoir && has_v ? 0.67 : 0.82).rows;
+                     words == 1 && c.reservoir && has_v ? 0.67 : 0.82);
 }
+
+int pair_band_rows(const phx_config& c, int w, bool has_v, int cus) { return pair_fill(c, w, has_v, cus).rows; }
 
 // Two steps per launch where nothing has to happen between them (no noise, no norm to
 // restore): the wide form whose band height the library chooses, with two columns per
@@ -244,8 +250,11 @@ int pair_band_rows(const phx_config& c, int w, bool has_v, int cus)
 // 45 to 49 without).  Undriven complex128 with a potential: from 2^23 cells, where HBM bounds
 // the single steps (without the reservoir 20.1 / 24.3 at 1536^2, 26.4 / 28.0 at 2048^2, 62.3 /
 // 59.1 at 3000^2, 127 / 105 at 4096^2; with it 28.8 / 31.8, 52.0 / 52.3, 120 / 106, 216 / 209);
-// see also pair_pays.
-int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v)
+// see also pair_pays.  One complex64 column with the reservoir and a potential: below 2^21 cells
+// not where a pair walks 1.35 times the positions of a single step, which costs it more than the
+// launch that it saves (16 steps, single / pairs: 1.39 times at 888^2 127 / 154 us, with zero
+// boundaries 140 / 172; 1.32 at 1100^2 209 / 192; 1.09 at 1024^2 178 / 164 and 182 / 186).
+int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v, int cus)
 {
     if (c.components != 1 || c.imag_time || c.noise > 0.0) return 0;
     const int64_t cells = (int64_t)c.nx * c.ny;
@@ -254,6 +263,9 @@ int pair_columns(const phx_config& c, const StepShapeId& sh, bool has_v)
     if (!c64 && has_v && cells < ((int64_t)1 << 23)) return 0;
     const bool two = sh.waves == 2 && sh.rows == 0;
     if (!two && !(sh.waves == 1 && sh.rows == 64)) return 0;
+    if (c64 && !two && c.reservoir && has_v && cells < ((int64_t)1 << 21) &&
+        pair_fill(c, 1, has_v, cus).cost > 1.35 * step_fill(c, 1, false, cus).cost)
+        return 0;
     if (pair_pays(two || !c64 ? 2 : 1, c.reservoir != 0, has_v, ghosts)) return two ? 2 : 1;
     return c64 ? 1 : 0;
 }

@@ -139,7 +139,7 @@ def steps_us(s, steps):
     return best
 
 
-@pytest.mark.parametrize("nx,bc", [(1400, (0, 0)), (1400, (1, 1)), (1024, (0, 0))])
+@pytest.mark.parametrize("nx,bc", [(1400, (0, 0)), (1400, (1, 1)), (1024, (0, 0)), (888, (0, 0))])
 def test_default_shape_with_a_potential(nx, bc):
     """16 steps of the shape chosen by default take no longer (4 %, the spread of such runs) than
     on the region form.  (Bands planned at the rate of walks without a potential left one wave per
