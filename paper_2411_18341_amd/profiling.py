@@ -49,13 +49,21 @@ def kernel_kind(name: str) -> str:
     """Kernel kind as the solver's timing API names it (rk4_stage2, dp_stage7, ...),
     the region form of the whole-step kernel with its shape (rk4_step_8x6: 8 waves x
     6 rows), the streaming walks whatever their columns and band height (rk4_step_walk,
-    rk4_step_pair, rk4_step_spinor), or a shortened name for other kernels."""
+    rk4_step_pair, rk4_step_spinor), or a shortened name for other kernels.  Profiles of
+    earlier libraries name kernels that are gone: rk4_step_1x40 (a streaming form with bands
+    of 40 rows), rk4_step_wide8 and rk4_step_wide12 (a wide one by its input ring)."""
     m = re.search(r"(rk4_stage_kernel|dp_stage_kernel)<[^>]*?(\d+)>", name)
     if m:
         return ("rk4_stage" if m.group(1).startswith("rk4") else "dp_stage") + m.group(2)
+    m = re.search(r"rk4_stream_wide_kernel<[^>]*?, (\d+), \d+, \d+(?:, (?:true|false))*>", name)
+    if m:
+        return f"rk4_step_wide{m.group(1)}"
     m = re.search(r"rk4_step_kernel<[^>]*?(\d+), (\d+)>", name)
     if m:
         return f"rk4_step_{m.group(1)}x{m.group(2)}"
+    m = re.search(r"rk4_stream(?:_drive)?_kernel<[^>]*?, (\d+)(?:, (?:true|false))?>", name)
+    if m:
+        return f"rk4_step_1x{m.group(1)}"
     named = {"rk4_step_kernel": "rk4_step", "batch_step_kernel": "batch_step", "dp_restart_kernel": "dp_restart",
              "dp_err_sum_kernel": "dp_error", "dp_stream_kernel": "dp_step",
              "rk4_stream_pair_kernel": "rk4_step_pair", "rk4_stream_step_kernel": "rk4_step_walk",
